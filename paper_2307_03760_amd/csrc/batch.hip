@@ -28,6 +28,9 @@ __global__ void reset_queue(uint32_t *head) {
     if (threadIdx.x == 0) *head = 0;
 }
 
+// One input buffer for every codec's ring.
+constexpr uint32_t kBatchRingWords = kRingLdsWords > kRoundInWords ? kRingLdsWords : kRoundInWords;
+
 // Each wave claims `claim` consecutive queue positions at a time (one
 // atomic add for several small chunks) until the queue is empty.  Every
 // store of a per-chunk result is made by all lanes with the same value (a
@@ -38,7 +41,7 @@ __global__ void __launch_bounds__(kWave * WPB)
     decode_batch(const uint8_t *codecs, const uint8_t *comp, const uint64_t *coff, uint8_t *out,
                  const uint64_t *ooff, uint32_t n, const uint32_t *order, uint32_t *head,
                  uint32_t claim, int32_t *status, unsigned long long *err, uint64_t *ticks) {
-    __shared__ __align__(16) uint32_t s_ring[WPB][kRingLdsWords];
+    __shared__ __align__(16) uint32_t s_ring[WPB][kBatchRingWords];
     __shared__ __align__(16) uint32_t s_land[WPB][kLandWords];
     __shared__ __align__(16) WaveScratch<CODAG_DEFLATE, TB, H> s_scratch[WPB];
     const uint32_t wave = uni(threadIdx.x / kWave);
@@ -86,7 +89,7 @@ __global__ void __launch_bounds__(kWave * WPB)
 
 template <int TB, uint32_t H>
 constexpr uint32_t batch_lds_per_wave() {
-    return (uint32_t)(4 * kRingLdsWords + 4 * kLandWords + sizeof(WaveScratch<CODAG_DEFLATE, TB, H>));
+    return (uint32_t)(4 * kBatchRingWords + 4 * kLandWords + sizeof(WaveScratch<CODAG_DEFLATE, TB, H>));
 }
 
 }  // namespace codag

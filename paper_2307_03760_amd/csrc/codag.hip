@@ -137,10 +137,7 @@ int launch_deflate(const uint8_t *comp, const uint64_t *coff, uint8_t *out, cons
     if (hist_kib == 16)
         return launch_plain<CODAG_DEFLATE, TB, 16384>(comp, coff, out, ooff, n, wpb, status, err,
                                                       ticks, stream);
-    if (hist_kib == 2)
-        return launch_plain<CODAG_DEFLATE, TB, 2048>(comp, coff, out, ooff, n, wpb, status, err,
-                                                     ticks, stream);
-    if (hist_kib == 4)
+    if (hist_kib <= 4)  // the linear window is at least 4 KiB
         return launch_plain<CODAG_DEFLATE, TB, 4096>(comp, coff, out, ooff, n, wpb, status, err,
                                                      ticks, stream);
     if (hist_kib == 32)

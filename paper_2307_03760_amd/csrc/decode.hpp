@@ -50,7 +50,7 @@ struct RingOf<CODAG_LZ4> {
 // for the kernels' arrays).
 template <int Codec>
 constexpr uint32_t ring_lds_words() {
-    return RingOf<Codec>::T::kLdsWords;
+    return Codec == CODAG_DEFLATE ? kRoundInWords : RingOf<Codec>::T::kLdsWords;
 }
 template <int Codec>
 constexpr uint32_t land_lds_words() {

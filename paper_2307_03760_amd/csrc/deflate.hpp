@@ -2,10 +2,12 @@
 //
 // CODAG (Section II-A, III) locates Deflate's cost in Huffman decoding and
 // dictionary copies.  Here:
-//   * The symbol chain is wave-uniform scalar code: a 64-bit bit buffer in
-//     scalar registers, refilled one 32-bit word at a time from the LDS input
-//     ring, and one lookup per symbol in LDS tables that the whole wave builds
-//     in parallel for each block.
+//   * A block's symbols are decoded by all lanes at once, each lane decoding
+//     its own stretch of the input with lookups in LDS tables that the whole
+//     wave builds in parallel for each block (inflate_lanes below).  Headers
+//     and whatever is rare are wave-uniform scalar code: a 64-bit bit buffer
+//     in scalar registers, refilled one 32-bit word at a time from the LDS
+//     input ring.
 //   * Output goes first to a per-wave history window in LDS (the last H bytes
 //     of output) and reaches HBM behind the decoder, 1 KiB at a time, as one
 //     16-byte store per lane of an aligned kilobyte ("coalesced on-demand
@@ -22,54 +24,69 @@
 
 namespace codag {
 
-// Table entry (16 bits): bits 0-3 code length, 4-12 symbol, 13-15 kind.
-enum : uint32_t {
-    kLit = 0,      // literal byte (symbol 0..255)
-    kBase = 1,     // length symbol 257..285, or distance symbol 0..29
-    kEob = 2,      // end of block
-    kSlow = 3,     // code longer than the table: canonical decode
-    kInvalid = 4,  // no code starts with these bits
-    kBadSym = 5,   // a code for a symbol that may not appear (286, 287; 30, 31)
-    kSym = 6,      // code-length alphabet symbol
-};
-
-__device__ __forceinline__ uint32_t entry16(uint32_t kind, uint32_t len, uint32_t sym) {
-    return len | (sym << 4) | (kind << 13);
-}
+// Table entry (32 bits).  Bits 0-4: input bits of the code and its extra bits
+// together; 5-8: code length; 9-12: extra-bit count.
+//   literal/length table: 12-20 output bytes (1 for a literal, the base
+//     length for a copy; ex is at most 5, bits 9-11), 21-28 the literal;
+//   distance table: 13-27 the base distance;
+//   code-length table: 13-17 the symbol.
+// With kEntStop, bits 21-22 say why: end of block, no code starts with these
+// bits, or a code for a symbol that may not appear (286, 287; 30, 31).
+// Everything a token needs is in its two entries, so decoding a token takes
+// no arithmetic on symbols (16-bit entries with the bases in closed form
+// cost about 20 more vector instructions per candidate).
+constexpr uint32_t kEntSlow = 1u << 29;  // code longer than the table: canonical decode
+constexpr uint32_t kEntStop = 1u << 30;
+constexpr uint32_t kEntCopy = 1u << 31;  // length symbol
+enum : uint32_t { kWhyEob = 1, kWhyInvalid = 2, kWhyBadSym = 3 };
+constexpr uint32_t kEntInvalid = kEntStop | (kWhyInvalid << 21);
 
 enum TableUse { kLitLen = 0, kDist = 1, kCodeLen = 2 };
 
-__device__ __forceinline__ uint32_t symbol_kind(int use, uint32_t s) {
-    if (use == kCodeLen) return kSym;
-    if (use == kLitLen) return s < 256 ? kLit : s == 256 ? kEob : s <= 285 ? kBase : kBadSym;
-    return s <= 29 ? kBase : kBadSym;
+__device__ __forceinline__ uint32_t ent_bits(uint32_t e) { return e & 31; }
+__device__ __forceinline__ uint32_t ent_cl(uint32_t e) { return (e >> 5) & 15; }
+__device__ __forceinline__ uint32_t ent_ex(uint32_t e) { return (e >> 9) & 15; }     // distance entries
+__device__ __forceinline__ uint32_t ent_lex(uint32_t e) { return (e >> 9) & 7; }     // literal/length entries
+__device__ __forceinline__ uint32_t ent_len(uint32_t e) { return (e >> 12) & 511; }
+__device__ __forceinline__ uint32_t ent_byte(uint32_t e) { return (e >> 21) & 255; }
+__device__ __forceinline__ uint32_t ent_why(uint32_t e) { return (e >> 21) & 3; }
+__device__ __forceinline__ uint32_t ent_dist(uint32_t e) { return (e >> 13) & 0x7fff; }
+__device__ __forceinline__ uint32_t ent_sym(uint32_t e) { return (e >> 13) & 31; }   // code lengths
+
+// Length and distance bases and extra-bit counts (RFC 1951 section 3.2.5)
+// in closed form.
+__device__ __forceinline__ uint32_t length_extra(uint32_t k) {  // k = symbol - 257
+    return (k < 8 || k == 28) ? 0 : (k >> 2) - 1;
+}
+__device__ __forceinline__ uint32_t length_base(uint32_t k) {
+    return k < 8 ? k + 3 : k == 28 ? 258 : ((4 + (k & 3)) << ((k >> 2) - 1)) + 3;
+}
+__device__ __forceinline__ uint32_t dist_extra(uint32_t d) { return d < 4 ? 0 : (d >> 1) - 1; }
+__device__ __forceinline__ uint32_t dist_base(uint32_t d) {
+    return d < 4 ? d + 1 : ((2 + (d & 1)) << ((d >> 1) - 1)) + 1;
 }
 
-// Base value and extra-bit count of length symbols 257..285 (lane k holds
-// symbol 257 + k) and distance symbols 0..29 (lane k holds symbol k), packed
-// as base | extra << 16 (RFC 1951 section 3.2.5).
-__device__ __forceinline__ uint32_t length_lane_table() {
-    uint32_t k = lane();
-    if (k >= 29) return 0;
-    if (k == 28) return 258;
-    if (k < 8) return k + 3;
-    uint32_t e = (k >> 2) - 1;
-    return (((4 + (k & 3)) << e) + 3) | (e << 16);
-}
-__device__ __forceinline__ uint32_t distance_lane_table() {
-    uint32_t k = lane();
-    if (k >= 30) return 0;
-    if (k < 4) return k + 1;
-    uint32_t e = (k >> 1) - 1;
-    return (((2 + (k & 1)) << e) + 1) | (e << 16);
+// The entry of symbol s with a code of cl bits.
+__device__ __forceinline__ uint32_t table_entry(int use, uint32_t s, uint32_t cl) {
+    if (use == kCodeLen) return cl | (cl << 5) | (s << 13);
+    if (use == kLitLen) {
+        if (s < 256) return cl | (cl << 5) | (1u << 12) | (s << 21);
+        if (s == 256) return cl | (cl << 5) | kEntStop | (kWhyEob << 21);
+        if (s > 285) return cl | (cl << 5) | kEntStop | (kWhyBadSym << 21);
+        const uint32_t ex = length_extra(s - 257);
+        return (cl + ex) | (cl << 5) | (ex << 9) | (length_base(s - 257) << 12) | kEntCopy;
+    }
+    if (s > 29) return cl | (cl << 5) | kEntStop | (kWhyBadSym << 21);
+    const uint32_t ex = dist_extra(s);
+    return (cl + ex) | (cl << 5) | (ex << 9) | (dist_base(s) << 13);
 }
 
-// Per-code metadata for the slow path: count, first code and offset into
-// `sorted` for each code length 1..15.
+// Canonical decoding of one code: codes of length k, left-aligned to 15
+// bits, lie below lim[k] (and at or above lim[k - 1]); their symbols are
+// sorted[base[k] + code].
 struct CodeMeta {
-    uint32_t count[16];
-    uint32_t first[16];
-    uint32_t offs[16];
+    uint32_t lim[16];
+    uint32_t base[16];
 };
 
 struct BuildResult {
@@ -82,7 +99,7 @@ struct BuildResult {
 // are lens[0..n) (n <= 320), lane-parallel: per-length counts and each
 // symbol's rank come from ballots, then every symbol fills its table slots.
 __device__ __forceinline__ BuildResult build_table(const uint8_t *lens, uint32_t n, uint32_t tb,
-                                                   int use, uint16_t *tab, uint16_t *sorted,
+                                                   int use, uint32_t *tab, uint16_t *sorted,
                                                    CodeMeta *meta) {
     const uint32_t l = lane();
     uint32_t cnt[16];
@@ -114,44 +131,45 @@ __device__ __forceinline__ BuildResult build_table(const uint8_t *lens, uint32_t
     r.total = total;
     r.ones = cnt[1];
     if (left < 0) return r;
-    if (l < 16) {
-        uint32_t code = 0, off = 0, c = 0, f = 0, o = 0;
+    {
+        uint32_t code = 0, off = 0, lim = 0, base = 0;
 #pragma unroll
         for (int len = 1; len < 16; len++) {
             if ((uint32_t)len == l) {
-                c = cnt[len];
-                f = code;
-                o = off;
+                lim = (code + cnt[len]) << (15 - len);
+                base = off - code;
             }
             off += cnt[len];
             code = (code + cnt[len]) << 1;
         }
-        meta->count[l] = c;
-        meta->first[l] = f;
-        meta->offs[l] = o;
+        if (l < 16) {
+            meta->lim[l] = lim;
+            meta->base[l] = base;
+        }
     }
     if (left > 0) {  // incomplete: codes not in the set are invalid
-        for (uint32_t i = l; i < (1u << tb); i += kWave) tab[i] = (uint16_t)entry16(kInvalid, 0, 0);
+        for (uint32_t i = l; i < (1u << tb); i += kWave) tab[i] = kEntInvalid;
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
 #pragma unroll
     for (int p = 0; p < 5; p++) {
         uint32_t s = 64 * p + l;
         uint32_t m = s < n ? lens[s] : 0;
         if (m != 0) {
-            uint32_t code = meta->first[m] + rank[p];
-            sorted[meta->offs[m] + rank[p]] = (uint16_t)s;
+            // The first code of length m is the limit below it at m bits.
+            const uint32_t code = (meta->lim[m - 1] >> (15 - m)) + rank[p];
+            sorted[meta->base[m] + code] = (uint16_t)s;
             if (m <= tb) {
                 uint32_t rev = __builtin_bitreverse32(code) >> (32 - m);
-                uint16_t e = (uint16_t)entry16(symbol_kind(use, s), m, s);
+                const uint32_t e = table_entry(use, s, m);
                 for (uint32_t k = 0; k < (1u << (tb - m)); k++) tab[rev | (k << m)] = e;
             } else {
                 uint32_t prefix = code >> (m - tb);
-                tab[__builtin_bitreverse32(prefix) >> (32 - tb)] = (uint16_t)entry16(kSlow, 0, 0);
+                tab[__builtin_bitreverse32(prefix) >> (32 - tb)] = kEntSlow;
             }
         }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     return r;
 }
 
@@ -162,17 +180,33 @@ constexpr uint32_t kCodeLenBits = 7;
 __constant__ const uint8_t kCodeLenOrder[19] = {16, 17, 18, 0, 8,  7, 9,  6, 10, 5,
                                                 11, 4,  12, 3, 13, 2, 14, 1, 15};
 
-// What one wave keeps in LDS while inflating, besides the input ring: the
-// Huffman tables and the output history window.
+// A round of the lane-parallel decoder takes 64 lanes x 256 bits of input,
+// each lane's share cut into four segments of 64 bits.
+constexpr uint32_t kLaneBits = 256, kSegBits = 64, kLaneSegs = kLaneBits / kSegBits;
+constexpr uint32_t kRoundSegs = kWave * kLaneSegs;
+// The round's input: 64 x 32 bytes, up to 8 bytes of alignment before them
+// and the eight-byte reads past the last bit, in 16-byte pieces.
+constexpr uint32_t kRoundPieces = 130, kRoundInWords = 4 * kRoundPieces;
+constexpr uint32_t kCopyQueue = 160;  // copies of one emission step
+
+// What one wave keeps in LDS while inflating, besides its input: the Huffman
+// tables, the output history window and the lane-parallel decoder's lists.
+// (The window comes first: LZ4 uses a Deflate slice's.)
 template <int TB, uint32_t H>
 struct DeflateLds {
-    uint8_t window[H];  // output byte at absolute address a lives at window[a % H]
-    uint16_t lit[1u << TB];
-    uint16_t dist[1u << kDistBits];  // also the code-length table (7 bits)
+    uint8_t window[H];
+    uint8_t window_pad[16];  // eight-byte reads may pass the window's end
+    uint32_t lit[1u << TB];
+    uint32_t dist[1u << kDistBits];  // also the code-length table (7 bits)
     CodeMeta lit_meta, dist_meta;
     uint16_t lit_sorted[288];
     uint16_t dist_sorted[32];
-    uint8_t lens[320];
+    union {
+        uint8_t lens[320];          // while a block's tables are built
+        uint32_t segs[kRoundSegs];  // while its symbols decode
+    };
+    uint32_t queue[kCopyQueue];
+    uint16_t queue_dst[kCopyQueue];
 };
 
 // Wave-uniform LSB-first bit reader over the ring.
@@ -241,20 +275,20 @@ struct BitIn {
     __device__ __forceinline__ uint32_t byte_pos() const { return next - cnt / 8; }
 };
 
-// Canonical decode of a code longer than the table (CODAG's "Huffman tree
-// traversal"): extends the code one bit at a time through lengths 1..15.
-__device__ __forceinline__ uint32_t slow_symbol(const BitIn &bi, const CodeMeta *meta,
-                                                const uint16_t *sorted, int use) {
-    uint32_t code = 0, bits = (uint32_t)bi.buf;
-    for (uint32_t len = 1; len < 16; len++) {
-        code = (code << 1) | ((bits >> (len - 1)) & 1);
-        uint32_t c = uni(meta->count[len]), f = uni(meta->first[len]);
-        if (code - f < c) {
-            uint32_t s = uni((uint32_t)sorted[uni(meta->offs[len]) + code - f]);
-            return entry16(symbol_kind(use, s), len, s);
-        }
-    }
-    return entry16(kInvalid, 0, 0);
+// Canonical decode of a code longer than a table of tb bits (CODAG's
+// "Huffman tree traversal"): the code's length is where its bits, left-
+// aligned, fall below that length's limit.  x holds the next 15 bits at
+// least; per lane, and the same code serves the wave-uniform reader.
+__device__ __forceinline__ uint32_t slow_entry(uint32_t x, uint32_t tb, const CodeMeta *meta,
+                                               const uint16_t *sorted, int use) {
+    const uint32_t rev = __builtin_bitreverse32(x) >> 17;
+    uint32_t len = tb + 1;
+#pragma unroll
+    for (uint32_t k = 1; k < 16; k++)
+        if (k > tb) len += rev >= meta->lim[k] ? 1u : 0u;
+    if (len > 15) return kEntInvalid;
+    const uint32_t at = meta->base[len] + (rev >> (15 - len));
+    return table_entry(use, sorted[min(at, use == kLitLen ? 287u : 31u)], len);
 }
 
 // Single-byte LDS writes in the decode loops are issued by all lanes with
@@ -368,11 +402,107 @@ struct WindowOut {
     }
 };
 
+// The Deflate decoders' output: as WindowOut, but the window is linear.  It
+// holds offsets [wlo, o0 + pos) at win[x - wlo]; when an append would pass
+// its end, the complete kilobytes are flushed and the newest ones slide to
+// the front, so runs of bytes never wrap and may be read and written eight
+// at a time at any alignment.  wlo and fa are multiples of 1 KiB, and
+// everything below wlo + 512 is in HBM once wlo > 0 (appends are of at most
+// kAppend bytes), so a copy whose source starts below wlo reads HBM alone.
+template <uint32_t H>
+struct LinearOut {
+    static_assert(H >= 4096, "an append, a slide and a copy must fit");
+    static constexpr uint32_t kAppend = H - 2560;
+    uint8_t *base;  // 1 KiB aligned
+    uint8_t *win;
+    uint32_t o0, wlo, fa, cap, pos, room;
+
+    __device__ __forceinline__ void init(uint8_t *out, uint32_t capacity, uint8_t *window) {
+        o0 = (uint32_t)(reinterpret_cast<uintptr_t>(out) & 1023);
+        base = out - o0;
+        win = window;
+        wlo = 0;
+        fa = 0;
+        cap = capacity;
+        pos = 0;
+        room = H - o0;
+    }
+    // (The mask keeps the slot of an offset outside the window in bounds.)
+    __device__ __forceinline__ uint32_t slot(uint32_t x) const { return (x - wlo) & (H - 1); }
+
+    __device__ __forceinline__ void flush_block(uint32_t limit) {
+        const uint32_t a = fa + 16 * lane(), sl = a - wlo;
+        if (a >= o0 && a + 16 <= limit) {
+            *reinterpret_cast<uint4 *>(base + a) = *reinterpret_cast<const uint4 *>(win + sl);
+        } else if (a + 16 > o0 && a < limit) {
+            for (uint32_t k = 0; k < 16; k++)
+                if (a + k >= o0 && a + k < limit) base[a + k] = win[sl + k];
+        }
+        fa += 1024;
+    }
+    // Room for len <= kAppend more bytes.
+    __device__ __forceinline__ void make_room(uint32_t len) {
+        if (room >= len) return;
+        wave_sync();
+        const uint32_t at = o0 + pos;
+        while (fa + 1024 <= at) flush_block(o0 + cap);
+        const uint32_t lo = (at + len - H + 1023) & ~1023u, d = lo - wlo;
+        for (uint32_t i = 0; i < at - lo; i += 1024) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(win + d + i + 16 * lane());
+            wave_sync();
+            *reinterpret_cast<uint4 *>(win + i + 16 * lane()) = v;
+        }
+        wlo = lo;
+        room = wlo + H - at;
+        wave_sync();
+    }
+    __device__ __forceinline__ void put_literal(uint32_t b) {
+        make_room(1);
+        win[slot(o0 + pos)] = (uint8_t)b;  // same byte from every lane
+        pos++;
+        room--;
+    }
+    // Back-reference: len bytes (at most 258) from dist bytes back (dist <=
+    // pos).  With len > dist the bytes repeat with period dist.
+    __device__ __forceinline__ void copy(uint32_t dist, uint32_t len) {
+        make_room(len);
+        const uint32_t dst = o0 + pos, src = dst - dist;
+        if (src < wlo) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            for (uint32_t i = lane(); i < len; i += kWave) win[slot(dst + i)] = base[src + i];
+        } else {
+            copy_near(src, dst, dist, len);
+        }
+        pos += len;
+        room -= len;
+    }
+    // A copy within the window by the whole wave, overlapping or not.
+    __device__ __forceinline__ void copy_near(uint32_t src, uint32_t dst, uint32_t dist, uint32_t len) const {
+        if (dist >= len) {
+            for (uint32_t i = lane(); i < len; i += kWave) win[slot(dst + i)] = win[slot(src + i)];
+        } else {
+            uint32_t r = lane() % dist;
+            const uint32_t step = kWave % dist;
+            for (uint32_t i = lane(); i < len; i += kWave) {
+                win[slot(dst + i)] = win[slot(src + r)];
+                r += step;
+                if (r >= dist) r -= dist;
+            }
+        }
+        wave_sync();
+    }
+    // Writes every byte produced so far to HBM.
+    __device__ __forceinline__ void finish() {
+        const uint32_t end = o0 + pos;
+        while (fa < end) flush_block(end);
+    }
+};
+
 // Reads a dynamic block's header up to its code lengths (RFC 1951 3.2.7):
 // HLIT, HDIST, HCLEN, the code-length code (built into cltab, 7-bit
 // table), then the HLIT + HDIST lengths into lens.  Returns a status.
 template <class Ring>
-__device__ __forceinline__ int read_code_lengths(Ring &in, BitIn &bi, uint16_t *cltab,
+__device__ __forceinline__ int read_code_lengths(Ring &in, BitIn &bi, uint32_t *cltab,
                                                  CodeMeta *meta, uint16_t *sorted, uint8_t *lens,
                                                  uint32_t &hlit, uint32_t &hdist, uint32_t &hclen) {
     const uint32_t l = lane();
@@ -396,9 +526,9 @@ __device__ __forceinline__ int read_code_lengths(Ring &in, BitIn &bi, uint16_t *
     uint32_t idx = 0, total = hlit + hdist, prev = 0;
     while (idx < total) {
         bi.refill(in);
-        uint32_t e = uni((uint32_t)cltab[bi.peek(kCodeLenBits)]);
-        uint32_t sym = (e >> 4) & 511;
-        if (!bi.drop(e & 15)) return CODAG_E_TRUNCATED;
+        uint32_t e = uni(cltab[bi.peek(kCodeLenBits)]);
+        uint32_t sym = ent_sym(e);
+        if (!bi.drop(ent_cl(e))) return CODAG_E_TRUNCATED;
         if (sym < 16) {
             lens[idx] = (uint8_t)sym;  // same byte from every lane
             prev = sym;
@@ -440,59 +570,40 @@ constexpr int kMore = 1;
 // length/distance pairs; everything rare leaves the loop.  With ONE, it
 // returns kMore after the first literal or copy.
 template <int TB, uint32_t H, bool ONE = false, class Ring>
-__device__ __forceinline__ int inflate_symbols(Ring &in, BitIn &bi, WindowOut<H> &o,
-                                               DeflateLds<TB, H> *lds, bool have_dist,
-                                               uint32_t len_tab, uint32_t dist_tab) {
+__device__ __forceinline__ int inflate_symbols(Ring &in, BitIn &bi, LinearOut<H> &o, DeflateLds<TB, H> *lds) {
     int st;
     for (;;) {
         bi.refill1(in);
-        uint32_t e = uni((uint32_t)lds->lit[bi.peek(TB)]);
-        if (e < (kBase << 13)) {  // literal
-            bi.skip(e & 15);
-            if (o.pos == o.cap) {
-                st = CODAG_E_OVERFLOW;
-                break;
-            }
-            o.put_literal(e >> 4);
-            if (ONE) return kMore;
-            continue;
-        }
-        if ((e >> 13) == kSlow) e = slow_symbol(bi, &lds->lit_meta, lds->lit_sorted, kLitLen);
-        uint32_t kind = e >> 13;
-        if (kind == kLit) {
-            bi.skip(e & 15);
-            if (o.pos == o.cap) {
-                st = CODAG_E_OVERFLOW;
-                break;
-            }
-            o.put_literal((e >> 4) & 255);
-            if (ONE) return kMore;
-            continue;
-        }
-        if (kind != kBase) {  // end of block, or an invalid code
-            if (kind != kInvalid) bi.skip(e & 15);
-            st = kind == kEob ? CODAG_OK : CODAG_E_CORRUPT;
+        uint32_t e = uni(lds->lit[bi.peek(TB)]);
+        if (e & kEntSlow) e = uni(slow_entry((uint32_t)bi.buf, TB, &lds->lit_meta, lds->lit_sorted, kLitLen));
+        bi.skip(ent_cl(e));
+        if (e & kEntStop) {  // end of block, or an invalid code
+            st = ent_why(e) == kWhyEob ? CODAG_OK : CODAG_E_CORRUPT;
             break;
         }
+        if (!(e & kEntCopy)) {
+            if (o.pos == o.cap) {
+                st = CODAG_E_OVERFLOW;
+                break;
+            }
+            o.put_literal(ent_byte(e));
+            if (ONE) return kMore;
+            continue;
+        }
         // Length, then distance.
-        bi.skip(e & 15);
-        uint32_t lb = readlane(len_tab, ((e >> 4) & 511) - 257);
-        uint32_t ex = lb >> 16;
-        uint32_t len = (lb & 0xffff) + bi.peek(ex);
-        bi.skip(ex);
+        const uint32_t lex = ent_lex(e);
+        const uint32_t len = ent_len(e) + bi.peek(lex);
+        bi.skip(lex);
         bi.refill1(in);
-        uint32_t d = uni((uint32_t)lds->dist[bi.peek(kDistBits)]);
-        if ((d >> 13) == kSlow) d = slow_symbol(bi, &lds->dist_meta, lds->dist_sorted, kDist);
-        if ((d >> 13) != kBase || !have_dist) {
-            if ((d >> 13) == kBadSym && have_dist) bi.skip(d & 15);
+        uint32_t d = uni(lds->dist[bi.peek(kDistBits)]);
+        if (d & kEntSlow) d = uni(slow_entry((uint32_t)bi.buf, kDistBits, &lds->dist_meta, lds->dist_sorted, kDist));
+        bi.skip(ent_cl(d));
+        if (d & kEntStop) {  // invalid, or a block without distance codes
             st = CODAG_E_CORRUPT;
             break;
         }
-        bi.skip(d & 15);
-        uint32_t db = readlane(dist_tab, (d >> 4) & 31);
-        uint32_t dex = db >> 16;
-        uint32_t dist = (db & 0xffff) + bi.peek(dex);
-        bi.skip(dex);
+        const uint32_t dist = ent_dist(d) + bi.peek(ent_ex(d));
+        bi.skip(ent_ex(d));
         if (dist > o.pos) {
             st = CODAG_E_CORRUPT;
             break;
@@ -528,19 +639,6 @@ __device__ __forceinline__ int inflate_symbols(Ring &in, BitIn &bi, WindowOut<H>
 
 constexpr uint32_t kBatchOut = 1024;
 
-// Length and distance bases and extra-bit counts (RFC 1951 section 3.2.5)
-// in closed form.
-__device__ __forceinline__ uint32_t length_extra(uint32_t k) {  // k = symbol - 257
-    return (k < 8 || k == 28) ? 0 : (k >> 2) - 1;
-}
-__device__ __forceinline__ uint32_t length_base(uint32_t k) {
-    return k < 8 ? k + 3 : k == 28 ? 258 : ((4 + (k & 3)) << ((k >> 2) - 1)) + 3;
-}
-__device__ __forceinline__ uint32_t dist_extra(uint32_t d) { return d < 4 ? 0 : (d >> 1) - 1; }
-__device__ __forceinline__ uint32_t dist_base(uint32_t d) {
-    return d < 4 ? d + 1 : ((2 + (d & 1)) << ((d >> 1) - 1)) + 1;
-}
-
 // Token words: a literal is 1 << 16 | byte, a copy is length << 16 | 0x8000;
 // bits 8-13 hold the bits the token takes in the input; 0x4000 marks a
 // token the batch cannot take (0x4000: end of block, 0xc000: anything that
@@ -555,7 +653,7 @@ constexpr uint32_t kTokCopy = 0x8000u, kTokStop = 0x4000u, kTokOther = 0xc000u;
 template <int TB, uint32_t H, bool ALIGNED = false>
 __device__ __forceinline__ void lane_token(uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3,
                                            uint32_t s4, uint32_t b, const DeflateLds<TB, H> *lds,
-                                           bool have_dist, uint32_t &info, uint32_t &dist) {
+                                           uint32_t &info, uint32_t &dist) {
     // ALIGNED: b is a multiple of 32, so lane l starts in word l / 32 and
     // s4 is not needed.
     const uint32_t a = (ALIGNED ? 0u : (b & 31)) + lane();
@@ -567,30 +665,23 @@ __device__ __forceinline__ void lane_token(uint32_t s0, uint32_t s1, uint32_t s2
                        __builtin_amdgcn_alignbit(wb, wa, sh);
     const uint32_t xl = (uint32_t)x;
     const uint32_t e = lds->lit[xl & ((1u << TB) - 1)];
-    const uint32_t kind = e >> 13, cl = e & 15, sym = (e >> 4) & 511;
     // Every lane also decodes a length/distance pair from its bits (the
     // distance lookup reads the table whatever the entry was) and the kind
     // picks the result: no branches, so no scalar mask bookkeeping.  The
     // length code and its extra bits end by bit 20, the distance code's
-    // index by bit 28, its extra bits by bit 50.
-    // The choices are all-ones/zero masks rather than conditionals, which
-    // the compiler would turn back into branches.
-    const uint32_t kk = (sym - 257) & 31;  // length symbol 257 + kk
-    const uint32_t lsmall = 0u - (uint32_t)(kk < 8), l258 = 0u - (uint32_t)(kk == 28);
-    const uint32_t ex = ((kk >> 2) - 1) & ~(lsmall | l258);
-    const uint32_t lbig = ((4 + (kk & 3)) << (((kk >> 2) - 1) & 31)) + 3;
-    const uint32_t lbase = (((kk + 3) & lsmall) | (lbig & ~lsmall) | l258) & (258u | ~l258);
-    const uint32_t len = lbase + ((xl >> cl) & ((1u << ex) - 1));
-    const uint32_t p2 = cl + ex;
+    // index by bit 28, its extra bits by bit 50.  The choices are
+    // all-ones/zero masks rather than conditionals, which the compiler would
+    // turn back into branches.
+    const uint32_t cl = ent_cl(e), p2 = ent_bits(e);
+    const uint32_t len = ent_len(e) + ((xl >> cl) & ((1u << ent_lex(e)) - 1));
     const uint32_t d = lds->dist[(xl >> p2) & ((1u << kDistBits) - 1)];
-    const uint32_t dcl = d & 15, ds = (d >> 4) & 31, q = p2 + dcl;  // distance symbol ds
-    const uint32_t dsmall = 0u - (uint32_t)(ds < 4);
-    const uint32_t dex = ((ds >> 1) - 1) & ~dsmall;
-    const uint32_t dbase = ((ds + 1) & dsmall) | ((((2 + (ds & 1)) << dex) + 1) & ~dsmall);
-    const uint32_t dv = dbase + ((uint32_t)(x >> q) & ((1u << dex) - 1));
-    const uint32_t m_lit = 0u - (uint32_t)(kind == kLit), m_eob = 0u - (uint32_t)(kind == kEob);
-    const uint32_t m_copy = 0u - (uint32_t)(kind == kBase && have_dist && (d >> 13) == kBase);
-    info = (((1u << 16) | (cl << 8) | sym) & m_lit) | ((kTokStop | (cl << 8)) & m_eob) |
+    const uint32_t q = p2 + ent_cl(d), dex = ent_ex(d);
+    const uint32_t dv = ent_dist(d) + ((uint32_t)(x >> q) & ((1u << dex) - 1));
+    const uint32_t odd = e & (kEntSlow | kEntStop);
+    const uint32_t m_lit = 0u - (uint32_t)(odd == 0 && !(e & kEntCopy));
+    const uint32_t m_eob = 0u - (uint32_t)((e & kEntStop) && ent_why(e) == kWhyEob);
+    const uint32_t m_copy = 0u - (uint32_t)(odd == 0 && (e & kEntCopy) && !(d & (kEntSlow | kEntStop)));
+    info = (((1u << 16) | (cl << 8) | ent_byte(e)) & m_lit) | ((kTokStop | (cl << 8)) & m_eob) |
            (((len << 16) | kTokCopy | ((q + dex) << 8)) & m_copy) | (kTokOther & ~(m_lit | m_eob | m_copy));
     dist = dv & m_copy;
 }
@@ -617,9 +708,8 @@ __device__ __forceinline__ uint32_t walk_word(uint32_t info) {
 }
 
 template <int TB, uint32_t H, class Ring>
-__device__ __forceinline__ int inflate_batched(Ring &in, BitIn &bi, WindowOut<H> &o,
-                                               DeflateLds<TB, H> *lds, bool have_dist,
-                                               uint32_t len_tab, uint32_t dist_tab) {
+__device__ __forceinline__ int inflate_batched(Ring &in, BitIn &bi, LinearOut<H> &o,
+                                               DeflateLds<TB, H> *lds) {
     const uint32_t l = lane();
     // Candidates are decoded for fixed 64-bit windows of the input (lane l:
     // the token at bit 64 w + l).  The walk's tokens are staged, as packed
@@ -653,7 +743,7 @@ __device__ __forceinline__ int inflate_batched(Ring &in, BitIn &bi, WindowOut<H>
             const uint32_t c0 = wi + 64 - cend;
             uint32_t info, dist;
             lane_token<TB, H, true>(readlane(cache, c0), readlane(cache, c0 + 1), readlane(cache, c0 + 2),
-                                    readlane(cache, c0 + 3), 0u, 64 * wk, lds, have_dist, info, dist);
+                                    readlane(cache, c0 + 3), 0u, 64 * wk, lds, info, dist);
             cur = pack_token(info, dist);
             walk = walk_word(info);
         };
@@ -731,15 +821,15 @@ __device__ __forceinline__ int inflate_batched(Ring &in, BitIn &bi, WindowOut<H>
             const bool valid = l < ntok;
             const uint32_t len = valid ? vlen : 0;
             const bool is_copy = valid && (tok & kTokCopy);
-            const uint32_t start = o.o0 + total0;  // first byte of the batch (window coordinates)
+            const uint32_t start = o.o0 + total0;  // first byte of the batch
             const uint32_t dst = o.o0 + before;    // this token's first byte
             uint8_t *const lit_to = valid && !is_copy ? o.win + o.slot(dst) : trash;
             *lit_to = (uint8_t)tok;
             const uint32_t src = dst - tdist;
             const bool before = is_copy && src + len <= start;  // source entirely before the batch
-            // Bytes below lds_from may be overwritten in the window by this
-            // batch; they were flushed to HBM before it started.
-            const int32_t lds_from = (int32_t)(start + bout) - (int32_t)H;
+            // Bytes below lds_from have left the window; they were flushed to
+            // HBM before this batch started.
+            const int32_t lds_from = (int32_t)o.wlo;
             const bool far = ballot(before && (int32_t)src < lds_from) != 0;
             if (!far) {
                 // Every source byte is in the window: no global loads, so
@@ -835,13 +925,330 @@ __device__ __forceinline__ int inflate_batched(Ring &in, BitIn &bi, WindowOut<H>
         bi.seek(in, p >> 3);
         bi.skip(p & 7);
         if (stop == 2) return bi.remain < 0 ? CODAG_E_TRUNCATED : CODAG_OK;
-        int st = inflate_symbols<TB, H, true>(in, bi, o, lds, have_dist, len_tab, dist_tab);
+        int st = inflate_symbols<TB, H, true>(in, bi, o, lds);
         if (st != kMore) return st;
         p = 8 * bi.next - bi.cnt;
         // A window's candidates depend only on its input bits: if the next
         // token is still in window wk, they stay.
         have = have && (p >> 6) == wk;
         wk = p >> 6;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Lane-parallel symbol decoding.
+//
+// A round takes the next 64 x 256 bits of input, and lane l decodes, token
+// after token, the tokens that start in its own 256 bits.  Only lane 0 knows
+// where its first token starts; the others begin at their first bit, which is
+// usually inside a token.  A Huffman decoder started off the track falls back
+// onto it after a few tokens, so most lanes end at a true token start all the
+// same: each lane then starts over where the lane before it ended, and the
+// pass is repeated until no start moves (4 to 5 passes on text, 4 on columns,
+// 6 to 9 with the fixed code).  Every lane works on tokens it alone decodes,
+// so a pass costs about 25 loop trips for some 1,400 tokens, where one
+// candidate per bit of a 64-bit window costs a trip and a serial walk for
+// every five.  Each lane notes per 64-bit segment where the segment's first
+// token starts and how many output bytes and copies its tokens make.
+//
+// The segments are then written out, up to 64 at a time, one per lane (as
+// many as fit kAppend output bytes and the copy queue): a prefix sum gives
+// each segment's place in the output, its lane decodes it once more, puts
+// literals into the window and queues copies, and the queue is run 64 copies
+// at a time.  A segment too large by itself is written by one lane, in parts.
+//
+// Sizes: with 256 bits a lane the passes take 6 trips per 64 tokens of text,
+// with 128 and 64 bits 10 and 17 (counted on the CPU); 512 bits would take
+// 4.6 but 4 KiB of input and two KiB of segment notes per wave.  Segments are
+// 64 bits because the output window bounds one step to about 340 tokens.
+// Measured against the window-by-window decoder: 16,384 chunks of 64 KiB
+// 12.49 to 5.40 ms, 48 chunks of 60 KB (one wave each, nothing else running)
+// 1,811 to 733 us, 256 KiB ORC blocks 7.33 to 2.98 ms, a learned batch of
+// 2,000 chunks 16.66 to 5.83 ms.  A wave holds 12 KiB of LDS instead of 8 (13
+// instead of 20 waves per CU), which the shorter work more than pays for.
+// Codes that hardly ever fall back (all of one length) would need a pass per
+// lane: past kMaxPasses a round keeps the lanes that are on the track and the
+// rest of the block goes to the window-by-window decoder.
+// ---------------------------------------------------------------------------
+
+constexpr uint32_t kMaxPasses = 20;
+
+typedef uint64_t u64_any __attribute__((aligned(1), may_alias));
+typedef uint32_t u32_any __attribute__((aligned(1), may_alias));
+typedef uint16_t u16_any __attribute__((aligned(1), may_alias));
+
+// Copies longer than this are made by the whole wave, one after another.
+constexpr uint32_t kLongCopy = 32;
+
+// Runs the nq queued copies of an emission step whose output starts at
+// `start`.  Their sources are the output before them: 64 copies at a time,
+// every copy whose source ends before the lowest pending copy's output goes
+// at once, eight bytes per access at any alignment (byte by byte, sixteen
+// masked stores a piece, this was the larger half of a step).
+template <uint32_t H, int TB>
+__device__ __forceinline__ void run_copies(const LinearOut<H> &o, const DeflateLds<TB, H> *lds, uint32_t nq,
+                                           uint32_t start) {
+    const uint32_t l = lane();
+    for (uint32_t k0 = 0; k0 < nq; k0 += kWave) {
+        const bool v = k0 + l < nq;
+        const uint32_t at = min(k0 + l, kCopyQueue - 1);
+        const uint32_t q = lds->queue[at];
+        const uint32_t len = v ? (q & 255) + 3 : 0u, dist = ((q >> 8) & 0x7fff) + 1;
+        const uint32_t dst = start + lds->queue_dst[at], src = dst - dist;
+        const bool far = v && src < o.wlo;  // left the window: wholly in HBM
+        if (ballot(far)) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        uint64_t pend = ballot(v);
+        while (pend) {
+            const uint32_t t = (uint32_t)__builtin_ctzll(pend), front = readlane(dst, t);
+            const bool ready = ((pend >> l) & 1) && src + len <= front;
+            const uint64_t rm = ballot(ready);
+            if (!rm) {  // the lowest pending copy repeats its own output
+                o.copy_near(readlane(src, t), front, readlane(dist, t), readlane(len, t));
+                pend &= pend - 1;
+                continue;
+            }
+            if (ready && len <= kLongCopy) {
+                uint8_t *const to = o.win + (dst - o.wlo);
+                const uint32_t tail = len > 8 ? len - 8 : 0u;
+                uint64_t a, b;
+                if (far) {
+                    a = *reinterpret_cast<const u64_any *>(o.base + src);
+                    b = *reinterpret_cast<const u64_any *>(o.base + src + tail);
+                } else {
+                    const uint8_t *from = o.win + (src - o.wlo);
+                    a = *reinterpret_cast<const u64_any *>(from);
+                    b = *reinterpret_cast<const u64_any *>(from + tail);
+                }
+                if (len >= 8) {
+                    *reinterpret_cast<u64_any *>(to) = a;
+                    for (uint32_t j = 8; j < tail; j += 8) {
+                        uint64_t m;
+                        if (far) m = *reinterpret_cast<const u64_any *>(o.base + src + j);
+                        else m = *reinterpret_cast<const u64_any *>(o.win + (src - o.wlo) + j);
+                        *reinterpret_cast<u64_any *>(to + j) = m;
+                    }
+                    *reinterpret_cast<u64_any *>(to + tail) = b;
+                } else if (len >= 4) {
+                    *reinterpret_cast<u32_any *>(to) = (uint32_t)a;
+                    *reinterpret_cast<u32_any *>(to + len - 4) = (uint32_t)(a >> (8 * (len - 4)));
+                } else {
+                    *reinterpret_cast<u16_any *>(to) = (uint16_t)a;
+                    to[2] = (uint8_t)(a >> 16);
+                }
+            }
+            for (uint64_t lm = ballot(ready && len > kLongCopy); lm; lm &= lm - 1) {
+                const uint32_t k = (uint32_t)__builtin_ctzll(lm);
+                const uint32_t cs = readlane(src, k), cd = readlane(dst, k), cl = readlane(len, k);
+                const uint32_t j = min(8 * l, cl - 8);
+                if (8 * l < cl) {
+                    uint64_t a;
+                    if (cs < o.wlo) a = *reinterpret_cast<const u64_any *>(o.base + cs + j);
+                    else a = *reinterpret_cast<const u64_any *>(o.win + (cs - o.wlo) + j);
+                    *reinterpret_cast<u64_any *>(o.win + (cd - o.wlo) + j) = a;
+                }
+            }
+            pend &= ~rm;
+            wave_sync();
+        }
+    }
+}
+
+// One token from its bits (raw >> sh): its table entries, the slow codes
+// resolved.  d is 0 (no bits) for a literal.
+template <int TB, uint32_t H>
+__device__ __forceinline__ void token_entries(uint64_t bits, const DeflateLds<TB, H> *lds, uint32_t &e, uint32_t &d) {
+    const uint32_t x = (uint32_t)bits;
+    e = lds->lit[x & ((1u << TB) - 1)];
+    if (e & kEntSlow) e = slow_entry(x, TB, &lds->lit_meta, lds->lit_sorted, kLitLen);
+    // The length code and its extra bits end by bit 20.
+    const uint32_t d0 = lds->dist[(x >> ent_bits(e)) & ((1u << kDistBits) - 1)];
+    d = (e & kEntCopy) ? d0 : 0u;
+    if (d & kEntSlow)
+        d = slow_entry((uint32_t)(bits >> ent_bits(e)), kDistBits, &lds->dist_meta, lds->dist_sorted, kDist);
+}
+
+template <int TB, uint32_t H, class Ring>
+__device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &o, DeflateLds<TB, H> *lds) {
+    static_assert(Ring::kLdsWords <= kRoundInWords, "the round's input takes the ring's place");
+    const uint32_t l = lane();
+    uint8_t *const inb = reinterpret_cast<uint8_t *>(in.ring);
+    const uint32_t endbit = 8 * in.gend;
+    uint32_t p = 8 * bi.next - bi.cnt;  // bit position of the next code
+    for (;;) {
+        // Bits past the end read as zero; a block that goes on there is cut
+        // off, whatever they decode to.
+        if (p >= endbit) return CODAG_E_TRUNCATED;
+        // ---- the round's input
+        const uint32_t b0 = p & ~(kSegBits - 1), a0 = (b0 >> 3) & ~15u, ofs = (b0 >> 3) & 15;
+        wave_sync();
+#pragma unroll
+        for (uint32_t k = 0; k < 3; k++) {
+            const uint32_t idx = kWave * k + l, at = a0 + 16 * idx;
+            if (idx < kRoundPieces && at < in.gend)
+                __builtin_amdgcn_global_load_lds(in.gbase + at, (lds_void *)(in.ring + 256 * k), 16, 0, 0);
+        }
+        wait_vm();
+        if (a0 + 16 * kRoundPieces > in.gend) {  // zero the bytes past the end of the chunk
+#pragma unroll
+            for (uint32_t k = 0; k < 3; k++) {
+                const uint32_t idx = kWave * k + l, at = a0 + 16 * idx;
+                if (idx < kRoundPieces && at + 16 > in.gend) {
+                    const uint32_t valid = at < in.gend ? in.gend - at : 0;
+                    uint4 v = valid ? reinterpret_cast<const uint4 *>(in.ring)[idx] : make_uint4(0, 0, 0, 0);
+                    uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                    for (int j = 0; j < 4; j++) {
+                        const int keep = (int)valid - 4 * j;
+                        w[j] &= keep >= 4 ? 0xffffffffu : keep <= 0 ? 0u : ((1u << (8 * keep)) - 1);
+                    }
+                    reinterpret_cast<uint4 *>(in.ring)[idx] = make_uint4(w[0], w[1], w[2], w[3]);
+                }
+            }
+        }
+        wave_sync();
+
+        // ---- passes: every lane's tokens, until every start is true
+        const uint8_t *const mine = inb + ofs + (kLaneBits / 8) * l;
+        uint32_t live = min((uint32_t)kWave, (endbit - b0 + kLaneBits - 1) / kLaneBits);
+        uint32_t rs = l == 0 ? p - b0 : 0u;  // this lane's first token, relative to its first bit
+        uint32_t tried = ~0u, re = 0, rz = 0, why = 0;  // where it started, ended, stopped and why
+        uint32_t m = 0;                                 // lanes whose tokens are true
+        bool poor = false;
+        for (uint32_t pass = 0;; pass++) {
+            const bool need = l < live && rs != tried;
+            const uint64_t nm = ballot(need);
+            if (!nm) {
+                m = live;
+                break;
+            }
+            if (pass == kMaxPasses) {
+                m = (uint32_t)__builtin_ctzll(nm);
+                poor = true;
+                break;
+            }
+            if (need) {
+                tried = rs;
+                why = 0;
+                uint32_t r = rs, sp = rs, acc = 0;  // acc: output bytes << 12 | copies << 6
+                do {
+                    const uint64_t bits = *reinterpret_cast<const u64_any *>(mine + (r >> 3)) >> (r & 7);
+                    uint32_t e, d;
+                    token_entries(bits, lds, e, d);
+                    if ((e | d) & kEntStop) {
+                        why = (e & kEntStop) ? ent_why(e) : (uint32_t)kWhyInvalid;
+                        break;
+                    }
+                    acc += ((ent_len(e) + (((uint32_t)bits >> ent_cl(e)) & ((1u << ent_lex(e)) - 1))) << 12) +
+                           ((e >> 31) << 6);
+                    const uint32_t r2 = r + ent_bits(e) + ent_bits(d);
+                    if ((r ^ r2) & ~(kSegBits - 1)) {
+                        lds->segs[kLaneSegs * l + r / kSegBits] = (sp & (kSegBits - 1)) | acc;
+                        sp = r2;
+                        acc = 0;
+                    }
+                    r = r2;
+                } while (r < kLaneBits);
+                rz = re = r;
+                if (why) {
+                    lds->segs[kLaneSegs * l + r / kSegBits] = (sp & (kSegBits - 1)) | acc;
+                    if (why == kWhyEob) {
+                        // The end-of-block code's length, from its entry again.
+                        const uint64_t bits = *reinterpret_cast<const u64_any *>(mine + (r >> 3)) >> (r & 7);
+                        uint32_t e, d;
+                        token_entries(bits, lds, e, d);
+                        re = r + ent_cl(e);
+                    }
+                }
+            }
+            // Start over where the lane before ended (if it did not stop).
+            const uint32_t ue = wave_shift_up1(why ? ~0u : re);
+            if (l != 0 && ue != ~0u) rs = ue - kLaneBits;
+            const uint64_t moved = ballot(l < live && rs != tried);
+            const uint64_t stops = ballot(l < live && why != 0) & (moved ? (moved & (0 - moved)) - 1 : ~0ull);
+            if (stops) live = (uint32_t)__builtin_ctzll(stops) + 1;  // a true stop: nothing follows it
+        }
+        wave_sync();
+        const uint32_t whyl = readlane(why, m - 1), zl = readlane(rz, m - 1);
+        const uint32_t nseg = kLaneSegs * (m - 1) + (whyl ? zl / kSegBits + 1 : kLaneSegs);
+        p = b0 + kLaneBits * (m - 1) + readlane(re, m - 1);
+
+        // ---- write the segments
+        for (uint32_t g0 = 0; g0 < nseg;) {
+            const uint32_t g = g0 + l;
+            const uint32_t c = g < nseg ? lds->segs[g] : 0u;
+            const uint32_t so = c >> 12, sc = (c >> 6) & 63;
+            const uint32_t incl = wave_inclusive_sum32((so << 12) | sc);
+            const uint64_t over = ballot(g >= nseg || (incl >> 12) > LinearOut<H>::kAppend || (incl & 4095) > kCopyQueue);
+            uint32_t cnt = over ? (uint32_t)__builtin_ctzll(over) : (uint32_t)kWave;
+            const bool part = cnt == 0;  // one segment does not fit: its lane writes what does
+            if (part) cnt = 1;
+            uint32_t made = part ? LinearOut<H>::kAppend : readlane(incl, cnt - 1) >> 12;
+            uint32_t nq = readlane(incl, cnt - 1) & 4095;
+            o.make_room(made);
+            const uint32_t start = o.o0 + o.pos, lim = o.o0 + o.cap;
+            uint32_t dst = start + (incl >> 12) - so, qi = (incl & 4095) - sc;
+            uint32_t r = c & (kSegBits - 1);
+            const uint32_t er = whyl && g == nseg - 1 ? zl & (kSegBits - 1) : kSegBits;
+            int bad = CODAG_OK;
+            if (l < cnt) {
+                const uint8_t *const seg = inb + ofs + (kSegBits / 8) * g;
+                while (r < er) {
+                    const uint64_t bits = *reinterpret_cast<const u64_any *>(seg + (r >> 3)) >> (r & 7);
+                    uint32_t e, d;
+                    token_entries(bits, lds, e, d);
+                    const uint32_t len = ent_len(e) + (((uint32_t)bits >> ent_cl(e)) & ((1u << ent_lex(e)) - 1));
+                    if (part && (dst - start + len > LinearOut<H>::kAppend || qi == kCopyQueue)) break;
+                    r += ent_bits(e) + ent_bits(d);
+                    if (dst + len > lim) bad = CODAG_E_OVERFLOW;
+                    if (e & kEntCopy) {
+                        const uint32_t dist = ent_dist(d) + ((uint32_t)(bits >> (ent_bits(e) + ent_cl(d))) &
+                                                             ((1u << ent_ex(d)) - 1));
+                        if (dist > dst - o.o0) bad = CODAG_E_CORRUPT;
+                        if (bad) break;
+                        lds->queue[qi] = (len - 3) | ((dist - 1) << 8);
+                        lds->queue_dst[qi] = (uint16_t)(dst - start);
+                        qi++;
+                    } else {
+                        if (bad) break;
+                        o.win[dst - o.wlo] = (uint8_t)ent_byte(e);
+                    }
+                    dst += len;
+                }
+            }
+            wave_sync();
+            const uint64_t badm = ballot(bad != CODAG_OK);
+            const uint32_t bl = badm ? (uint32_t)__builtin_ctzll(badm) : 0u;  // the first bad token's lane
+            if (badm || part) {
+                nq = readlane(qi, bl);
+                made = readlane(dst, bl) - start;
+            }
+            run_copies<H, TB>(o, lds, nq, start);
+            o.pos += made;
+            o.room -= made;
+            if (badm)
+                return b0 + kSegBits * (g0 + bl) + readlane(r, bl) > endbit ? CODAG_E_TRUNCATED
+                                                                           : (int)readlane((uint32_t)bad, bl);
+            if (part) {
+                const uint32_t r0 = readlane(r, 0);
+                if (r0 >= readlane(er, 0)) {
+                    g0++;
+                } else {
+                    if (l == 0) lds->segs[g0] = ((c - (made << 12) - (nq << 6)) & ~(kSegBits - 1)) | r0;
+                    wave_sync();
+                }
+            } else {
+                g0 += cnt;
+            }
+        }
+        if (!whyl && !poor) continue;
+        in.restart(p >> 3);
+        bi.seek(in, p >> 3);
+        bi.skip(p & 7);
+        if (whyl == kWhyEob) return p > endbit ? CODAG_E_TRUNCATED : CODAG_OK;
+        if (!whyl) return inflate_batched<TB, H>(in, bi, o, lds);
+        const int st = inflate_symbols<TB, H, true>(in, bi, o, lds);
+        if (st != kMore) return st;
+        p = 8 * bi.next - bi.cnt;
     }
 }
 
@@ -852,9 +1259,8 @@ __device__ __forceinline__ int inflate_batched(Ring &in, BitIn &bi, WindowOut<H>
 // round trip.  Anything but a plain literal or an in-range copy goes through
 // one step of the symbol-at-a-time loop, so statuses are that loop's.
 template <int TB, uint32_t H, class Ring>
-__device__ __forceinline__ int inflate_leader(Ring &in, BitIn &bi, WindowOut<H> &o,
-                                              DeflateLds<TB, H> *lds, bool have_dist,
-                                              uint32_t len_tab, uint32_t dist_tab) {
+__device__ __forceinline__ int inflate_leader(Ring &in, BitIn &bi, LinearOut<H> &o,
+                                              DeflateLds<TB, H> *lds) {
     uint32_t p = 8 * bi.next - bi.cnt;  // bit position of the next code
     uint32_t *slot = reinterpret_cast<uint32_t *>(lds->lens);  // free while symbols decode
     for (;;) {
@@ -863,7 +1269,7 @@ __device__ __forceinline__ int inflate_leader(Ring &in, BitIn &bi, WindowOut<H> 
         if (lane() == 0) {
             uint32_t info, dist;
             lane_token<TB, H>(in.word(wi), in.word(wi + 1), in.word(wi + 2), in.word(wi + 3),
-                              in.word(wi + 4), p, lds, have_dist, info, dist);
+                              in.word(wi + 4), p, lds, info, dist);
             slot[0] = info;
             slot[1] = dist;
         }
@@ -889,7 +1295,7 @@ __device__ __forceinline__ int inflate_leader(Ring &in, BitIn &bi, WindowOut<H> 
         }
         bi.seek(in, p >> 3);
         bi.skip(p & 7);
-        int st = inflate_symbols<TB, H, true>(in, bi, o, lds, have_dist, len_tab, dist_tab);
+        int st = inflate_symbols<TB, H, true>(in, bi, o, lds);
         if (st != kMore) return st;
         p = 8 * bi.next - bi.cnt;
     }
@@ -909,11 +1315,9 @@ __device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t c
     const uint32_t l = lane();
     BitIn bi;
     bi.seek(in, in.skip);
-    WindowOut<H> o;
+    LinearOut<H> o;
     o.init(out, cap, lds->window);
-    const uint32_t len_tab = length_lane_table(), dist_tab = distance_lane_table();
     bool fixed_ready = false;
-    bool have_dist = true;
     int st = CODAG_OK;
 
     for (;;) {
@@ -962,7 +1366,6 @@ __device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t c
                                 &lds->dist_meta);
                     fixed_ready = true;
                 }
-                have_dist = true;
             } else {
                 // Dynamic block header (RFC 1951 section 3.2.7).
                 fixed_ready = false;
@@ -984,12 +1387,14 @@ __device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t c
                     st = CODAG_E_CORRUPT;
                     break;
                 }
-                have_dist = dr.total != 0;
+                // Without distance codes (total 0) every table entry is invalid.
             }
             if constexpr (MODE == kLeaderLane)
-                st = inflate_leader<TB, H>(in, bi, o, lds, have_dist, len_tab, dist_tab);
+                st = inflate_leader<TB, H>(in, bi, o, lds);
+            else if constexpr (Ring::kLaneRounds)
+                st = inflate_lanes<TB, H>(in, bi, o, lds);
             else
-                st = inflate_batched<TB, H>(in, bi, o, lds, have_dist, len_tab, dist_tab);
+                st = inflate_batched<TB, H>(in, bi, o, lds);
             if (st) break;
         }
         if (last) break;

@@ -32,7 +32,7 @@ namespace codag {
 // ---------------------------------------------------------------------------
 
 struct FeatureLds {
-    uint16_t cl[1u << kCodeLenBits];
+    uint32_t cl[1u << kCodeLenBits];
     CodeMeta meta;
     uint16_t sorted[32];
     uint8_t lens[320];

@@ -45,6 +45,7 @@ template <uint32_t F>
 struct InRingT {
     static constexpr uint32_t kFetch = F, kBytes = 2 * F, kWords = kBytes / 4;
     static constexpr uint32_t kLdsWords = kWords + 4, kLand = F / 4;  // allocation sizes in words
+    static constexpr bool kLaneRounds = false;  // Deflate decodes window by window from this ring
 
     const uint8_t *gbase;  // 16-byte aligned
     uint32_t skip;         // chunk start relative to gbase (0..15)
@@ -161,6 +162,7 @@ struct DirectRing {
     static_assert(F == 512 || F % 1024 == 0, "fetch size");
     static constexpr uint32_t kFetch = F, kBytes = 2 * F, kWords = kBytes / 4;
     static constexpr uint32_t kLdsWords = kWords + 4, kLand = 0;
+    static constexpr bool kLaneRounds = true;  // Deflate decodes in lane-parallel rounds
     static constexpr uint32_t kLanes = F < 1024 ? F / 16 : kWave;  // lanes per fetch instruction
     static constexpr uint32_t kIssues = (F + 1023) / 1024;
 
@@ -278,6 +280,7 @@ __device__ __forceinline__ void lds_release(uint32_t *p, uint32_t v) {
 
 struct PrefetchRing {
     static constexpr uint32_t kFetch = 1024, kBytes = kPrefetchSlots * kFetch, kWords = kBytes / 4;
+    static constexpr bool kLaneRounds = false;
     uint32_t skip, gend, loaded;  // loaded: bytes known to be in the ring
     PrefetchShared *sh;
 

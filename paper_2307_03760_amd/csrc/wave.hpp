@@ -31,6 +31,15 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, uint32_t l) {
     return ((uint64_t)readlane((uint32_t)(v >> 32), l) << 32) | readlane((uint32_t)v, l);
 }
 
+// Orders LDS accesses of this wave's lanes: those before it are visible to
+// every lane after it (DS operations of one wave execute in order, so only
+// the compiler needs telling).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
 
 // Value of v in lane `from` (its low 6 bits), for every lane at once.  A
