@@ -19,8 +19,10 @@ namespace codag {
 // Plain launch: one chunk per wave, WPB waves per workgroup, every chunk of
 // one codec.  Each wave's LDS is a slice of three distinct arrays so the
 // compiler can tell ring reads from landing-buffer fetches.
+// At least four waves per SIMD: 128 VGPRs, which Deflate would pass by a few
+// (three waves: 5% slower over 8,192 chunks).
 template <int Codec, int TB, uint32_t H, int WPB>
-__global__ void __launch_bounds__(kWave * WPB)
+__global__ void __launch_bounds__(kWave * WPB) __attribute__((amdgpu_waves_per_eu(4)))
     decode_plain(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff,
                  uint32_t n, int32_t *status, unsigned long long *err, uint64_t *ticks) {
     __shared__ __align__(16) uint32_t s_ring[WPB][ring_lds_words<Codec>()];
@@ -122,7 +124,7 @@ int launch_lz4(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const ui
                uint64_t n, int wpb, int hist_kib, int32_t *status, unsigned long long *err,
                uint64_t *ticks, hipStream_t stream) {
     switch (hist_kib) {
-        case 2: return launch_plain<CODAG_LZ4, 9, 2048>(comp, coff, out, ooff, n, wpb, status, err, ticks, stream);
+        case 2:  // the linear window is at least 4 KiB
         case 4: return launch_plain<CODAG_LZ4, 9, 4096>(comp, coff, out, ooff, n, wpb, status, err, ticks, stream);
         case 8: return launch_plain<CODAG_LZ4, 9, 8192>(comp, coff, out, ooff, n, wpb, status, err, ticks, stream);
         case 16: return launch_plain<CODAG_LZ4, 9, 16384>(comp, coff, out, ooff, n, wpb, status, err, ticks, stream);
@@ -173,9 +175,7 @@ int decompress(int codec, const uint8_t *comp_buf, const uint64_t *chunk_offsets
     // waves.
     int wpb = opts && opts->waves_per_block ? opts->waves_per_block : lz77 ? 1 : 4;
     int tb = opts && opts->lit_table_bits ? opts->lit_table_bits : 9;
-    // LZ4 batches fit a 2 KiB window, and the smaller window keeps more
-    // waves resident; Deflate's token batches want 4 KiB.
-    int hist = opts && opts->history_kib ? opts->history_kib : codec == CODAG_LZ4 ? 2 : 4;
+    int hist = opts && opts->history_kib ? opts->history_kib : 4;
     if (opts && (opts->group_parallel < 0 || opts->group_parallel > 2)) return CODAG_E_INVALID_ARGUMENT;
     if (opts && opts->group_parallel == 2 && opts->chunk_ticks) return CODAG_E_INVALID_ARGUMENT;
     if ((wpb != 1 && wpb != 2 && wpb != 4) || (tb != 9 && tb != 10) ||

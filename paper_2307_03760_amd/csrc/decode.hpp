@@ -19,21 +19,20 @@ template <int TB, uint32_t H>
 struct WaveScratch<CODAG_DEFLATE, TB, H> {
     DeflateLds<TB, H> t;
 };
-// The LZ4 window is the first member of both, so a Deflate slice (as the
-// batched launch allocates) serves LZ4 too.
+// A Deflate slice (as the batched launch allocates) has room for LZ4's.
 template <int TB, uint32_t H>
 struct WaveScratch<CODAG_LZ4, TB, H> {
     Lz4Lds<H> t;
+    static_assert(sizeof(Lz4Lds<H>) <= sizeof(DeflateLds<TB, H>), "LZ4 in a Deflate slice");
 };
 
 __device__ __forceinline__ uint64_t error_key(uint64_t chunk, int st) {
     return (chunk << 4) | (uint64_t)(uint32_t)(-st);
 }
 
-// The input ring each codec decodes from.  Deflate and LZ4 spend tens of
-// microseconds per input kilobyte and are held to fewer waves per CU by
-// their LDS, so they fetch synchronously into a 1 KiB ring; the RLE decoders
-// read input fast and keep the fetch-ahead ring.
+// The input each codec decodes from.  Deflate and LZ4 are held to fewer waves
+// per CU by their LDS, so they fetch a kilobyte or two synchronously; the RLE
+// decoders read input fast and keep the fetch-ahead ring.
 template <int Codec>
 struct RingOf {
     using T = InRing;
@@ -44,7 +43,7 @@ struct RingOf<CODAG_DEFLATE> {
 };
 template <>
 struct RingOf<CODAG_LZ4> {
-    using T = DirectRing<512>;
+    using T = LinearIn;
 };
 // LDS words of a codec's ring and landing buffer (at least one word each,
 // for the kernels' arrays).

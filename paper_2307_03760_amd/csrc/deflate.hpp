@@ -21,6 +21,7 @@
 
 #include "../../include/codag.h"
 #include "stream.hpp"
+#include "window.hpp"
 
 namespace codag {
 
@@ -85,8 +86,8 @@ __device__ __forceinline__ uint32_t table_entry(int use, uint32_t s, uint32_t cl
 // bits, lie below lim[k] (and at or above lim[k - 1]); their symbols are
 // sorted[base[k] + code].
 struct CodeMeta {
-    uint32_t lim[16];
-    uint32_t base[16];
+    uint16_t lim[16];
+    uint16_t base[16];  // modulo 2^16
 };
 
 struct BuildResult {
@@ -143,8 +144,8 @@ __device__ __forceinline__ BuildResult build_table(const uint8_t *lens, uint32_t
             code = (code + cnt[len]) << 1;
         }
         if (l < 16) {
-            meta->lim[l] = lim;
-            meta->base[l] = base;
+            meta->lim[l] = (uint16_t)lim;
+            meta->base[l] = (uint16_t)base;
         }
     }
     if (left > 0) {  // incomplete: codes not in the set are invalid
@@ -157,8 +158,8 @@ __device__ __forceinline__ BuildResult build_table(const uint8_t *lens, uint32_t
         uint32_t m = s < n ? lens[s] : 0;
         if (m != 0) {
             // The first code of length m is the limit below it at m bits.
-            const uint32_t code = (meta->lim[m - 1] >> (15 - m)) + rank[p];
-            sorted[meta->base[m] + code] = (uint16_t)s;
+            const uint32_t code = ((uint32_t)meta->lim[m - 1] >> (15 - m)) + rank[p];
+            sorted[(uint16_t)(meta->base[m] + code)] = (uint16_t)s;
             if (m <= tb) {
                 uint32_t rev = __builtin_bitreverse32(code) >> (32 - m);
                 const uint32_t e = table_entry(use, s, m);
@@ -186,8 +187,7 @@ constexpr uint32_t kLaneBits = 256, kSegBits = 64, kLaneSegs = kLaneBits / kSegB
 constexpr uint32_t kRoundSegs = kWave * kLaneSegs;
 // The round's input: 64 x 32 bytes, up to 8 bytes of alignment before them
 // and the eight-byte reads past the last bit, in 16-byte pieces.
-constexpr uint32_t kRoundPieces = 130, kRoundInWords = 4 * kRoundPieces;
-constexpr uint32_t kCopyQueue = 160;  // copies of one emission step
+constexpr uint32_t kRoundPieces = kWave * kLaneBits / 128 + 2, kRoundInWords = 4 * kRoundPieces;
 
 // What one wave keeps in LDS while inflating, besides its input: the Huffman
 // tables, the output history window and the lane-parallel decoder's lists.
@@ -196,17 +196,22 @@ template <int TB, uint32_t H>
 struct DeflateLds {
     uint8_t window[H];
     uint8_t window_pad[16];  // eight-byte reads may pass the window's end
-    uint32_t lit[1u << TB];
-    uint32_t dist[1u << kDistBits];  // also the code-length table (7 bits)
-    CodeMeta lit_meta, dist_meta;
-    uint16_t lit_sorted[288];
-    uint16_t dist_sorted[32];
+    // Literal/length codes, distance codes (their part also serves the
+    // code-length code), and one zero: the entry of a lane with nothing to
+    // decode, which takes no bits and makes no output.
+    static constexpr uint32_t kIdle = (1u << TB) + (1u << kDistBits);
+    uint32_t tab[(1u << TB) + (1u << kDistBits) + 1];
+    CodeMeta meta[2];
+    uint16_t sorted[288 + 32];
     union {
         uint8_t lens[320];          // while a block's tables are built
         uint32_t segs[kRoundSegs];  // while its symbols decode
     };
-    uint32_t queue[kCopyQueue];
-    uint16_t queue_dst[kCopyQueue];
+    uint64_t queue[kCopyQueue + 1];  // pending copies, and a spare
+
+    __device__ __forceinline__ uint32_t *dist() { return tab + (1u << TB); }
+    __device__ __forceinline__ const uint32_t *dist() const { return tab + (1u << TB); }
+    __device__ __forceinline__ uint16_t *dist_sorted() { return sorted + 288; }
 };
 
 // Wave-uniform LSB-first bit reader over the ring.
@@ -287,7 +292,7 @@ __device__ __forceinline__ uint32_t slow_entry(uint32_t x, uint32_t tb, const Co
     for (uint32_t k = 1; k < 16; k++)
         if (k > tb) len += rev >= meta->lim[k] ? 1u : 0u;
     if (len > 15) return kEntInvalid;
-    const uint32_t at = meta->base[len] + (rev >> (15 - len));
+    const uint32_t at = (uint16_t)(meta->base[len] + (rev >> (15 - len)));
     return table_entry(use, sorted[min(at, use == kLitLen ? 287u : 31u)], len);
 }
 
@@ -296,207 +301,6 @@ __device__ __forceinline__ uint32_t slow_entry(uint32_t x, uint32_t tb, const Co
 // inside a loop that also has early exits makes the compiler treat the loop
 // exit as divergent, which moves the whole bit reader out of scalar
 // registers.
-
-// Output through the LDS history window.  Positions are 32-bit offsets from
-// `base`, the chunk's output address rounded down to 1 KiB (uniform values
-// stay in scalar registers; there are no scalar 64-bit ordered compares).
-// Bytes below `fa` are in HBM; bytes in [fa, o0 + pos) only in the window,
-// where the byte at offset x lives at window[(base + x) % H].
-// `room` = fa + H - (o0 + pos): bytes that can be appended before the oldest
-// unflushed kilobyte must go out.
-template <uint32_t H>
-struct WindowOut {
-    uint8_t *base;  // 1 KiB aligned
-    uint8_t *win;   // the wave's window (H bytes, LDS)
-    uint32_t o0;    // the chunk's first output byte, relative to base (0..1023)
-    uint32_t fa;    // relative, multiple of 1 KiB
-    uint32_t cap, pos, room;
-
-    __device__ __forceinline__ void init(uint8_t *out, uint32_t capacity, uint8_t *window) {
-        // Pointer arithmetic keeps `base` a global pointer: flat stores
-        // would also count against the LDS wait counter.
-        o0 = (uint32_t)(reinterpret_cast<uintptr_t>(out) & 1023);
-        base = out - o0;
-        win = window;
-        fa = 0;
-        cap = capacity;
-        pos = 0;
-        room = H - o0;
-    }
-    // base is 1 KiB aligned and H a power of two >= 1 KiB, so the slot of an
-    // offset does not depend on base.
-    __device__ __forceinline__ uint32_t slot(uint32_t x) const { return x & (H - 1); }
-
-    // Writes the kilobyte [fa, fa + 1024) to HBM, restricted to the bytes of
-    // the chunk's range below `limit` (relative).
-    __device__ __forceinline__ void flush_block(uint32_t limit) {
-        uint32_t a = fa + 16 * lane();
-        uint32_t sl = slot(a);
-        if (a >= o0 && a + 16 <= limit) {
-            *reinterpret_cast<uint4 *>(base + a) = *reinterpret_cast<const uint4 *>(win + sl);
-        } else if (a + 16 > o0 && a < limit) {
-            for (uint32_t k = 0; k < 16; k++)
-                if (a + k >= o0 && a + k < limit) base[a + k] = win[sl + k];
-        }
-        fa += 1024;
-    }
-    __device__ __forceinline__ void make_room(uint32_t len) {
-        while (room < len) {
-            flush_block(o0 + cap);
-            room += 1024;
-        }
-    }
-    // As make_room for len <= 258: one flush always suffices.
-    __device__ __forceinline__ void make_room1(uint32_t len) {
-        if (room < len) {
-            flush_block(o0 + cap);
-            room += 1024;
-        }
-    }
-    __device__ __forceinline__ void put_literal(uint32_t b) {
-        make_room1(1);
-        win[slot(o0 + pos)] = (uint8_t)b;  // same byte from every lane
-        pos++;
-        room--;
-    }
-    // Back-reference: len bytes from dist bytes back (dist <= pos).  With
-    // len > dist the bytes repeat with period dist.
-    __device__ __forceinline__ void copy(uint32_t dist, uint32_t len) {
-        make_room1(len);
-        uint32_t dst = o0 + pos;
-        if (dist + len <= H) {
-            // Every source byte is still in the window and this copy's own
-            // writes only replace bytes older than dist.
-            if (dist >= len) {
-                for (uint32_t i = lane(); i < len; i += kWave) win[slot(dst + i)] = win[slot(dst - dist + i)];
-            } else {
-                uint32_t r = lane() % dist, step = kWave % dist;
-                for (uint32_t i = lane(); i < len; i += kWave) {
-                    win[slot(dst + i)] = win[slot(dst - dist + r)];
-                    r += step;
-                    if (r >= dist) r -= dist;
-                }
-            }
-        } else {
-            // Far reference (dist > H - len >= len): bytes below dst + len - H
-            // may be overwritten in the window but are already in HBM.
-            int32_t lds_from = (int32_t)(dst + len) - (int32_t)H;
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            for (uint32_t i = lane(); i < len; i += kWave) {
-                uint32_t q = dst - dist + i;
-                // Separate loads keep each access in its own address space (a
-                // select between the two pointers would become a flat load).
-                uint8_t g = 0;
-                if ((int32_t)q < lds_from) g = base[q];
-                uint8_t w = win[slot(q)];
-                win[slot(dst + i)] = (int32_t)q >= lds_from ? w : g;
-            }
-        }
-        pos += len;
-        room -= len;
-    }
-    // Writes every byte produced so far to HBM.
-    __device__ __forceinline__ void finish() {
-        uint32_t end = o0 + pos;
-        while (fa < end) flush_block(end);
-    }
-};
-
-// The Deflate decoders' output: as WindowOut, but the window is linear.  It
-// holds offsets [wlo, o0 + pos) at win[x - wlo]; when an append would pass
-// its end, the complete kilobytes are flushed and the newest ones slide to
-// the front, so runs of bytes never wrap and may be read and written eight
-// at a time at any alignment.  wlo and fa are multiples of 1 KiB, and
-// everything below wlo + 512 is in HBM once wlo > 0 (appends are of at most
-// kAppend bytes), so a copy whose source starts below wlo reads HBM alone.
-template <uint32_t H>
-struct LinearOut {
-    static_assert(H >= 4096, "an append, a slide and a copy must fit");
-    static constexpr uint32_t kAppend = H - 2560;
-    uint8_t *base;  // 1 KiB aligned
-    uint8_t *win;
-    uint32_t o0, wlo, fa, cap, pos, room;
-
-    __device__ __forceinline__ void init(uint8_t *out, uint32_t capacity, uint8_t *window) {
-        o0 = (uint32_t)(reinterpret_cast<uintptr_t>(out) & 1023);
-        base = out - o0;
-        win = window;
-        wlo = 0;
-        fa = 0;
-        cap = capacity;
-        pos = 0;
-        room = H - o0;
-    }
-    // (The mask keeps the slot of an offset outside the window in bounds.)
-    __device__ __forceinline__ uint32_t slot(uint32_t x) const { return (x - wlo) & (H - 1); }
-
-    __device__ __forceinline__ void flush_block(uint32_t limit) {
-        const uint32_t a = fa + 16 * lane(), sl = a - wlo;
-        if (a >= o0 && a + 16 <= limit) {
-            *reinterpret_cast<uint4 *>(base + a) = *reinterpret_cast<const uint4 *>(win + sl);
-        } else if (a + 16 > o0 && a < limit) {
-            for (uint32_t k = 0; k < 16; k++)
-                if (a + k >= o0 && a + k < limit) base[a + k] = win[sl + k];
-        }
-        fa += 1024;
-    }
-    // Room for len <= kAppend more bytes.
-    __device__ __forceinline__ void make_room(uint32_t len) {
-        if (room >= len) return;
-        wave_sync();
-        const uint32_t at = o0 + pos;
-        while (fa + 1024 <= at) flush_block(o0 + cap);
-        const uint32_t lo = (at + len - H + 1023) & ~1023u, d = lo - wlo;
-        for (uint32_t i = 0; i < at - lo; i += 1024) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(win + d + i + 16 * lane());
-            wave_sync();
-            *reinterpret_cast<uint4 *>(win + i + 16 * lane()) = v;
-        }
-        wlo = lo;
-        room = wlo + H - at;
-        wave_sync();
-    }
-    __device__ __forceinline__ void put_literal(uint32_t b) {
-        make_room(1);
-        win[slot(o0 + pos)] = (uint8_t)b;  // same byte from every lane
-        pos++;
-        room--;
-    }
-    // Back-reference: len bytes (at most 258) from dist bytes back (dist <=
-    // pos).  With len > dist the bytes repeat with period dist.
-    __device__ __forceinline__ void copy(uint32_t dist, uint32_t len) {
-        make_room(len);
-        const uint32_t dst = o0 + pos, src = dst - dist;
-        if (src < wlo) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            for (uint32_t i = lane(); i < len; i += kWave) win[slot(dst + i)] = base[src + i];
-        } else {
-            copy_near(src, dst, dist, len);
-        }
-        pos += len;
-        room -= len;
-    }
-    // A copy within the window by the whole wave, overlapping or not.
-    __device__ __forceinline__ void copy_near(uint32_t src, uint32_t dst, uint32_t dist, uint32_t len) const {
-        if (dist >= len) {
-            for (uint32_t i = lane(); i < len; i += kWave) win[slot(dst + i)] = win[slot(src + i)];
-        } else {
-            uint32_t r = lane() % dist;
-            const uint32_t step = kWave % dist;
-            for (uint32_t i = lane(); i < len; i += kWave) {
-                win[slot(dst + i)] = win[slot(src + r)];
-                r += step;
-                if (r >= dist) r -= dist;
-            }
-        }
-        wave_sync();
-    }
-    // Writes every byte produced so far to HBM.
-    __device__ __forceinline__ void finish() {
-        const uint32_t end = o0 + pos;
-        while (fa < end) flush_block(end);
-    }
-};
 
 // Reads a dynamic block's header up to its code lengths (RFC 1951 3.2.7):
 // HLIT, HDIST, HCLEN, the code-length code (built into cltab, 7-bit
@@ -559,61 +363,49 @@ __device__ __forceinline__ int read_code_lengths(Ring &in, BitIn &bi, uint32_t *
     return CODAG_OK;
 }
 
-// Returned by the one-symbol form of inflate_symbols after a literal or a
-// copy (not a status).
-constexpr int kMore = 1;
+// Not statuses: a symbol was decoded and the block goes on; the next symbol
+// is for inflate_symbol.
+enum : int { kMore = 1, kOneSymbol = 2 };
 
-// Symbols of one Huffman block, up to and including end-of-block.  Returns
-// CODAG_OK at the end of the block or an error status; running past the end
-// of input anywhere before that point is reported as CODAG_E_TRUNCATED.
-// The loop is kept small and with few exits: literals first, then
-// length/distance pairs; everything rare leaves the loop.  With ONE, it
-// returns kMore after the first literal or copy.
-template <int TB, uint32_t H, bool ONE = false, class Ring>
-__device__ __forceinline__ int inflate_symbols(Ring &in, BitIn &bi, LinearOut<H> &o, DeflateLds<TB, H> *lds) {
+// One symbol of a Huffman block, however unusual: kMore after a literal or a
+// copy, CODAG_OK at the end of the block, or an error status; running past
+// the end of input at or before that point is CODAG_E_TRUNCATED.
+template <int TB, uint32_t H, class Ring>
+__device__ __forceinline__ int inflate_symbol(Ring &in, BitIn &bi, LinearOut<H> &o, DeflateLds<TB, H> *lds) {
+    bi.refill1(in);
+    uint32_t e = uni(lds->tab[bi.peek(TB)]);
+    if (e & kEntSlow) e = uni(slow_entry((uint32_t)bi.buf, TB, &lds->meta[0], lds->sorted, kLitLen));
+    bi.skip(ent_cl(e));
     int st;
-    for (;;) {
-        bi.refill1(in);
-        uint32_t e = uni(lds->lit[bi.peek(TB)]);
-        if (e & kEntSlow) e = uni(slow_entry((uint32_t)bi.buf, TB, &lds->lit_meta, lds->lit_sorted, kLitLen));
-        bi.skip(ent_cl(e));
-        if (e & kEntStop) {  // end of block, or an invalid code
-            st = ent_why(e) == kWhyEob ? CODAG_OK : CODAG_E_CORRUPT;
-            break;
-        }
-        if (!(e & kEntCopy)) {
-            if (o.pos == o.cap) {
-                st = CODAG_E_OVERFLOW;
-                break;
-            }
+    if (e & kEntStop) {  // end of block, or an invalid code
+        st = ent_why(e) == kWhyEob ? CODAG_OK : CODAG_E_CORRUPT;
+    } else if (!(e & kEntCopy)) {
+        if (o.pos != o.cap) {
             o.put_literal(ent_byte(e));
-            if (ONE) return kMore;
-            continue;
+            return kMore;
         }
+        st = CODAG_E_OVERFLOW;
+    } else {
         // Length, then distance.
         const uint32_t lex = ent_lex(e);
         const uint32_t len = ent_len(e) + bi.peek(lex);
         bi.skip(lex);
         bi.refill1(in);
-        uint32_t d = uni(lds->dist[bi.peek(kDistBits)]);
-        if (d & kEntSlow) d = uni(slow_entry((uint32_t)bi.buf, kDistBits, &lds->dist_meta, lds->dist_sorted, kDist));
+        uint32_t d = uni(lds->dist()[bi.peek(kDistBits)]);
+        if (d & kEntSlow) d = uni(slow_entry((uint32_t)bi.buf, kDistBits, &lds->meta[1], lds->dist_sorted(), kDist));
         bi.skip(ent_cl(d));
-        if (d & kEntStop) {  // invalid, or a block without distance codes
-            st = CODAG_E_CORRUPT;
-            break;
+        st = CODAG_E_CORRUPT;  // an invalid code, or a block without distance codes
+        if (!(d & kEntStop)) {
+            const uint32_t dist = ent_dist(d) + bi.peek(ent_ex(d));
+            bi.skip(ent_ex(d));
+            if (dist <= o.pos) {
+                if (o.pos + len <= o.cap) {
+                    o.copy(dist, len);
+                    return kMore;
+                }
+                st = CODAG_E_OVERFLOW;
+            }
         }
-        const uint32_t dist = ent_dist(d) + bi.peek(ent_ex(d));
-        bi.skip(ent_ex(d));
-        if (dist > o.pos) {
-            st = CODAG_E_CORRUPT;
-            break;
-        }
-        if (o.pos + len > o.cap) {
-            st = CODAG_E_OVERFLOW;
-            break;
-        }
-        o.copy(dist, len);
-        if (ONE) return kMore;
     }
     return bi.remain < 0 ? CODAG_E_TRUNCATED : st;
 }
@@ -664,7 +456,7 @@ __device__ __forceinline__ void lane_token(uint32_t s0, uint32_t s1, uint32_t s2
     const uint64_t x = ((uint64_t)__builtin_amdgcn_alignbit(wc, wb, sh) << 32) |
                        __builtin_amdgcn_alignbit(wb, wa, sh);
     const uint32_t xl = (uint32_t)x;
-    const uint32_t e = lds->lit[xl & ((1u << TB) - 1)];
+    const uint32_t e = lds->tab[xl & ((1u << TB) - 1)];
     // Every lane also decodes a length/distance pair from its bits (the
     // distance lookup reads the table whatever the entry was) and the kind
     // picks the result: no branches, so no scalar mask bookkeeping.  The
@@ -674,7 +466,7 @@ __device__ __forceinline__ void lane_token(uint32_t s0, uint32_t s1, uint32_t s2
     // turn back into branches.
     const uint32_t cl = ent_cl(e), p2 = ent_bits(e);
     const uint32_t len = ent_len(e) + ((xl >> cl) & ((1u << ent_lex(e)) - 1));
-    const uint32_t d = lds->dist[(xl >> p2) & ((1u << kDistBits) - 1)];
+    const uint32_t d = lds->dist()[(xl >> p2) & ((1u << kDistBits) - 1)];
     const uint32_t q = p2 + ent_cl(d), dex = ent_ex(d);
     const uint32_t dv = ent_dist(d) + ((uint32_t)(x >> q) & ((1u << dex) - 1));
     const uint32_t odd = e & (kEntSlow | kEntStop);
@@ -925,13 +717,7 @@ __device__ __forceinline__ int inflate_batched(Ring &in, BitIn &bi, LinearOut<H>
         bi.seek(in, p >> 3);
         bi.skip(p & 7);
         if (stop == 2) return bi.remain < 0 ? CODAG_E_TRUNCATED : CODAG_OK;
-        int st = inflate_symbols<TB, H, true>(in, bi, o, lds);
-        if (st != kMore) return st;
-        p = 8 * bi.next - bi.cnt;
-        // A window's candidates depend only on its input bits: if the next
-        // token is still in window wk, they stay.
-        have = have && (p >> 6) == wk;
-        wk = p >> 6;
+        return kOneSymbol;
     }
 }
 
@@ -962,10 +748,12 @@ __device__ __forceinline__ int inflate_batched(Ring &in, BitIn &bi, LinearOut<H>
 // 4.6 but 4 KiB of input and two KiB of segment notes per wave.  Segments are
 // 64 bits because the output window bounds one step to about 340 tokens.
 // Measured against the window-by-window decoder: 16,384 chunks of 64 KiB
-// 12.49 to 5.40 ms, 48 chunks of 60 KB (one wave each, nothing else running)
-// 1,811 to 733 us, 256 KiB ORC blocks 7.33 to 2.98 ms, a learned batch of
-// 2,000 chunks 16.66 to 5.83 ms.  A wave holds 12 KiB of LDS instead of 8 (13
-// instead of 20 waves per CU), which the shorter work more than pays for.
+// 12.6 to 5.6 ms, 48 chunks of 60 KB (one wave each, nothing else running)
+// 1,814 to 624 us, a learned batch of 2,000 chunks 16.3 to 4.7 ms.
+// A wave holds 12 KiB of LDS instead of 8 (13 instead of 20 waves per CU),
+// which the shorter work more than pays for.  Smaller footprints measured
+// over 20,480 chunks: 14 waves (a 3 KiB window, 128 copies) 6.81 against 6.96
+// ms but 10% slower for a lone wave, 16 waves (192 bits a lane besides) 7.41.
 // Codes that hardly ever fall back (all of one length) would need a pass per
 // lane: past kMaxPasses a round keeps the lanes that are on the track and the
 // rest of the block goes to the window-by-window decoder.
@@ -973,105 +761,79 @@ __device__ __forceinline__ int inflate_batched(Ring &in, BitIn &bi, LinearOut<H>
 
 constexpr uint32_t kMaxPasses = 20;
 
-typedef uint64_t u64_any __attribute__((aligned(1), may_alias));
-typedef uint32_t u32_any __attribute__((aligned(1), may_alias));
-typedef uint16_t u16_any __attribute__((aligned(1), may_alias));
+// One token per lane and loop trip.  x holds the next TB bits, so the
+// literal/length lookup goes out together with the read of the eight input
+// bytes that the distance code and the extra bits come from; the distance
+// lookup is the trip's second wait.  Every lane goes through every trip, the
+// idle ones on a table entry of zero: with the loops' conditions as branches
+// around their effects, a trip spent more on execution masks than on decoding
+// (700 cycles of a lone wave).  What is rare (codes longer than the tables,
+// stops) is behind one branch that the wave takes when any lane needs it.
+template <int TB, uint32_t H>
+struct LaneToken {
+    const uint8_t *at;  // the stretch's first byte (LDS)
+    uint32_t r, x;      // next token's first bit in the stretch; its TB bits
+    uint32_t e, d;      // its entries; d is 0 for a literal
+    uint64_t raw;
 
-// Copies longer than this are made by the whole wave, one after another.
-constexpr uint32_t kLongCopy = 32;
-
-// Runs the nq queued copies of an emission step whose output starts at
-// `start`.  Their sources are the output before them: 64 copies at a time,
-// every copy whose source ends before the lowest pending copy's output goes
-// at once, eight bytes per access at any alignment (byte by byte, sixteen
-// masked stores a piece, this was the larger half of a step).
-template <uint32_t H, int TB>
-__device__ __forceinline__ void run_copies(const LinearOut<H> &o, const DeflateLds<TB, H> *lds, uint32_t nq,
-                                           uint32_t start) {
-    const uint32_t l = lane();
-    for (uint32_t k0 = 0; k0 < nq; k0 += kWave) {
-        const bool v = k0 + l < nq;
-        const uint32_t at = min(k0 + l, kCopyQueue - 1);
-        const uint32_t q = lds->queue[at];
-        const uint32_t len = v ? (q & 255) + 3 : 0u, dist = ((q >> 8) & 0x7fff) + 1;
-        const uint32_t dst = start + lds->queue_dst[at], src = dst - dist;
-        const bool far = v && src < o.wlo;  // left the window: wholly in HBM
-        if (ballot(far)) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        uint64_t pend = ballot(v);
-        while (pend) {
-            const uint32_t t = (uint32_t)__builtin_ctzll(pend), front = readlane(dst, t);
-            const bool ready = ((pend >> l) & 1) && src + len <= front;
-            const uint64_t rm = ballot(ready);
-            if (!rm) {  // the lowest pending copy repeats its own output
-                o.copy_near(readlane(src, t), front, readlane(dist, t), readlane(len, t));
-                pend &= pend - 1;
-                continue;
+    __device__ __forceinline__ void read() { raw = *reinterpret_cast<const u64_any *>(at + (r >> 3)); }
+    __device__ __forceinline__ void start(const uint8_t *stretch, uint32_t bit) {
+        at = stretch;
+        r = bit;
+        read();
+        x = (uint32_t)(raw >> (r & 7));
+    }
+    // The low 32 bits from the token on: length code and extra bits end by
+    // bit 20, the distance lookup's index by bit 28.
+    __device__ __forceinline__ uint32_t bits() const { return (uint32_t)(raw >> (r & 7)); }
+    // Looks the token up; true if some lane's needs resolve().
+    __device__ __forceinline__ bool look(const DeflateLds<TB, H> *lds, bool on) {
+        e = lds->tab[on ? x & ((1u << TB) - 1) : DeflateLds<TB, H>::kIdle];
+        read();
+        const uint32_t d0 = lds->dist()[(bits() >> ent_bits(e)) & ((1u << kDistBits) - 1)];
+        d = d0 & (uint32_t)((int32_t)e >> 31);
+        return ballot(((e | d) & (kEntSlow | kEntStop)) != 0) != 0;
+    }
+    // Codes longer than the tables; true if the lane's token is a stop.
+    __device__ __forceinline__ bool resolve(const DeflateLds<TB, H> *lds) {
+        if (!((e | d) & (kEntSlow | kEntStop))) return false;
+        const uint64_t b = raw >> (r & 7);
+        if (e & kEntSlow) {
+            e = slow_entry((uint32_t)b, TB, &lds->meta[0], lds->sorted, kLitLen);
+            d = (e & kEntCopy) ? lds->dist()[(uint32_t)(b >> ent_bits(e)) & ((1u << kDistBits) - 1)] : 0u;
+        }
+        if (d & kEntSlow)
+            d = slow_entry((uint32_t)(b >> ent_bits(e)), kDistBits, &lds->meta[1], lds->sorted + 288, kDist);
+        return ((e | d) & kEntStop) != 0;
+    }
+    __device__ __forceinline__ uint32_t length() const {
+        return ent_len(e) + ((bits() >> ent_cl(e)) & ((1u << ent_lex(e)) - 1));
+    }
+    __device__ __forceinline__ uint32_t distance() const {
+        return ent_dist(d) + ((uint32_t)(raw >> ((r & 7) + ent_bits(e) + ent_cl(d))) & ((1u << ent_ex(d)) - 1));
+    }
+    // Past the token.  Of raw's 57 bits from r on, the longest token leaves
+    // nine.
+    __device__ __forceinline__ void next() {
+        const uint32_t n = ent_bits(e) + ent_bits(d), old = r;
+        r += n;
+        x = (uint32_t)(raw >> ((old & 7) + n));
+        if constexpr (TB > 9) {
+            if (ballot(n > 57 - TB)) {
+                read();
+                x = bits();
             }
-            if (ready && len <= kLongCopy) {
-                uint8_t *const to = o.win + (dst - o.wlo);
-                const uint32_t tail = len > 8 ? len - 8 : 0u;
-                uint64_t a, b;
-                if (far) {
-                    a = *reinterpret_cast<const u64_any *>(o.base + src);
-                    b = *reinterpret_cast<const u64_any *>(o.base + src + tail);
-                } else {
-                    const uint8_t *from = o.win + (src - o.wlo);
-                    a = *reinterpret_cast<const u64_any *>(from);
-                    b = *reinterpret_cast<const u64_any *>(from + tail);
-                }
-                if (len >= 8) {
-                    *reinterpret_cast<u64_any *>(to) = a;
-                    for (uint32_t j = 8; j < tail; j += 8) {
-                        uint64_t m;
-                        if (far) m = *reinterpret_cast<const u64_any *>(o.base + src + j);
-                        else m = *reinterpret_cast<const u64_any *>(o.win + (src - o.wlo) + j);
-                        *reinterpret_cast<u64_any *>(to + j) = m;
-                    }
-                    *reinterpret_cast<u64_any *>(to + tail) = b;
-                } else if (len >= 4) {
-                    *reinterpret_cast<u32_any *>(to) = (uint32_t)a;
-                    *reinterpret_cast<u32_any *>(to + len - 4) = (uint32_t)(a >> (8 * (len - 4)));
-                } else {
-                    *reinterpret_cast<u16_any *>(to) = (uint16_t)a;
-                    to[2] = (uint8_t)(a >> 16);
-                }
-            }
-            for (uint64_t lm = ballot(ready && len > kLongCopy); lm; lm &= lm - 1) {
-                const uint32_t k = (uint32_t)__builtin_ctzll(lm);
-                const uint32_t cs = readlane(src, k), cd = readlane(dst, k), cl = readlane(len, k);
-                const uint32_t j = min(8 * l, cl - 8);
-                if (8 * l < cl) {
-                    uint64_t a;
-                    if (cs < o.wlo) a = *reinterpret_cast<const u64_any *>(o.base + cs + j);
-                    else a = *reinterpret_cast<const u64_any *>(o.win + (cs - o.wlo) + j);
-                    *reinterpret_cast<u64_any *>(o.win + (cd - o.wlo) + j) = a;
-                }
-            }
-            pend &= ~rm;
-            wave_sync();
         }
     }
-}
-
-// One token from its bits (raw >> sh): its table entries, the slow codes
-// resolved.  d is 0 (no bits) for a literal.
-template <int TB, uint32_t H>
-__device__ __forceinline__ void token_entries(uint64_t bits, const DeflateLds<TB, H> *lds, uint32_t &e, uint32_t &d) {
-    const uint32_t x = (uint32_t)bits;
-    e = lds->lit[x & ((1u << TB) - 1)];
-    if (e & kEntSlow) e = slow_entry(x, TB, &lds->lit_meta, lds->lit_sorted, kLitLen);
-    // The length code and its extra bits end by bit 20.
-    const uint32_t d0 = lds->dist[(x >> ent_bits(e)) & ((1u << kDistBits) - 1)];
-    d = (e & kEntCopy) ? d0 : 0u;
-    if (d & kEntSlow)
-        d = slow_entry((uint32_t)(bits >> ent_bits(e)), kDistBits, &lds->dist_meta, lds->dist_sorted, kDist);
-}
+};
 
 template <int TB, uint32_t H, class Ring>
-__device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &o, DeflateLds<TB, H> *lds) {
+__device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &o, DeflateLds<TB, H> *lds,
+                                             bool &windows) {
     static_assert(Ring::kLdsWords <= kRoundInWords, "the round's input takes the ring's place");
     const uint32_t l = lane();
     uint8_t *const inb = reinterpret_cast<uint8_t *>(in.ring);
+    uint8_t *const spare = reinterpret_cast<uint8_t *>(&lds->queue[kCopyQueue]);
     const uint32_t endbit = 8 * in.gend;
     uint32_t p = 8 * bi.next - bi.cnt;  // bit position of the next code
     for (;;) {
@@ -1126,43 +888,37 @@ __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &
                 poor = true;
                 break;
             }
+            LaneToken<TB, H> t;
+            t.start(mine, rs);
+            bool on = need;
+            uint32_t sp = rs, acc = 0;  // the segment's first token; its output bytes << 12 | copies << 6
             if (need) {
                 tried = rs;
                 why = 0;
-                uint32_t r = rs, sp = rs, acc = 0;  // acc: output bytes << 12 | copies << 6
-                do {
-                    const uint64_t bits = *reinterpret_cast<const u64_any *>(mine + (r >> 3)) >> (r & 7);
-                    uint32_t e, d;
-                    token_entries(bits, lds, e, d);
-                    if ((e | d) & kEntStop) {
-                        why = (e & kEntStop) ? ent_why(e) : (uint32_t)kWhyInvalid;
-                        break;
-                    }
-                    acc += ((ent_len(e) + (((uint32_t)bits >> ent_cl(e)) & ((1u << ent_lex(e)) - 1))) << 12) +
-                           ((e >> 31) << 6);
-                    const uint32_t r2 = r + ent_bits(e) + ent_bits(d);
-                    if ((r ^ r2) & ~(kSegBits - 1)) {
-                        lds->segs[kLaneSegs * l + r / kSegBits] = (sp & (kSegBits - 1)) | acc;
-                        sp = r2;
-                        acc = 0;
-                    }
-                    r = r2;
-                } while (r < kLaneBits);
-                rz = re = r;
-                if (why) {
-                    lds->segs[kLaneSegs * l + r / kSegBits] = (sp & (kSegBits - 1)) | acc;
-                    if (why == kWhyEob) {
-                        // The end-of-block code's length, from its entry again.
-                        const uint64_t bits = *reinterpret_cast<const u64_any *>(mine + (r >> 3)) >> (r & 7);
-                        uint32_t e, d;
-                        token_entries(bits, lds, e, d);
-                        re = r + ent_cl(e);
-                    }
-                }
             }
+            do {
+                if (t.look(lds, on) && t.resolve(lds)) {
+                    why = (t.e & kEntStop) ? ent_why(t.e) : (uint32_t)kWhyInvalid;
+                    rz = t.r;
+                    re = why == kWhyEob ? t.r + ent_cl(t.e) : t.r;
+                    lds->segs[kLaneSegs * l + t.r / kSegBits] = (sp & (kSegBits - 1)) | acc;
+                    t.e = t.d = 0;
+                    on = false;
+                }
+                acc += (t.length() << 12) + ((t.e >> 31) << 6);
+                const uint32_t from = t.r;
+                t.next();
+                if ((from ^ t.r) & ~(kSegBits - 1)) {
+                    lds->segs[kLaneSegs * l + from / kSegBits] = (sp & (kSegBits - 1)) | acc;
+                    sp = t.r;
+                    acc = 0;
+                }
+                on = on && t.r < kLaneBits;
+            } while (ballot(on));
+            if (need && !why) rz = re = t.r;
             // Start over where the lane before ended (if it did not stop).
             const uint32_t ue = wave_shift_up1(why ? ~0u : re);
-            if (l != 0 && ue != ~0u) rs = ue - kLaneBits;
+            if (l != 0 && l < live && ue != ~0u) rs = ue - kLaneBits;
             const uint64_t moved = ballot(l < live && rs != tried);
             const uint64_t stops = ballot(l < live && why != 0) & (moved ? (moved & (0 - moved)) - 1 : ~0ull);
             if (stops) live = (uint32_t)__builtin_ctzll(stops) + 1;  // a true stop: nothing follows it
@@ -1187,34 +943,36 @@ __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &
             o.make_room(made);
             const uint32_t start = o.o0 + o.pos, lim = o.o0 + o.cap;
             uint32_t dst = start + (incl >> 12) - so, qi = (incl & 4095) - sc;
-            uint32_t r = c & (kSegBits - 1);
             const uint32_t er = whyl && g == nseg - 1 ? zl & (kSegBits - 1) : kSegBits;
+            const bool tight = start + made > lim;  // the output range ends in this step
             int bad = CODAG_OK;
-            if (l < cnt) {
-                const uint8_t *const seg = inb + ofs + (kSegBits / 8) * g;
-                while (r < er) {
-                    const uint64_t bits = *reinterpret_cast<const u64_any *>(seg + (r >> 3)) >> (r & 7);
-                    uint32_t e, d;
-                    token_entries(bits, lds, e, d);
-                    const uint32_t len = ent_len(e) + (((uint32_t)bits >> ent_cl(e)) & ((1u << ent_lex(e)) - 1));
-                    if (part && (dst - start + len > LinearOut<H>::kAppend || qi == kCopyQueue)) break;
-                    r += ent_bits(e) + ent_bits(d);
-                    if (dst + len > lim) bad = CODAG_E_OVERFLOW;
-                    if (e & kEntCopy) {
-                        const uint32_t dist = ent_dist(d) + ((uint32_t)(bits >> (ent_bits(e) + ent_cl(d))) &
-                                                             ((1u << ent_ex(d)) - 1));
-                        if (dist > dst - o.o0) bad = CODAG_E_CORRUPT;
-                        if (bad) break;
-                        lds->queue[qi] = (len - 3) | ((dist - 1) << 8);
-                        lds->queue_dst[qi] = (uint16_t)(dst - start);
-                        qi++;
-                    } else {
-                        if (bad) break;
-                        o.win[dst - o.wlo] = (uint8_t)ent_byte(e);
-                    }
-                    dst += len;
+            LaneToken<TB, H> t;
+            t.start(inb + ofs + (kSegBits / 8) * min(g, nseg - 1), c & (kSegBits - 1));
+            bool on = l < cnt && t.r < er;
+            while (ballot(on)) {
+                if (t.look(lds, on)) t.resolve(lds);
+                uint32_t len = t.length();
+                if (part && on && (dst - start + len > LinearOut<H>::kAppend || qi == kCopyQueue)) {
+                    t.e = t.d = len = 0;  // the step is full
+                    on = false;
                 }
+                const bool copy = (int32_t)t.e < 0;
+                const uint32_t dist = t.distance();
+                if (ballot(copy && dist > dst - o.o0) || tight) {
+                    if (on && dst + len > lim) bad = CODAG_E_OVERFLOW;
+                    if (copy && dist > dst - o.o0) bad = CODAG_E_CORRUPT;
+                }
+                const bool lit = on && !copy && !bad;
+                uint8_t *const to = lit ? o.win + (dst - o.wlo) : spare;
+                *to = (uint8_t)ent_byte(t.e);
+                const bool queued = copy && !bad;
+                lds->queue[queued ? qi : kCopyQueue] = copy_entry(len, dst - start, dist);
+                qi += queued ? 1u : 0u;
+                dst += bad ? 0u : len;
+                t.next();
+                on = on && t.r < er && !bad;
             }
+            const uint32_t r = t.r;
             wave_sync();
             const uint64_t badm = ballot(bad != CODAG_OK);
             const uint32_t bl = badm ? (uint32_t)__builtin_ctzll(badm) : 0u;  // the first bad token's lane
@@ -1222,7 +980,7 @@ __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &
                 nq = readlane(qi, bl);
                 made = readlane(dst, bl) - start;
             }
-            run_copies<H, TB>(o, lds, nq, start);
+            run_copies<H>(o, lds->queue, nq, start);
             o.pos += made;
             o.room -= made;
             if (badm)
@@ -1245,10 +1003,8 @@ __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &
         bi.seek(in, p >> 3);
         bi.skip(p & 7);
         if (whyl == kWhyEob) return p > endbit ? CODAG_E_TRUNCATED : CODAG_OK;
-        if (!whyl) return inflate_batched<TB, H>(in, bi, o, lds);
-        const int st = inflate_symbols<TB, H, true>(in, bi, o, lds);
-        if (st != kMore) return st;
-        p = 8 * bi.next - bi.cnt;
+        windows = !whyl;
+        return whyl ? kOneSymbol : kMore;
     }
 }
 
@@ -1295,7 +1051,7 @@ __device__ __forceinline__ int inflate_leader(Ring &in, BitIn &bi, LinearOut<H> 
         }
         bi.seek(in, p >> 3);
         bi.skip(p & 7);
-        int st = inflate_symbols<TB, H, true>(in, bi, o, lds);
+        const int st = inflate_symbol<TB, H>(in, bi, o, lds);
         if (st != kMore) return st;
         p = 8 * bi.next - bi.cnt;
     }
@@ -1317,6 +1073,7 @@ __device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t c
     bi.seek(in, in.skip);
     LinearOut<H> o;
     o.init(out, cap, lds->window);
+    lds->tab[DeflateLds<TB, H>::kIdle] = 0;
     bool fixed_ready = false;
     int st = CODAG_OK;
 
@@ -1361,40 +1118,47 @@ __device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t c
                         lds->lens[s] = (uint8_t)v;
                     }
                     __builtin_amdgcn_wave_barrier();
-                    build_table(lds->lens, 288, TB, kLitLen, lds->lit, lds->lit_sorted, &lds->lit_meta);
-                    build_table(lds->lens + 288, 32, kDistBits, kDist, lds->dist, lds->dist_sorted,
-                                &lds->dist_meta);
+                    build_table(lds->lens, 288, TB, kLitLen, lds->tab, lds->sorted, &lds->meta[0]);
+                    build_table(lds->lens + 288, 32, kDistBits, kDist, lds->dist(), lds->dist_sorted(),
+                                &lds->meta[1]);
                     fixed_ready = true;
                 }
             } else {
                 // Dynamic block header (RFC 1951 section 3.2.7).
                 fixed_ready = false;
                 uint32_t hlit, hdist, hclen;
-                st = read_code_lengths(in, bi, lds->dist, &lds->dist_meta, lds->dist_sorted,
+                st = read_code_lengths(in, bi, lds->dist(), &lds->meta[1], lds->dist_sorted(),
                                        lds->lens, hlit, hdist, hclen);
                 if (st) break;
                 __builtin_amdgcn_wave_barrier();
                 if (uni((uint32_t)lds->lens[256]) == 0) { st = CODAG_E_CORRUPT; break; }
-                BuildResult lr = build_table(lds->lens, hlit, TB, kLitLen, lds->lit, lds->lit_sorted,
-                                             &lds->lit_meta);
+                BuildResult lr = build_table(lds->lens, hlit, TB, kLitLen, lds->tab, lds->sorted,
+                                             &lds->meta[0]);
                 if (lr.left < 0 || (lr.left > 0 && !(lr.total == 1 && lr.ones == 1))) {
                     st = CODAG_E_CORRUPT;
                     break;
                 }
-                BuildResult dr = build_table(lds->lens + hlit, hdist, kDistBits, kDist, lds->dist,
-                                             lds->dist_sorted, &lds->dist_meta);
+                BuildResult dr = build_table(lds->lens + hlit, hdist, kDistBits, kDist, lds->dist(),
+                                             lds->dist_sorted(), &lds->meta[1]);
                 if (dr.left < 0 || (dr.left > 0 && dr.total != 0 && !(dr.total == 1 && dr.ones == 1))) {
                     st = CODAG_E_CORRUPT;
                     break;
                 }
                 // Without distance codes (total 0) every table entry is invalid.
             }
-            if constexpr (MODE == kLeaderLane)
+            if constexpr (MODE == kLeaderLane) {
                 st = inflate_leader<TB, H>(in, bi, o, lds);
-            else if constexpr (Ring::kLaneRounds)
-                st = inflate_lanes<TB, H>(in, bi, o, lds);
-            else
-                st = inflate_batched<TB, H>(in, bi, o, lds);
+            } else {
+                bool windows = !Ring::kLaneRounds;
+                do {
+                    if constexpr (Ring::kLaneRounds)
+                        st = windows ? inflate_batched<TB, H>(in, bi, o, lds)
+                                     : inflate_lanes<TB, H>(in, bi, o, lds, windows);
+                    else
+                        st = inflate_batched<TB, H>(in, bi, o, lds);
+                    if (st == kOneSymbol) st = inflate_symbol<TB, H>(in, bi, o, lds);
+                } while (st == kMore);
+            }
             if (st) break;
         }
         if (last) break;
