@@ -181,10 +181,11 @@ __device__ __forceinline__ int lz4_sequence(LinearIn &in, LinearOut<H> &o, Lz4Ld
     mlen = mlen + 4 < mlen ? 0xffffffffu : mlen + 4;
     if (off == 0 || off > o.pos + s.made) return CODAG_E_CORRUPT;
     if (mlen > cap - o.pos - s.made) return CODAG_E_OVERFLOW;
-    // Pieces of at most kMaxCopy bytes; each repeats the bytes `off` back, so
-    // splitting a match does not change what it writes.
+    // Pieces of at most kMaxCopy bytes, none below the three that a copy has at
+    // least; each repeats the bytes `off` back, so splitting a match does not
+    // change what it writes.
     while (mlen) {
-        const uint32_t n = min(mlen, kMaxCopy);
+        const uint32_t n = mlen > kMaxCopy ? kMaxCopy - 8 : mlen;
         if (s.made + n > kAppend || s.nq == kCopyQueue) {
             lz4_end(o, lds, s);
             lz4_begin(o, s);

@@ -51,6 +51,7 @@ def _block(rng, lit_choices, match_choices, off_choices, total):
     ([0, 1, 2, 3, 4, 7, 8, 13, 14], [4, 5, 8, 18, 19], [4, 17, 2000, 5000, 65535]),
     ([0, 14, 15, 16, 269, 270, 600], [4, 18, 19, 20, 272, 273, 274, 275], [1, 8, 273, 4096, 30000]),
     ([1], [273], [1, 7, 272, 273, 274]),                            # steps that end by bytes
+    ([0, 1, 5], [511, 512, 513, 514, 515, 516, 1017, 1018, 1025, 1026], [1, 4, 7, 600]),  # matches made in pieces
     ([0, 2000], [600, 1535, 1536, 2560, 9000], [1, 511, 512, 513, 6000]),
 ])
 def test_steps(dev, lits, matches, offs):
