@@ -60,10 +60,15 @@ enum {
  *   lit_table_bits    Deflate literal/length lookup-table bits, 9 or 10
  *                     (default 9); longer codes take a slower path.
  *   history_kib       Deflate and LZ4 output window kept in LDS per wave: 2,
- *                     4, 8, 16 or 32 KiB (default 4 for Deflate, 2 for
- *                     LZ4).  Back-references reaching
+ *                     4, 8, 16 or 32 KiB (default 4; 2 is served by the
+ *                     4 KiB window).  Back-references reaching
  *                     further read the already written output from HBM.
  *                     With 32 the workgroup holds one wave.
+ *                     Deflate launches of at most 512 chunks, and ZLIB
+ *                     streams of as many, that set none of waves_per_block,
+ *                     lit_table_bits, history_kib and chunk_ticks are
+ *                     decoded by a workgroup of 8 or 16 waves per chunk with
+ *                     a 32 KiB window.
  *   chunk_ticks       optional device array (n_chunks uint64): receives each
  *                     chunk's decode time in shader clock cycles.
  *   group_parallel    RLE codecs: 0 = automatic (RLE v1 launches of at

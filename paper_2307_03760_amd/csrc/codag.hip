@@ -194,7 +194,7 @@ int decompress(int codec, const uint8_t *comp_buf, const uint64_t *chunk_offsets
                               (uint32_t)n_chunks, chunk_status, ds->err, s);
     if (typed)
         return launch_typed(codec, eb, uns != 0, comp_buf, chunk_offsets, out_buf, out_offsets,
-                            (uint32_t)n_chunks, chunk_status, ds->err, ticks, s);
+                            (uint32_t)n_chunks, chunk_status, ds->err, ticks, opts && opts->group_parallel == 1, s);
     switch (codec) {
         case CODAG_RLE_V1: {
             const int gp = opts ? opts->group_parallel : 0;
@@ -224,6 +224,12 @@ int decompress(int codec, const uint8_t *comp_buf, const uint64_t *chunk_offsets
             return launch_lz4(comp_buf, chunk_offsets, out_buf, out_offsets, n_chunks, wpb, hist,
                               chunk_status, ds->err, ticks, s);
         default:
+            // Few chunks, and nothing asked of the one-wave decoder: a team of
+            // waves each.
+            if (n_chunks <= kTeamMaxChunks && !ticks &&
+                !(opts && (opts->waves_per_block || opts->lit_table_bits || opts->history_kib)))
+                return launch_deflate_team(comp_buf, chunk_offsets, out_buf, out_offsets, (uint32_t)n_chunks,
+                                           chunk_status, ds->err, s);
             if (tb == 9)
                 return launch_deflate<9>(comp_buf, chunk_offsets, out_buf, out_offsets, n_chunks,
                                          wpb, hist, chunk_status, ds->err, ticks, s);

@@ -189,13 +189,9 @@ constexpr uint32_t kRoundSegs = kWave * kLaneSegs;
 // and the eight-byte reads past the last bit, in 16-byte pieces.
 constexpr uint32_t kRoundPieces = kWave * kLaneBits / 128 + 2, kRoundInWords = 4 * kRoundPieces;
 
-// What one wave keeps in LDS while inflating, besides its input: the Huffman
-// tables, the output history window and the lane-parallel decoder's lists.
-// (The window comes first: LZ4 uses a Deflate slice's.)
-template <int TB, uint32_t H>
-struct DeflateLds {
-    uint8_t window[H];
-    uint8_t window_pad[16];  // eight-byte reads may pass the window's end
+// A block's Huffman tables.
+template <int TB>
+struct DeflateTables {
     // Literal/length codes, distance codes (their part also serves the
     // code-length code), and one zero: the entry of a lane with nothing to
     // decode, which takes no bits and makes no output.
@@ -203,15 +199,23 @@ struct DeflateLds {
     uint32_t tab[(1u << TB) + (1u << kDistBits) + 1];
     CodeMeta meta[2];
     uint16_t sorted[288 + 32];
+
+    __device__ __forceinline__ uint32_t *dist() { return tab + (1u << TB); }
+    __device__ __forceinline__ const uint32_t *dist() const { return tab + (1u << TB); }
+    __device__ __forceinline__ uint16_t *dist_sorted() { return sorted + 288; }
+};
+
+// What one wave keeps in LDS while inflating, besides its input: the Huffman
+// tables, the output history window and the lane-parallel decoder's lists.
+template <int TB, uint32_t H>
+struct DeflateLds : DeflateTables<TB> {
     union {
         uint8_t lens[320];          // while a block's tables are built
         uint32_t segs[kRoundSegs];  // while its symbols decode
     };
     uint64_t queue[kCopyQueue + 1];  // pending copies, and a spare
-
-    __device__ __forceinline__ uint32_t *dist() { return tab + (1u << TB); }
-    __device__ __forceinline__ const uint32_t *dist() const { return tab + (1u << TB); }
-    __device__ __forceinline__ uint16_t *dist_sorted() { return sorted + 288; }
+    __attribute__((aligned(16))) uint8_t window[H];
+    uint8_t window_pad[16];  // eight-byte reads may pass the window's end
 };
 
 // Wave-uniform LSB-first bit reader over the ring.
@@ -328,6 +332,51 @@ __device__ __forceinline__ int read_code_lengths(Ring &in, BitIn &bi, uint32_t *
     BuildResult cl = build_table(lens, 19, kCodeLenBits, kCodeLen, cltab, sorted, meta);
     if (cl.left != 0) return CODAG_E_CORRUPT;
     uint32_t idx = 0, total = hlit + hdist, prev = 0;
+    // The lengths a 64-bit window at a time: every lane decodes the symbol
+    // that would start at its bit, a walk marks the real ones, a prefix sum
+    // gives their places.  (Symbol by symbol a block's 300 lengths took about
+    // 350 cycles each, a tenth of a 64 KiB chunk's time.)  Anything unusual --
+    // the end of the input near, a repeat past the last length or without one
+    // before it -- is left to the loop below.
+    for (uint32_t s = l; s < 320; s += kWave) lens[s] = 0;
+    wave_sync();
+    uint32_t p = 8 * bi.next - bi.cnt;
+    while (idx < total && p + 128 <= 8 * in.gend) {
+        in.ensure((p >> 3) + 24);
+        const uint32_t a = p + l;
+        const uint32_t x = __builtin_amdgcn_alignbit(in.word((a >> 5) + 1), in.word(a >> 5), a & 31);
+        const uint32_t e = cltab[x & ((1u << kCodeLenBits) - 1)];
+        const uint32_t sym = ent_sym(e), cl = ent_cl(e);
+        const uint32_t ex = sym < 16 ? 0u : sym == 16 ? 2u : sym == 17 ? 3u : 7u;
+        const uint32_t rep = (sym < 16 ? 1u : sym == 18 ? 11u : 3u) + ((x >> cl) & ((1u << ex) - 1));
+        const uint32_t step = (cl + ex) | (rep << 8);
+        uint32_t t = 0, n = idx;
+        uint64_t mark = 0;
+        while (t < kWave && n < total) {
+            const uint32_t w = readlane(step, t);
+            mark |= 1ull << t;
+            t += w & 255;
+            n += w >> 8;
+        }
+        const uint64_t m16 = ballot(sym == 16);
+        if (n > total || (idx == 0 && (m16 & 1))) break;
+        const bool mine = (mark >> l) & 1;
+        const uint32_t reps = mine ? rep : 0u;
+        const uint32_t at = idx + wave_inclusive_sum32(reps) - reps;
+        const uint32_t own = sym < 16 ? sym : 0u;
+        const uint64_t below = mark & ~m16 & ((1ull << l) - 1);
+        const uint32_t pulled = lane_pull(own, 63 - (uint32_t)__builtin_clzll(below | 1));
+        const uint32_t val = sym != 16 ? own : below ? pulled : prev;
+        if (mine && val) {
+            const uint32_t k = sym == 16 ? rep : 1u;  // 1, or 3..6
+            for (uint32_t j = 0; j < k; j++) lens[at + j] = (uint8_t)val;
+        }
+        prev = readlane(val, 63 - (uint32_t)__builtin_clzll(mark));
+        idx = n;
+        p += t;
+    }
+    bi.seek(in, p >> 3);
+    bi.skip(p & 7);
     while (idx < total) {
         bi.refill(in);
         uint32_t e = uni(cltab[bi.peek(kCodeLenBits)]);
@@ -769,7 +818,7 @@ constexpr uint32_t kMaxPasses = 20;
 // around their effects, a trip spent more on execution masks than on decoding
 // (700 cycles of a lone wave).  What is rare (codes longer than the tables,
 // stops) is behind one branch that the wave takes when any lane needs it.
-template <int TB, uint32_t H>
+template <int TB>
 struct LaneToken {
     const uint8_t *at;  // the stretch's first byte (LDS)
     uint32_t r, x;      // next token's first bit in the stretch; its TB bits
@@ -787,15 +836,15 @@ struct LaneToken {
     // bit 20, the distance lookup's index by bit 28.
     __device__ __forceinline__ uint32_t bits() const { return (uint32_t)(raw >> (r & 7)); }
     // Looks the token up; true if some lane's needs resolve().
-    __device__ __forceinline__ bool look(const DeflateLds<TB, H> *lds, bool on) {
-        e = lds->tab[on ? x & ((1u << TB) - 1) : DeflateLds<TB, H>::kIdle];
+    __device__ __forceinline__ bool look(const DeflateTables<TB> *lds, bool on) {
+        e = lds->tab[on ? x & ((1u << TB) - 1) : DeflateTables<TB>::kIdle];
         read();
         const uint32_t d0 = lds->dist()[(bits() >> ent_bits(e)) & ((1u << kDistBits) - 1)];
         d = d0 & (uint32_t)((int32_t)e >> 31);
         return ballot(((e | d) & (kEntSlow | kEntStop)) != 0) != 0;
     }
     // Codes longer than the tables; true if the lane's token is a stop.
-    __device__ __forceinline__ bool resolve(const DeflateLds<TB, H> *lds) {
+    __device__ __forceinline__ bool resolve(const DeflateTables<TB> *lds) {
         if (!((e | d) & (kEntSlow | kEntStop))) return false;
         const uint64_t b = raw >> (r & 7);
         if (e & kEntSlow) {
@@ -827,6 +876,69 @@ struct LaneToken {
     }
 };
 
+// One pass of the lanes with `need`: the tokens from bit rs of the lane's
+// stretch on.  re is where the lane ended, rz the token it stopped at (why:
+// kWhyEob, ...; 0: it did not); segs gets its segments' first tokens, output
+// bytes << 12 and copies << 6.
+template <int TB>
+__device__ __forceinline__ void lane_pass(const DeflateTables<TB> *lds, uint32_t *segs, const uint8_t *mine, bool need,
+                                          uint32_t rs, uint32_t &tried, uint32_t &re, uint32_t &rz, uint32_t &why) {
+    LaneToken<TB> t;
+    t.start(mine, rs);
+    bool on = need;
+    uint32_t sp = rs, acc = 0;
+    if (need) {
+        tried = rs;
+        why = 0;
+    }
+    do {
+        if (t.look(lds, on) && t.resolve(lds)) {
+            why = (t.e & kEntStop) ? ent_why(t.e) : (uint32_t)kWhyInvalid;
+            rz = t.r;
+            re = why == kWhyEob ? t.r + ent_cl(t.e) : t.r;
+            segs[t.r / kSegBits] = (sp & (kSegBits - 1)) | acc;
+            t.e = t.d = 0;
+            on = false;
+        }
+        acc += (t.length() << 12) + ((t.e >> 31) << 6);
+        const uint32_t from = t.r;
+        t.next();
+        if ((from ^ t.r) & ~(kSegBits - 1)) {
+            segs[from / kSegBits] = (sp & (kSegBits - 1)) | acc;
+            sp = t.r;
+            acc = 0;
+        }
+        on = on && t.r < kLaneBits;
+    } while (ballot(on));
+    if (need && !why) rz = re = t.r;
+}
+
+// Writes the looked-up token of an emitting lane: a literal into the window, a
+// copy into the queue at qi (its last entry, queue[spare_at], takes the other
+// lanes' stores).  A token whose distance reaches before the chunk or whose
+// output passes its end sets bad and stops the lane.
+template <int TB, uint32_t H>
+__device__ __forceinline__ void emit_token(LaneToken<TB> &t, const LinearOut<H> &o, uint64_t *queue, uint32_t spare_at,
+                                           uint8_t *spare, uint32_t start, uint32_t lim, bool tight, bool &on,
+                                           uint32_t er, uint32_t &dst, uint32_t &qi, int &bad) {
+    const uint32_t len = t.length();
+    const bool copy = (int32_t)t.e < 0;
+    const uint32_t dist = t.distance();
+    if (ballot(copy && dist > dst - o.o0) || tight) {
+        if (on && dst + len > lim) bad = CODAG_E_OVERFLOW;
+        if (copy && dist > dst - o.o0) bad = CODAG_E_CORRUPT;
+    }
+    const bool lit = on && !copy && !bad;
+    uint8_t *const to = lit ? o.win + (dst - o.wlo) : spare;
+    *to = (uint8_t)ent_byte(t.e);
+    const bool queued = copy && !bad;
+    queue[queued ? qi : spare_at] = copy_entry(len, dst - start, dist);
+    qi += queued ? 1u : 0u;
+    dst += bad ? 0u : len;
+    t.next();
+    on = on && t.r < er && !bad;
+}
+
 template <int TB, uint32_t H, class Ring>
 __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &o, DeflateLds<TB, H> *lds,
                                              bool &windows) {
@@ -843,30 +955,7 @@ __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &
         // ---- the round's input
         const uint32_t b0 = p & ~(kSegBits - 1), a0 = (b0 >> 3) & ~15u, ofs = (b0 >> 3) & 15;
         wave_sync();
-#pragma unroll
-        for (uint32_t k = 0; k < 3; k++) {
-            const uint32_t idx = kWave * k + l, at = a0 + 16 * idx;
-            if (idx < kRoundPieces && at < in.gend)
-                __builtin_amdgcn_global_load_lds(in.gbase + at, (lds_void *)(in.ring + 256 * k), 16, 0, 0);
-        }
-        wait_vm();
-        if (a0 + 16 * kRoundPieces > in.gend) {  // zero the bytes past the end of the chunk
-#pragma unroll
-            for (uint32_t k = 0; k < 3; k++) {
-                const uint32_t idx = kWave * k + l, at = a0 + 16 * idx;
-                if (idx < kRoundPieces && at + 16 > in.gend) {
-                    const uint32_t valid = at < in.gend ? in.gend - at : 0;
-                    uint4 v = valid ? reinterpret_cast<const uint4 *>(in.ring)[idx] : make_uint4(0, 0, 0, 0);
-                    uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                    for (int j = 0; j < 4; j++) {
-                        const int keep = (int)valid - 4 * j;
-                        w[j] &= keep >= 4 ? 0xffffffffu : keep <= 0 ? 0u : ((1u << (8 * keep)) - 1);
-                    }
-                    reinterpret_cast<uint4 *>(in.ring)[idx] = make_uint4(w[0], w[1], w[2], w[3]);
-                }
-            }
-        }
+        load_pieces<kRoundPieces, kWave>(in.gbase, in.gend, a0, in.ring, l);
         wave_sync();
 
         // ---- passes: every lane's tokens, until every start is true
@@ -888,34 +977,7 @@ __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &
                 poor = true;
                 break;
             }
-            LaneToken<TB, H> t;
-            t.start(mine, rs);
-            bool on = need;
-            uint32_t sp = rs, acc = 0;  // the segment's first token; its output bytes << 12 | copies << 6
-            if (need) {
-                tried = rs;
-                why = 0;
-            }
-            do {
-                if (t.look(lds, on) && t.resolve(lds)) {
-                    why = (t.e & kEntStop) ? ent_why(t.e) : (uint32_t)kWhyInvalid;
-                    rz = t.r;
-                    re = why == kWhyEob ? t.r + ent_cl(t.e) : t.r;
-                    lds->segs[kLaneSegs * l + t.r / kSegBits] = (sp & (kSegBits - 1)) | acc;
-                    t.e = t.d = 0;
-                    on = false;
-                }
-                acc += (t.length() << 12) + ((t.e >> 31) << 6);
-                const uint32_t from = t.r;
-                t.next();
-                if ((from ^ t.r) & ~(kSegBits - 1)) {
-                    lds->segs[kLaneSegs * l + from / kSegBits] = (sp & (kSegBits - 1)) | acc;
-                    sp = t.r;
-                    acc = 0;
-                }
-                on = on && t.r < kLaneBits;
-            } while (ballot(on));
-            if (need && !why) rz = re = t.r;
+            lane_pass<TB>(lds, lds->segs + kLaneSegs * l, mine, need, rs, tried, re, rz, why);
             // Start over where the lane before ended (if it did not stop).
             const uint32_t ue = wave_shift_up1(why ? ~0u : re);
             if (l != 0 && l < live && ue != ~0u) rs = ue - kLaneBits;
@@ -946,31 +1008,16 @@ __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &
             const uint32_t er = whyl && g == nseg - 1 ? zl & (kSegBits - 1) : kSegBits;
             const bool tight = start + made > lim;  // the output range ends in this step
             int bad = CODAG_OK;
-            LaneToken<TB, H> t;
+            LaneToken<TB> t;
             t.start(inb + ofs + (kSegBits / 8) * min(g, nseg - 1), c & (kSegBits - 1));
             bool on = l < cnt && t.r < er;
             while (ballot(on)) {
                 if (t.look(lds, on)) t.resolve(lds);
-                uint32_t len = t.length();
-                if (part && on && (dst - start + len > LinearOut<H>::kAppend || qi == kCopyQueue)) {
-                    t.e = t.d = len = 0;  // the step is full
+                if (part && on && (dst - start + t.length() > LinearOut<H>::kAppend || qi == kCopyQueue)) {
+                    t.e = t.d = 0;  // the step is full
                     on = false;
                 }
-                const bool copy = (int32_t)t.e < 0;
-                const uint32_t dist = t.distance();
-                if (ballot(copy && dist > dst - o.o0) || tight) {
-                    if (on && dst + len > lim) bad = CODAG_E_OVERFLOW;
-                    if (copy && dist > dst - o.o0) bad = CODAG_E_CORRUPT;
-                }
-                const bool lit = on && !copy && !bad;
-                uint8_t *const to = lit ? o.win + (dst - o.wlo) : spare;
-                *to = (uint8_t)ent_byte(t.e);
-                const bool queued = copy && !bad;
-                lds->queue[queued ? qi : kCopyQueue] = copy_entry(len, dst - start, dist);
-                qi += queued ? 1u : 0u;
-                dst += bad ? 0u : len;
-                t.next();
-                on = on && t.r < er && !bad;
+                emit_token<TB, H>(t, o, lds->queue, kCopyQueue, spare, start, lim, tight, on, er, dst, qi, bad);
             }
             const uint32_t r = t.r;
             wave_sync();
@@ -1064,16 +1111,16 @@ __device__ __forceinline__ int inflate_leader(Ring &in, BitIn &bi, LinearOut<H> 
 enum : int { kAllLanes = 0, kLeaderLane = 1 };
 
 // With `made` non-null the output range is a capacity: a final block that
-// ends inside it is OK and *made receives the bytes produced.
-template <int TB, uint32_t H, int MODE = kAllLanes, class Ring>
-__device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t cap,
-                                              DeflateLds<TB, H> *lds, uint32_t *made = nullptr) {
-    const uint32_t l = lane();
+// ends inside it is OK and *made receives the bytes produced.  `symbols`
+// decodes a Huffman block's symbols once its tables are built, up to and
+// including end-of-block, and returns a status.
+template <int TB, uint32_t H, class Ring, class Symbols>
+__device__ __forceinline__ int inflate_chunk(Ring &in, LinearOut<H> &o, DeflateLds<TB, H> *lds, uint32_t *made,
+                                             Symbols symbols) {
+    const uint32_t l = lane(), cap = o.cap;
     BitIn bi;
     bi.seek(in, in.skip);
-    LinearOut<H> o;
-    o.init(out, cap, lds->window);
-    lds->tab[DeflateLds<TB, H>::kIdle] = 0;
+    lds->tab[DeflateTables<TB>::kIdle] = 0;
     bool fixed_ready = false;
     int st = CODAG_OK;
 
@@ -1093,7 +1140,14 @@ __device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t c
             if (o.pos + len > cap) { st = CODAG_E_OVERFLOW; break; }
             uint32_t p = bi.byte_pos();
             if (p + len > in.gend) { st = CODAG_E_TRUNCATED; break; }
-            for (uint32_t done = 0; done < len;) {
+            uint32_t done = 0;
+            if constexpr (Ring::kLaneRounds) {
+                if (len >= LinearOut<H>::kStream) {
+                    o.stream(in.gbase + p, len);
+                    done = len;
+                }
+            }
+            while (done < len) {
                 uint32_t piece = min(len - done, Ring::kFetch / 2);
                 o.make_room(piece);
                 in.ensure(p + done + piece + 4);
@@ -1146,19 +1200,7 @@ __device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t c
                 }
                 // Without distance codes (total 0) every table entry is invalid.
             }
-            if constexpr (MODE == kLeaderLane) {
-                st = inflate_leader<TB, H>(in, bi, o, lds);
-            } else {
-                bool windows = !Ring::kLaneRounds;
-                do {
-                    if constexpr (Ring::kLaneRounds)
-                        st = windows ? inflate_batched<TB, H>(in, bi, o, lds)
-                                     : inflate_lanes<TB, H>(in, bi, o, lds, windows);
-                    else
-                        st = inflate_batched<TB, H>(in, bi, o, lds);
-                    if (st == kOneSymbol) st = inflate_symbol<TB, H>(in, bi, o, lds);
-                } while (st == kMore);
-            }
+            st = symbols(bi);
             if (st) break;
         }
         if (last) break;
@@ -1170,6 +1212,30 @@ __device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t c
         return CODAG_OK;
     }
     return o.pos == cap ? CODAG_OK : CODAG_E_UNDERFLOW;
+}
+
+template <int TB, uint32_t H, int MODE = kAllLanes, class Ring>
+__device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t cap,
+                                              DeflateLds<TB, H> *lds, uint32_t *made = nullptr) {
+    LinearOut<H> o;
+    o.init(out, cap, lds->window);
+    return inflate_chunk<TB, H>(in, o, lds, made, [&](BitIn &bi) {
+        if constexpr (MODE == kLeaderLane) {
+            return inflate_leader<TB, H>(in, bi, o, lds);
+        } else {
+            int st;
+            bool windows = !Ring::kLaneRounds;
+            do {
+                if constexpr (Ring::kLaneRounds)
+                    st = windows ? inflate_batched<TB, H>(in, bi, o, lds)
+                                 : inflate_lanes<TB, H>(in, bi, o, lds, windows);
+                else
+                    st = inflate_batched<TB, H>(in, bi, o, lds);
+                if (st == kOneSymbol) st = inflate_symbol<TB, H>(in, bi, o, lds);
+            } while (st == kMore);
+            return st;
+        }
+    });
 }
 
 }  // namespace codag

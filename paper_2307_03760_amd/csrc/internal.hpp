@@ -52,11 +52,35 @@ int launch_variant(int variant, int codec, const uint8_t *comp, const uint64_t *
                    const uint64_t *ooff, uint32_t n, int32_t *status, unsigned long long *err,
                    hipStream_t s);
 
-// Byte RLE and RLE element types other than signed 8-byte values (one wave
-// per chunk), on stream s.
+// Deflate by a workgroup of waves per chunk, on stream s, for launches of up to
+// kTeamMaxChunks chunks.
+int launch_deflate_team(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff, uint32_t n,
+                        int32_t *status, unsigned long long *err, hipStream_t s);
+constexpr uint32_t kTeamMaxChunks = 512;
+
+// The chunks of a compressed ORC stream, as its headers give them.
+struct OrcFrame {
+    uint64_t src;  // first byte of the chunk's payload in the framed stream
+    uint32_t len;  // payload bytes
+    uint32_t original;
+};
+
+struct OrcMeta {
+    uint32_t count;     // chunks found
+    uint32_t complete;  // the last chunk found ends the stream (no bytes after it)
+    unsigned long long key;  // first failure: chunk << 4 | -status, or all ones
+    uint64_t last;           // bytes the last chunk produced
+};
+
+// Decodes every ZLIB chunk of a stream with a workgroup of waves each.
+void launch_orc_frame_team(const uint8_t *framed, uint32_t block, uint8_t *out, uint64_t out_cap,
+                           const OrcFrame *frames, uint32_t max_frames, OrcMeta *meta, hipStream_t s);
+
+// Byte RLE and RLE element types other than signed 8-byte values, on stream
+// s; one_wave: one wave per chunk whatever the launch's size.
 int launch_typed(int codec, int elem_bytes, bool is_unsigned, const uint8_t *comp, const uint64_t *coff,
                  uint8_t *out, const uint64_t *ooff, uint32_t n, int32_t *status,
-                 unsigned long long *err, uint64_t *ticks, hipStream_t s);
+                 unsigned long long *err, uint64_t *ticks, bool one_wave, hipStream_t s);
 
 // Arguments of one batched launch (a captured graph is reused while they
 // stay the same).

@@ -58,30 +58,7 @@ struct LinearIn {
     __device__ __forceinline__ void load(uint32_t pos) {
         a0 = pos & ~15u;
         wave_sync();
-#pragma unroll
-        for (uint32_t k = 0; k < 2; k++) {
-            const uint32_t idx = kWave * k + lane(), at = a0 + 16 * idx;
-            if (idx < kPieces && at < gend)
-                __builtin_amdgcn_global_load_lds(gbase + at, (lds_void *)(buf + 256 * k), 16, 0, 0);
-        }
-        wait_vm();
-        if (a0 + kBytes > gend) {
-#pragma unroll
-            for (uint32_t k = 0; k < 2; k++) {
-                const uint32_t idx = kWave * k + lane(), at = a0 + 16 * idx;
-                if (idx < kPieces && at + 16 > gend) {
-                    const uint32_t valid = at < gend ? gend - at : 0;
-                    uint4 v = valid ? reinterpret_cast<const uint4 *>(buf)[idx] : make_uint4(0, 0, 0, 0);
-                    uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                    for (int j = 0; j < 4; j++) {
-                        const int keep = (int)valid - 4 * j;
-                        w[j] &= keep >= 4 ? 0xffffffffu : keep <= 0 ? 0u : ((1u << (8 * keep)) - 1);
-                    }
-                    reinterpret_cast<uint4 *>(buf)[idx] = make_uint4(w[0], w[1], w[2], w[3]);
-                }
-            }
-        }
+        load_pieces<kPieces, kWave>(gbase, gend, a0, buf, lane());
         wave_sync();
     }
     // Bytes [pos, pos + n) readable (n <= kMost).

@@ -40,6 +40,39 @@ typedef __attribute__((address_space(3))) void lds_void;
 // the landing buffer are preceded by this explicitly.
 __device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0f70); }
 
+// Loads P sixteen-byte pieces from position a0 (a multiple of 16) into an LDS
+// buffer with T threads, t this one's number (whole waves take part); bytes
+// past gend read as zero.  Waits for this wave's own pieces.
+template <uint32_t P, uint32_t T>
+__device__ __forceinline__ void load_pieces(const uint8_t *gbase, uint32_t gend, uint32_t a0, uint32_t *buf, uint32_t t) {
+    constexpr uint32_t kTurns = (P + T - 1) / T;
+    const uint32_t w = t & ~63u;
+#pragma unroll
+    for (uint32_t k = 0; k < kTurns; k++) {
+        const uint32_t idx = T * k + t, at = a0 + 16 * idx;
+        if (idx < P && at < gend)
+            __builtin_amdgcn_global_load_lds(gbase + at, (lds_void *)(buf + 4 * (T * k + uni(w))), 16, 0, 0);
+    }
+    wait_vm();
+    if (a0 + 16 * P > gend) {
+#pragma unroll
+        for (uint32_t k = 0; k < kTurns; k++) {
+            const uint32_t idx = T * k + t, at = a0 + 16 * idx;
+            if (idx < P && at + 16 > gend) {
+                const uint32_t valid = at < gend ? gend - at : 0;
+                uint4 v = valid ? reinterpret_cast<const uint4 *>(buf)[idx] : make_uint4(0, 0, 0, 0);
+                uint32_t x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const int keep = (int)valid - 4 * j;
+                    x[j] &= keep >= 4 ? 0xffffffffu : keep <= 0 ? 0u : ((1u << (8 * keep)) - 1);
+                }
+                reinterpret_cast<uint4 *>(buf)[idx] = make_uint4(x[0], x[1], x[2], x[3]);
+            }
+        }
+    }
+}
+
 // F is the fetch size (a multiple of 1 KiB); the ring holds 2F bytes.
 template <uint32_t F>
 struct InRingT {

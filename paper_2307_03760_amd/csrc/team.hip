@@ -1,0 +1,454 @@
+// Deflate by one workgroup per chunk, for launches with few chunks.
+//
+// One wave per chunk leaves most of the GPU idle when there are a few dozen
+// chunks, and each wave's time is a chain of dependent steps.  Here kTeam
+// waves decode a chunk together: a round of the lane-parallel decoder takes
+// kTeam x 64 x 256 bits, and the emission steps, the copies, the window's
+// flushes and slides are shared the same way.  Wave 0 alone reads block
+// headers, builds tables and takes whatever is rare; the others wait for
+// rounds.  The passes' trip count hardly grows with the number of lanes, so
+// a round costs about what a wave's round costs and takes kTeam times the
+// input.
+//
+// Measured against one wave per chunk: 48 chunks of 60 KB 624 to 187 us, 49
+// ORC blocks of 256 KiB 2.58 to 0.66 ms, 256 chunks of 64 KiB 689 to 195 us
+// with teams of 16; 512 chunks of 64 KiB 727 to 302 us with teams of 8.  1,024
+// chunks fill the GPU a wave each (780 us against 899 in teams of 8), hence
+// the limits.  Of a 64 KiB text chunk's 405,000 cycles the passes take some
+// 130,000, the copies 80,000, the block header and its tables 55,000.
+#include <hip/hip_runtime.h>
+
+#include "../../include/codag.h"
+#include "decode.hpp"
+#include "internal.hpp"
+
+namespace codag {
+
+constexpr uint32_t kTeamH = 32768;  // output window
+
+// Decoding by kTeam waves (8 or 16).
+template <uint32_t kTeam>
+struct Team {
+static constexpr uint32_t kTeamThreads = kTeam * kWave;
+static constexpr uint32_t kTeamQueue = kTeam * 160;
+static constexpr uint32_t kTeamPieces = kTeamThreads * kLaneBits / 128 + 2;
+// Lanes off the track at the end of a pass pass it on; a longer line of them
+// is a little likelier with more lanes.
+static constexpr uint32_t kTeamPasses = kMaxPasses + 4;
+// A step always takes a segment: at most 32 copies, 258 bytes each.
+static_assert(LinearOut<kTeamH>::kAppend >= 32 * 258 && kTeamQueue >= 32, "a step fits a segment");
+
+struct Lds {
+    DeflateLds<9, kTeamH> d;  // tables, window, and wave 0's own lists
+    uint32_t in[4 * kTeamPieces];
+    uint32_t segs[kTeam * kRoundSegs];
+    uint64_t queue[kTeamQueue + 1];
+    // Wave 0's orders: rounds from bit p on, or no more; and its output state.
+    uint32_t go, p, pos, wlo, fa, room;
+    // What the waves tell each other: where the last lane of each ended
+    // (~0: it stopped), its first lane of interest, its sums.
+    uint32_t edge[kTeam], first[kTeam], stop[kTeam], sum_out[kTeam], sum_cop[kTeam];
+    uint32_t last_why, last_z, last_e, made, nq;
+    uint32_t bad_lane[kTeam], bad_st[kTeam], bad_r[kTeam], bad_dst[kTeam], bad_qi[kTeam];
+    unsigned long long made_bits[kTeamQueue / kWave];  // copies made, a bit each
+};
+
+// The smallest wave * 64 + v[wave] over the waves (v < 64, or 64 for none):
+// kTeamThreads when there is none.
+static __device__ __forceinline__ uint32_t first_lane(const uint32_t *v) {
+    uint32_t r = kTeamThreads;
+#pragma unroll
+    for (uint32_t w = 0; w < kTeam; w++) {
+        const uint32_t x = uni(v[w]);
+        if (x < kWave && w * kWave + x < r) r = w * kWave + x;
+    }
+    return r;
+}
+
+// Room for len <= kAppend more bytes, by the whole team (the same decision on
+// every wave).
+static __device__ __forceinline__ void room(LinearOut<kTeamH> &o, uint32_t len, uint32_t tid) {
+    if (o.room >= len) return;
+    constexpr uint32_t kBlock = LinearOut<kTeamH>::kBlock;
+    const uint32_t at = o.o0 + o.pos;
+    if (o.fa < o.o0 && o.fa + kBlock <= at) {  // the chunk starts inside its first block
+        if (tid < kWave) o.flush_block(o.o0 + o.cap);
+        else o.fa += kBlock;
+    }
+    const uint32_t fe = at & ~(kBlock - 1);
+    for (uint32_t a = o.fa + 16 * tid; a < fe; a += 16 * kTeamThreads)
+        *reinterpret_cast<uint4 *>(o.base + a) = *reinterpret_cast<const uint4 *>(o.win + (a - o.wlo));
+    o.fa = max(o.fa, fe);
+    const uint32_t lo = (at + len - kTeamH + kBlock - 1) & ~(kBlock - 1), d = lo - o.wlo;
+    static_assert(kTeamH % (16 * kTeamThreads) == 0, "a slide's steps end at the window's end");
+    for (uint32_t i = 0; i < at - lo; i += 16 * kTeamThreads) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(o.win + d + i + 16 * tid);
+        __syncthreads();
+        *reinterpret_cast<uint4 *>(o.win + i + 16 * tid) = v;
+        __syncthreads();
+    }
+    o.wlo = lo;
+    o.room = lo + kTeamH - at;
+    wait_vm();  // the flushed bytes are there for any wave's copies
+    __syncthreads();
+}
+
+// Copies whose output starts below offset x of the step (they are in output
+// order).
+static __device__ __forceinline__ uint32_t copies_below(const uint64_t *queue, uint32_t nq, uint32_t x) {
+    uint32_t lo = 0;
+#pragma unroll
+    for (uint32_t step = kTeamQueue >= 2048 ? 2048 : 1024; step; step >>= 1) {
+        const uint32_t k = lo + step;
+        const uint32_t at = ((uint32_t)queue[min(k, kTeamQueue) - 1] >> 16) & 0xffff;
+        if (k <= nq && at < x) lo = k;
+    }
+    return lo;
+}
+
+// The nq queued copies of a step that starts at `start`.  The waves take them
+// 64 at a time, in order; a copy is made once the copies that overlap its
+// source are -- found by bisection, and looked up in a bitmap of the copies
+// made -- so a step takes as many rounds as copies of copies are deep.  (With
+// every copy waiting for all the copies below its source's end, 1,100 copies
+// of text took 64,000 cycles.)
+static __device__ __forceinline__ void copies(const LinearOut<kTeamH> &o, Lds *s, uint32_t nq, uint32_t start,
+                                            uint32_t wave) {
+    const uint32_t l = lane();
+    if (threadIdx.x < kTeamQueue / kWave) s->made_bits[threadIdx.x] = 0;
+    __syncthreads();
+    for (uint32_t k0 = wave * kWave; k0 < nq; k0 += kTeamThreads) {
+        const uint32_t k = k0 + l;
+        const bool v = k < nq;
+        const uint64_t q = s->queue[min(k, kTeamQueue - 1)];
+        const uint32_t len = v ? (uint32_t)q & 0xffff : 0u, dist = (uint32_t)(q >> 32);
+        const uint32_t at = (uint32_t)q >> 16, dst = start + at, src = dst - dist;
+        const bool far = v && src < o.wlo;
+        const bool repeats = v && dist < len;  // its own output
+        // Copies d0 .. d1 - 1 overlap the source [src, min(src + len, dst)).
+        uint32_t d0 = 0, d1 = 0;
+        const bool inside = v && src + len > start;
+        if (ballot(inside)) {
+            const uint32_t from = inside && src > start ? src - start : 0u;
+            const uint32_t to = inside ? min(at, at - dist + len) : 0u;
+            d1 = inside ? copies_below(s->queue, nq, to) : 0u;
+            // Few copies fit between the source's ends: walk down to the first
+            // that reaches past `from`.
+            d0 = d1;
+            bool more = d0 != 0;
+            while (ballot(more)) {
+                const uint32_t p = (uint32_t)s->queue[d0 - (more ? 1 : 0)];
+                more = more && (p >> 16) + (p & 0xffff) > from;
+                d0 -= more ? 1u : 0u;
+                more = more && d0 != 0;
+            }
+        }
+        if (ballot(far)) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        uint64_t pend = ballot(v);
+        const uint64_t all = pend;
+        while (pend) {
+            bool ready = (pend >> l) & 1;
+            for (uint32_t w = d0 / 64; ballot(ready && 64 * w < d1); w++) {
+                if (ready && 64 * w < d1) {
+                    uint64_t need = ~0ull;
+                    if (64 * w < d0) need &= ~0ull << (d0 & 63);
+                    if (64 * w + 64 > d1) need &= ~(~0ull << (d1 & 63));
+                    const uint64_t done = __hip_atomic_load(&s->made_bits[w], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    ready = (need & ~done) == 0;
+                }
+            }
+            const uint64_t rm = ballot(ready);
+            if (!rm) {
+                __builtin_amdgcn_s_sleep(1);  // the lowest pending copy of all goes on
+                continue;
+            }
+            make_copies(o, ready && !repeats, far, src, dst, len);
+            for (uint64_t m = ballot(ready && repeats); m; m &= m - 1) {
+                const uint32_t t = (uint32_t)__builtin_ctzll(m);
+                o.copy_near(readlane(src, t), readlane(dst, t), readlane(dist, t), readlane(len, t));
+            }
+            pend &= ~rm;
+            wave_sync();
+            if (l == 0)
+                __hip_atomic_store(&s->made_bits[k0 / kWave], all & ~pend, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+    __syncthreads();
+}
+
+// Rounds from bit p on until the block ends, an error, or something for wave
+// 0 alone: as inflate_lanes, with the same result on every wave.  p is left
+// at the next bit.
+static __device__ __forceinline__ int rounds(const uint8_t *gbase, uint32_t gend, uint32_t &p, LinearOut<kTeamH> &o,
+                                           Lds *s, uint32_t wave, bool &windows) {
+    constexpr uint32_t kAppend = LinearOut<kTeamH>::kAppend;
+    const uint32_t l = lane(), tid = wave * kWave + l;
+    uint8_t *const inb = reinterpret_cast<uint8_t *>(s->in);
+    uint8_t *const spare = reinterpret_cast<uint8_t *>(&s->queue[kTeamQueue]);
+    const uint32_t endbit = 8 * gend;
+    for (;;) {
+        if (p >= endbit) return CODAG_E_TRUNCATED;
+        const uint32_t b0 = p & ~(kSegBits - 1), a0 = (b0 >> 3) & ~15u, ofs = (b0 >> 3) & 15;
+        load_pieces<kTeamPieces, kTeamThreads>(gbase, gend, a0, s->in, tid);
+        __syncthreads();
+
+        // ---- passes
+        const uint8_t *const mine = inb + ofs + (kLaneBits / 8) * tid;
+        uint32_t live = min(kTeamThreads, (endbit - b0 + kLaneBits - 1) / kLaneBits);
+        uint32_t rs = tid == 0 ? p - b0 : 0u;
+        uint32_t tried = ~0u, re = 0, rz = 0, why = 0;
+        uint32_t m = 0;
+        bool poor = false;
+        for (uint32_t pass = 0;; pass++) {
+            const bool need = tid < live && rs != tried;
+            if (ballot(need))
+                lane_pass<9>(&s->d, s->segs + kLaneSegs * tid, mine, need, rs, tried, re, rz, why);
+            if (l == kWave - 1) s->edge[wave] = why ? ~0u : re;
+            __syncthreads();
+            uint32_t ue = wave_shift_up1(why ? ~0u : re);
+            const uint32_t ee = wave ? s->edge[wave - 1] : ~0u;
+            if (l == 0) ue = ee;
+            if (tid != 0 && tid < live && ue != ~0u) rs = ue - kLaneBits;
+            const uint64_t mv = ballot(tid < live && rs != tried), sm = ballot(tid < live && why != 0);
+            if (l == 0) {
+                s->first[wave] = mv ? (uint32_t)__builtin_ctzll(mv) : kWave;
+                s->stop[wave] = sm ? (uint32_t)__builtin_ctzll(sm) : kWave;
+            }
+            __syncthreads();
+            const uint32_t fm = first_lane(s->first), fs = first_lane(s->stop);
+            if (fs < fm) live = min(live, fs + 1);  // a true stop: nothing follows it
+            if (fm >= live) {
+                m = live;
+                break;
+            }
+            if (pass + 1 == kTeamPasses) {
+                m = fm;
+                poor = true;
+                break;
+            }
+        }
+        if (wave == (m - 1) / kWave) {
+            const uint32_t ll = (m - 1) % kWave;
+            const uint32_t a = readlane(why, ll), b = readlane(rz, ll), c = readlane(re, ll);
+            if (l == 0) {
+                s->last_why = a;
+                s->last_z = b;
+                s->last_e = c;
+            }
+        }
+        __syncthreads();
+        const uint32_t whyl = uni(s->last_why), zl = uni(s->last_z);
+        const uint32_t nseg = kLaneSegs * (m - 1) + (whyl ? zl / kSegBits + 1 : kLaneSegs);
+        p = b0 + kLaneBits * (m - 1) + uni(s->last_e);
+
+        // ---- write the segments
+        for (uint32_t g0 = 0; g0 < nseg;) {
+            const uint32_t g = g0 + tid;
+            const uint32_t c = g < nseg ? s->segs[g] : 0u;
+            const uint32_t so = c >> 12, sc = (c >> 6) & 63;
+            uint32_t io = wave_inclusive_sum32(so), ic = wave_inclusive_sum32(sc);
+            if (l == kWave - 1) {
+                s->sum_out[wave] = io;
+                s->sum_cop[wave] = ic;
+            }
+            __syncthreads();
+            for (uint32_t w = 0; w < wave; w++) {
+                io += uni(s->sum_out[w]);
+                ic += uni(s->sum_cop[w]);
+            }
+            const uint64_t over = ballot(g >= nseg || io > kAppend || ic > kTeamQueue);
+            if (l == 0) s->first[wave] = over ? (uint32_t)__builtin_ctzll(over) : kWave;
+            __syncthreads();
+            const uint32_t cnt = first_lane(s->first);  // 1 or more
+            if (tid == cnt - 1) {
+                s->made = io;
+                s->nq = ic;
+            }
+            __syncthreads();
+            uint32_t made = uni(s->made), nq = uni(s->nq);
+            room(o, made, tid);
+            const uint32_t start = o.o0 + o.pos, lim = o.o0 + o.cap;
+            const bool tight = start + made > lim;  // the output range ends in this step
+            uint32_t dst = start + io - so, qi = ic - sc;
+            const uint32_t er = whyl && g == nseg - 1 ? zl & (kSegBits - 1) : kSegBits;
+            int bad = CODAG_OK;
+            LaneToken<9> t;
+            t.start(inb + ofs + (kSegBits / 8) * min(g, nseg - 1), c & (kSegBits - 1));
+            bool on = tid < cnt && t.r < er;
+            while (ballot(on)) {
+                if (t.look(&s->d, on)) t.resolve(&s->d);
+                emit_token<9, kTeamH>(t, o, s->queue, kTeamQueue, spare, start, lim, tight, on, er, dst, qi, bad);
+            }
+            const uint64_t badm = ballot(bad != CODAG_OK);
+            if (badm) {
+                const uint32_t bl = (uint32_t)__builtin_ctzll(badm);
+                const uint32_t bs = readlane((uint32_t)bad, bl), br = readlane(t.r, bl), bd = readlane(dst, bl),
+                               bq = readlane(qi, bl);
+                if (l == 0) {
+                    s->bad_st[wave] = bs;
+                    s->bad_r[wave] = br;
+                    s->bad_dst[wave] = bd;
+                    s->bad_qi[wave] = bq;
+                }
+            }
+            if (l == 0) s->bad_lane[wave] = badm ? (uint32_t)__builtin_ctzll(badm) : kWave;
+            __syncthreads();
+            const uint32_t fb = first_lane(s->bad_lane);  // the first bad token's lane
+            if (fb < kTeamThreads) {
+                nq = uni(s->bad_qi[fb / kWave]);
+                made = uni(s->bad_dst[fb / kWave]) - start;
+            }
+            copies(o, s, nq, start, wave);
+            o.pos += made;
+            o.room -= made;
+            if (fb < kTeamThreads) {
+                const int st = (int)uni(s->bad_st[fb / kWave]);
+                return b0 + kSegBits * (g0 + fb) + uni(s->bad_r[fb / kWave]) > endbit ? CODAG_E_TRUNCATED : st;
+            }
+            g0 += cnt;
+            __syncthreads();
+        }
+        if (whyl == kWhyEob) return p > endbit ? CODAG_E_TRUNCATED : CODAG_OK;
+        if (whyl) return kOneSymbol;
+        if (poor) {
+            windows = true;
+            return kMore;
+        }
+        __syncthreads();  // the round's input is done with
+    }
+}
+
+// One chunk by the workgroup; the status is wave 0's.
+static __device__ __forceinline__ int chunk(const uint8_t *chunk, uint32_t len, uint8_t *out, uint32_t cap,
+                                          uint32_t *made, Lds *s, uint32_t *ring, uint32_t wave) {
+    DirectRing<512> in;
+    in.init(chunk, len, ring, nullptr);
+    LinearOut<kTeamH> o;
+    o.init(out, cap, s->d.window);
+    if (wave != 0) {
+        for (;;) {
+            __syncthreads();  // wave 0's orders
+            const uint32_t go = uni(s->go);
+            uint32_t p = uni(s->p);
+            o.pos = uni(s->pos);
+            o.wlo = uni(s->wlo);
+            o.fa = uni(s->fa);
+            o.room = uni(s->room);
+            __syncthreads();  // everyone has read them
+            if (!go) break;
+            bool windows = false;
+            rounds(in.gbase, in.gend, p, o, s, wave, windows);
+        }
+        return CODAG_OK;
+    }
+    const int st = inflate_chunk<9, kTeamH>(in, o, &s->d, made, [&](BitIn &bi) {
+        int r;
+        bool windows = false;
+        do {
+            if (windows) {
+                r = inflate_batched<9, kTeamH>(in, bi, o, &s->d);
+            } else {
+                uint32_t p = 8 * bi.next - bi.cnt;
+                if (lane() == 0) {
+                    s->go = 1;
+                    s->p = p;
+                    s->pos = o.pos;
+                    s->wlo = o.wlo;
+                    s->fa = o.fa;
+                    s->room = o.room;
+                }
+                wait_vm();  // what wave 0 wrote out is there for the others
+                __syncthreads();
+                __syncthreads();
+                r = rounds(in.gbase, in.gend, p, o, s, 0, windows);
+                in.restart(p >> 3);
+                bi.seek(in, p >> 3);
+                bi.skip(p & 7);
+            }
+            if (r == kOneSymbol) r = inflate_symbol<9, kTeamH>(in, bi, o, &s->d);
+        } while (r == kMore);
+        return r;
+    });
+    if (lane() == 0) s->go = 0;
+    __syncthreads();
+    __syncthreads();
+    return st;
+}
+
+};  // Team
+
+// A team of 16 takes a CU's LDS, of 8 half of it.
+constexpr uint32_t kBigTeamMaxChunks = 256;
+
+template <uint32_t kTeam>
+__global__ void __launch_bounds__(kTeam * kWave) __attribute__((amdgpu_waves_per_eu(4)))
+    deflate_team(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff, uint32_t n,
+                 int32_t *status, unsigned long long *err) {
+    __shared__ __align__(16) typename Team<kTeam>::Lds s;
+    __shared__ __align__(16) uint32_t s_ring[DirectRing<512>::kLdsWords];
+    const uint32_t wave = uni(threadIdx.x / kWave), c = blockIdx.x;
+    if (c >= n) return;
+    const uint64_t i0 = coff[c], i1 = coff[c + 1], o0 = ooff[c], o1 = ooff[c + 1];
+    int st = CODAG_E_INVALID_ARGUMENT;
+    if ((((i1 - i0) | (o1 - o0)) >> 31) == 0 && i1 - i0 < (1u << 28))
+        st = Team<kTeam>::chunk(comp + i0, (uint32_t)(i1 - i0), out + o0, (uint32_t)(o1 - o0), nullptr, &s, s_ring, wave);
+    if (wave == 0) report(c, st, status, err);
+}
+
+int launch_deflate_team(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff, uint32_t n,
+                        int32_t *status, unsigned long long *err, hipStream_t s) {
+    if (n <= kBigTeamMaxChunks)
+        hipLaunchKernelGGL(deflate_team<16>, dim3(n), dim3(16 * kWave), 0, s, comp, coff, out, ooff, n, status, err);
+    else
+        hipLaunchKernelGGL(deflate_team<8>, dim3(n), dim3(8 * kWave), 0, s, comp, coff, out, ooff, n, status, err);
+    return hipGetLastError() == hipSuccess ? CODAG_OK : CODAG_E_HIP;
+}
+
+// ORC chunk f into out + f * block, as orc_frame_decode with a team per chunk.
+template <uint32_t kTeam>
+__global__ void __launch_bounds__(kTeam * kWave) __attribute__((amdgpu_waves_per_eu(4)))
+    orc_frame_team(const uint8_t *framed, uint32_t block, uint8_t *out, uint64_t out_cap, const OrcFrame *frames,
+                   OrcMeta *meta) {
+    __shared__ __align__(16) typename Team<kTeam>::Lds s;
+    __shared__ __align__(16) uint32_t s_ring[DirectRing<512>::kLdsWords];
+    const uint32_t wave = uni(threadIdx.x / kWave);
+    const uint32_t count = uni(meta->count), complete = uni(meta->complete);
+    for (uint32_t f = blockIdx.x; f < count; f += gridDim.x) {
+        const uint64_t at = (uint64_t)f * block, src = uni64(frames[f].src);
+        const uint32_t len = uni(frames[f].len), original = uni(frames[f].original);
+        const bool last = f + 1 == count && complete;  // the chunk that ends the stream
+        const uint32_t room = at >= out_cap ? 0u : (uint32_t)min((uint64_t)block, out_cap - at);
+        int st = CODAG_OK;
+        uint32_t made = 0;
+        if (original) {
+            if (len > room) {
+                st = CODAG_E_OVERFLOW;
+            } else {
+                const uint32_t share = (len / kTeam + 1023) & ~1023u, a = min(len, wave * share);
+                wave_stream(out + at + a, framed + src + a, min(len - a, share));
+                made = len;
+            }
+        } else if (len >= (1u << 28)) {
+            st = CODAG_E_INVALID_ARGUMENT;
+        } else {
+            st = Team<kTeam>::chunk(framed + src, len, out + at, room, &made, &s, s_ring, wave);
+        }
+        if (st == CODAG_OK && !last && made != block) st = made < block ? CODAG_E_UNDERFLOW : CODAG_E_OVERFLOW;
+        if (threadIdx.x == 0) {
+            if (st != CODAG_OK) atomicMin(&meta->key, (unsigned long long)error_key(f, st));
+            else if (last) meta->last = made;
+        }
+    }
+}
+
+void launch_orc_frame_team(const uint8_t *framed, uint32_t block, uint8_t *out, uint64_t out_cap,
+                           const OrcFrame *frames, uint32_t max_frames, OrcMeta *meta, hipStream_t s) {
+    if (max_frames <= kBigTeamMaxChunks)
+        hipLaunchKernelGGL(orc_frame_team<16>, dim3(max_frames), dim3(16 * kWave), 0, s, framed, block, out, out_cap,
+                           frames, meta);
+    else
+        hipLaunchKernelGGL(orc_frame_team<8>, dim3(max_frames), dim3(8 * kWave), 0, s, framed, block, out, out_cap,
+                           frames, meta);
+}
+
+}  // namespace codag

@@ -49,7 +49,7 @@ int launch_width(int eb, const uint8_t *comp, const uint64_t *coff, uint8_t *out
 
 int launch_typed(int codec, int elem_bytes, bool is_unsigned, const uint8_t *comp, const uint64_t *coff,
                  uint8_t *out, const uint64_t *ooff, uint32_t n, int32_t *status,
-                 unsigned long long *err, uint64_t *ticks, hipStream_t s) {
+                 unsigned long long *err, uint64_t *ticks, bool one_wave, hipStream_t s) {
     if (codec == CODAG_BYTE_RLE)
         return launch_t<CODAG_BYTE_RLE, I64>(comp, coff, out, ooff, n, status, err, ticks, s);
     if (codec == CODAG_RLE_V1)
@@ -62,19 +62,6 @@ int launch_typed(int codec, int elem_bytes, bool is_unsigned, const uint8_t *com
 }
 
 // ---- compressed ORC streams ------------------------------------------------
-
-struct OrcFrame {
-    uint64_t src;  // first byte of the chunk's payload in the framed stream
-    uint32_t len;  // payload bytes
-    uint32_t original;
-};
-
-struct OrcMeta {
-    uint32_t count;     // chunks found
-    uint32_t complete;  // the last chunk found ends the stream (no bytes after it)
-    unsigned long long key;  // first failure: chunk << 4 | -status, or all ones
-    uint64_t last;           // bytes the last chunk produced
-};
 
 // One wave walks the chunk headers (a few per megabyte of stream).
 __global__ void __launch_bounds__(kWave)
@@ -117,7 +104,7 @@ __global__ void __launch_bounds__(kWave)
 // Chunk f (one wave per chunk, persistent grid) into out + f * block; a
 // compressed chunk is a raw Deflate stream (ZLIB) or an LZ4 block (LZ4).
 template <int Codec>
-__global__ void __launch_bounds__(kWave)
+__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
     orc_frame_decode(const uint8_t *framed, uint32_t block, uint8_t *out, uint64_t out_cap,
                      const OrcFrame *frames, OrcMeta *meta) {
     __shared__ __align__(16) uint32_t s_ring[ring_lds_words<Codec>()];
@@ -136,7 +123,7 @@ __global__ void __launch_bounds__(kWave)
             if (len > room) {
                 st = CODAG_E_OVERFLOW;
             } else {
-                for (uint32_t i = lane(); i < len; i += kWave) out[at + i] = framed[src + i];
+                wave_stream(out + at, framed + src, len);
                 made = len;
             }
         } else if (len >= (1u << 28)) {
@@ -186,7 +173,9 @@ extern "C" int codag_orc_decompress_stream(int codec, const uint8_t *framed, uin
     OrcFrame *frames = reinterpret_cast<OrcFrame *>(static_cast<char *>(ws) + sizeof(OrcMeta));
     hipLaunchKernelGGL(orc_frames, dim3(1), dim3(kWave), 0, s, framed, framed_len, frames, max_frames, meta);
     const uint32_t grid = max_frames < 2048 ? max_frames : 2048;
-    if (codec == CODAG_DEFLATE)
+    if (codec == CODAG_DEFLATE && max_frames <= kTeamMaxChunks)
+        launch_orc_frame_team(framed, block_size, out, out_cap, frames, max_frames, meta, s);
+    else if (codec == CODAG_DEFLATE)
         hipLaunchKernelGGL(orc_frame_decode<CODAG_DEFLATE>, dim3(grid), dim3(kWave), 0, s, framed,
                            block_size, out, out_cap, frames, meta);
     else

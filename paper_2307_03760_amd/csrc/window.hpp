@@ -12,6 +12,29 @@ typedef uint64_t u64_any __attribute__((aligned(1), may_alias));
 typedef uint32_t u32_any __attribute__((aligned(1), may_alias));
 typedef uint16_t u16_any __attribute__((aligned(1), may_alias));
 
+typedef uint32_t u128_any __attribute__((ext_vector_type(4), aligned(1), may_alias));
+
+// len bytes from src to dst in HBM (not overlapping) by one wave: sixteen
+// bytes a lane at any alignment, four kilobytes in flight.  (A byte a lane,
+// each load waited for, 256 KiB took about as long as inflating them.)
+__device__ __forceinline__ void wave_stream(uint8_t *dst, const uint8_t *src, uint32_t len) {
+    const uint32_t l16 = 16 * lane();
+    uint32_t i = 0;
+    for (; i + 4096 <= len; i += 4096) {
+        u128_any v[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; k++) v[k] = *reinterpret_cast<const u128_any *>(src + i + 1024 * k + l16);
+#pragma unroll
+        for (uint32_t k = 0; k < 4; k++) *reinterpret_cast<u128_any *>(dst + i + 1024 * k + l16) = v[k];
+    }
+    for (; i < len; i += 1024) {
+        const uint32_t a = i + l16;
+        if (a + 16 <= len) *reinterpret_cast<u128_any *>(dst + a) = *reinterpret_cast<const u128_any *>(src + a);
+    }
+    const uint32_t a = (len & ~15u) + lane();
+    if (a < len) dst[a] = src[a];
+}
+
 // Output through an LDS history window.  Positions are 32-bit offsets from
 // `base`, the chunk's output address rounded down to a block (uniform values
 // stay in scalar registers; there are no scalar 64-bit ordered compares).
@@ -107,15 +130,38 @@ struct LinearOut {
     }
     // A copy within the window by the whole wave, overlapping or not.
     __device__ __forceinline__ void copy_near(uint32_t src, uint32_t dst, uint32_t dist, uint32_t len) const {
+        const uint8_t *from = win + (src - wlo);
+        uint8_t *to = win + (dst - wlo);
         if (dist >= len) {
-            for (uint32_t i = lane(); i < len; i += kWave) win[slot(dst + i)] = win[slot(src + i)];
+            for (uint32_t i = lane(); i < len; i += kWave) to[i] = from[i];
         } else {
-            uint32_t r = lane() % dist;
-            const uint32_t step = kWave % dist;
-            for (uint32_t i = lane(); i < len; i += kWave) {
-                win[slot(dst + i)] = win[slot(src + r)];
-                r += step;
-                if (r >= dist) r -= dist;
+            // Byte i is byte i mod dist of the period.  i (dist + 1) < 2^20,
+            // so with m at or up to 2 above 2^20 / dist the quotient is exact.
+            const uint32_t m = (uint32_t)(1048576.0f * __builtin_amdgcn_rcpf((float)dist)) + 2;
+            for (uint32_t i = lane(); i < len; i += kWave) to[i] = from[i - dist * ((i * m) >> 20)];
+        }
+        wave_sync();
+    }
+    // Appends len >= kStream bytes of src (HBM): straight to the output, then
+    // the window is filled from there.
+    static constexpr uint32_t kStream = 4096;
+    __device__ __forceinline__ void stream(const uint8_t *src, uint32_t len) {
+        wave_sync();
+        finish();
+        wave_stream(base + o0 + pos, src, len);
+        pos += len;
+        const uint32_t end = o0 + pos;
+        fa = end & ~(kBlock - 1);
+        wlo = fa - 2 * kBlock;
+        room = wlo + H - end;
+        // The wave's own stores, read back.
+        wait_vm();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        for (uint32_t a = wlo + 16 * lane(); a < end; a += 1024) {
+            if (a + 16 <= end) {
+                *reinterpret_cast<uint4 *>(win + (a - wlo)) = *reinterpret_cast<const uint4 *>(base + a);
+            } else {
+                for (uint32_t k = a; k < end; k++) win[k - wlo] = base[k];
             }
         }
         wave_sync();
@@ -127,7 +173,7 @@ struct LinearOut {
     }
 };
 
-// Copies waiting to be made, in output order: length (at most kMaxCopy) |
+// Copies waiting to be made, in output order: length (3 to kMaxCopy) |
 // offset of the output from the step's start << 16 | distance << 32.
 constexpr uint32_t kCopyQueue = 152, kMaxCopy = 512;
 __device__ __forceinline__ uint64_t copy_entry(uint32_t len, uint32_t at, uint32_t dist) {
@@ -136,6 +182,55 @@ __device__ __forceinline__ uint64_t copy_entry(uint32_t len, uint32_t at, uint32
 
 // Copies longer than this are made by the whole wave, one after another.
 constexpr uint32_t kLongCopy = 32;
+
+// Makes the copies of the lanes that are `ready` (sources final, in the window
+// or, `far`, in HBM; no copy overlaps its own output), eight bytes per access
+// at any alignment.
+template <uint32_t H>
+__device__ __forceinline__ void make_copies(const LinearOut<H> &o, bool ready, bool far, uint32_t src, uint32_t dst,
+                                            uint32_t len) {
+    const uint32_t l = lane();
+    if (ready && len <= kLongCopy) {
+        uint8_t *const to = o.win + (dst - o.wlo);
+        const uint32_t tail = len > 8 ? len - 8 : 0u;
+        uint64_t a, b;
+        if (far) {
+            a = *reinterpret_cast<const u64_any *>(o.base + src);
+            b = *reinterpret_cast<const u64_any *>(o.base + src + tail);
+        } else {
+            const uint8_t *from = o.win + (src - o.wlo);
+            a = *reinterpret_cast<const u64_any *>(from);
+            b = *reinterpret_cast<const u64_any *>(from + tail);
+        }
+        if (len >= 8) {
+            *reinterpret_cast<u64_any *>(to) = a;
+            for (uint32_t j = 8; j < tail; j += 8) {
+                uint64_t m;
+                if (far) m = *reinterpret_cast<const u64_any *>(o.base + src + j);
+                else m = *reinterpret_cast<const u64_any *>(o.win + (src - o.wlo) + j);
+                *reinterpret_cast<u64_any *>(to + j) = m;
+            }
+            *reinterpret_cast<u64_any *>(to + tail) = b;
+        } else if (len >= 4) {
+            *reinterpret_cast<u32_any *>(to) = (uint32_t)a;
+            *reinterpret_cast<u32_any *>(to + len - 4) = (uint32_t)(a >> (8 * (len - 4)));
+        } else {
+            *reinterpret_cast<u16_any *>(to) = (uint16_t)a;
+            to[2] = (uint8_t)(a >> 16);
+        }
+    }
+    for (uint64_t lm = ballot(ready && len > kLongCopy); lm; lm &= lm - 1) {
+        const uint32_t k = (uint32_t)__builtin_ctzll(lm);
+        const uint32_t cs = readlane(src, k), cd = readlane(dst, k), cl = readlane(len, k);
+        const uint32_t j = min(8 * l, cl - 8);
+        if (8 * l < cl) {
+            uint64_t a;
+            if (cs < o.wlo) a = *reinterpret_cast<const u64_any *>(o.base + cs + j);
+            else a = *reinterpret_cast<const u64_any *>(o.win + (cs - o.wlo) + j);
+            *reinterpret_cast<u64_any *>(o.win + (cd - o.wlo) + j) = a;
+        }
+    }
+}
 
 // Runs the nq queued copies of an emission step whose output starts at
 // `start`.  Their sources are the output before them: 64 copies at a time,
@@ -164,46 +259,7 @@ __device__ __forceinline__ void run_copies(const LinearOut<H> &o, const uint64_t
                 pend &= pend - 1;
                 continue;
             }
-            if (ready && len <= kLongCopy) {
-                uint8_t *const to = o.win + (dst - o.wlo);
-                const uint32_t tail = len > 8 ? len - 8 : 0u;
-                uint64_t a, b;
-                if (far) {
-                    a = *reinterpret_cast<const u64_any *>(o.base + src);
-                    b = *reinterpret_cast<const u64_any *>(o.base + src + tail);
-                } else {
-                    const uint8_t *from = o.win + (src - o.wlo);
-                    a = *reinterpret_cast<const u64_any *>(from);
-                    b = *reinterpret_cast<const u64_any *>(from + tail);
-                }
-                if (len >= 8) {
-                    *reinterpret_cast<u64_any *>(to) = a;
-                    for (uint32_t j = 8; j < tail; j += 8) {
-                        uint64_t m;
-                        if (far) m = *reinterpret_cast<const u64_any *>(o.base + src + j);
-                        else m = *reinterpret_cast<const u64_any *>(o.win + (src - o.wlo) + j);
-                        *reinterpret_cast<u64_any *>(to + j) = m;
-                    }
-                    *reinterpret_cast<u64_any *>(to + tail) = b;
-                } else if (len >= 4) {
-                    *reinterpret_cast<u32_any *>(to) = (uint32_t)a;
-                    *reinterpret_cast<u32_any *>(to + len - 4) = (uint32_t)(a >> (8 * (len - 4)));
-                } else {
-                    *reinterpret_cast<u16_any *>(to) = (uint16_t)a;
-                    to[2] = (uint8_t)(a >> 16);
-                }
-            }
-            for (uint64_t lm = ballot(ready && len > kLongCopy); lm; lm &= lm - 1) {
-                const uint32_t k = (uint32_t)__builtin_ctzll(lm);
-                const uint32_t cs = readlane(src, k), cd = readlane(dst, k), cl = readlane(len, k);
-                const uint32_t j = min(8 * l, cl - 8);
-                if (8 * l < cl) {
-                    uint64_t a;
-                    if (cs < o.wlo) a = *reinterpret_cast<const u64_any *>(o.base + cs + j);
-                    else a = *reinterpret_cast<const u64_any *>(o.win + (cs - o.wlo) + j);
-                    *reinterpret_cast<u64_any *>(o.win + (cd - o.wlo) + j) = a;
-                }
-            }
+            make_copies(o, ready, far, src, dst, len);
             pend &= ~rm;
             wave_sync();
         }

@@ -1,5 +1,5 @@
 """GPU parity of the lane-parallel Deflate decoder at its own edges: rounds of
-64 x 256 bits, 64-bit segments, steps bounded by output and copy count, codes
+256 bits a lane (one wave, or a team of 8 or 16 waves), 64-bit segments, steps bounded by output and copy count, codes
 that never fall back onto the track, errors inside a round."""
 import zlib
 
@@ -30,8 +30,15 @@ def _z(data, level=6, strategy=zlib.Z_DEFAULT_STRATEGY):
 
 
 def _check(dev, blobs, sizes):
+    """By teams of 16 waves, of 8 (more than 256 chunks) and by one wave a chunk."""
     ch = workloads._pack([oracle.DEFLATE] * len(blobs), blobs, sizes)
-    return assert_parity(oracle.DEFLATE, ch, dev)
+    st = assert_parity(oracle.DEFLATE, ch, dev)
+    assert (assert_parity(oracle.DEFLATE, ch, dev, waves_per_block=1) == st).all()
+    k = 257 // len(blobs) + 1
+    if sum(sizes) * k < 1 << 28 and len(blobs) * k <= 512:
+        ch = workloads._pack([oracle.DEFLATE] * (len(blobs) * k), blobs * k, sizes * k)
+        assert (assert_parity(oracle.DEFLATE, ch, dev, guards=False) == np.tile(st, k)).all()
+    return st
 
 
 def _literals(bits_wanted):
@@ -52,7 +59,7 @@ def _literals(bits_wanted):
     return w.getvalue(), n
 
 
-@pytest.mark.parametrize("around", [64, 256, 512, 64 * 256, 64 * 256 + 64])
+@pytest.mark.parametrize("around", [64, 256, 512, 64 * 256, 64 * 256 + 64, 512 * 256, 1024 * 256])
 def test_block_ends_at_segment_lane_and_round_edges(dev, around):
     blobs, sizes = zip(*[_literals(b) for b in range(around - 9 + 80 * (around == 64), around + 10 + 80 * (around == 64))])
     assert (_check(dev, list(blobs), list(sizes)) == 0).all()
@@ -99,6 +106,22 @@ def test_copies_of_every_length_and_distance_relation(dev):
         fixed_litlen(w, 256)
         blobs.append(w.getvalue())
         sizes.append(n)
+    assert (_check(dev, blobs, sizes) == 0).all()
+
+
+def test_stored_blocks_and_history(dev):
+    """Stored blocks of many lengths, with copies that read them and the text
+    before them."""
+    rng = np.random.default_rng(8)
+    blobs, sizes = [], []
+    for n in (1, 100, 4095, 4096, 4097, 5000, 20000, 65535):
+        c = zlib.compressobj(6, zlib.DEFLATED, -15, 8)
+        text = workloads.zipf_text(3000, rng, workloads._vocab(0))
+        noise = rng.integers(0, 256, n, dtype=np.uint8).tobytes()
+        data = [text, noise, text + noise[:300] + noise[-700:], noise[: n // 2], text]
+        blobs.append(b"".join(c.compress(d) + c.flush(zlib.Z_FULL_FLUSH if i == 0 else zlib.Z_BLOCK)
+                              for i, d in enumerate(data)) + c.flush())
+        sizes.append(sum(map(len, data)))
     assert (_check(dev, blobs, sizes) == 0).all()
 
 
