@@ -74,7 +74,9 @@ enum {
  *   group_parallel    RLE codecs: 0 = automatic (RLE v1 launches of at
  *                     most 256 chunks and RLE v2 launches of at most 2048
  *                     chunks, without chunk_ticks, are decoded
- *                     group-parallel), 1 = one wave per chunk,
+ *                     group-parallel, and byte RLE launches of at most 2048
+ *                     chunks by a workgroup per chunk), 1 = one wave per
+ *                     chunk,
  *                     2 = group-parallel (not with chunk_ticks).
  *                     Group-parallel: an index pass finds where the groups
  *                     (RLE v1 runs and literal lists; RLE v2 runs) start,

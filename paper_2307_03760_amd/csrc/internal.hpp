@@ -76,6 +76,12 @@ struct OrcMeta {
 void launch_orc_frame_team(const uint8_t *framed, uint32_t block, uint8_t *out, uint64_t out_cap,
                            const OrcFrame *frames, uint32_t max_frames, OrcMeta *meta, hipStream_t s);
 
+// Byte RLE by one workgroup per chunk, on stream s, for launches of up to
+// kByteBlocksMaxChunks chunks.
+int launch_byte_rle_blocks(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff, uint32_t n,
+                           int32_t *status, unsigned long long *err, hipStream_t s);
+constexpr uint32_t kByteBlocksMaxChunks = 2048;
+
 // Byte RLE and RLE element types other than signed 8-byte values, on stream
 // s; one_wave: one wave per chunk whatever the launch's size.
 int launch_typed(int codec, int elem_bytes, bool is_unsigned, const uint8_t *comp, const uint64_t *coff,

@@ -50,6 +50,8 @@ int launch_width(int eb, const uint8_t *comp, const uint64_t *coff, uint8_t *out
 int launch_typed(int codec, int elem_bytes, bool is_unsigned, const uint8_t *comp, const uint64_t *coff,
                  uint8_t *out, const uint64_t *ooff, uint32_t n, int32_t *status,
                  unsigned long long *err, uint64_t *ticks, bool one_wave, hipStream_t s) {
+    if (codec == CODAG_BYTE_RLE && !one_wave && !ticks && n <= kByteBlocksMaxChunks)
+        return launch_byte_rle_blocks(comp, coff, out, ooff, n, status, err, s);
     if (codec == CODAG_BYTE_RLE)
         return launch_t<CODAG_BYTE_RLE, I64>(comp, coff, out, ooff, n, status, err, ticks, s);
     if (codec == CODAG_RLE_V1)
