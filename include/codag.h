@@ -64,11 +64,11 @@ enum {
  *                     4 KiB window).  Back-references reaching
  *                     further read the already written output from HBM.
  *                     With 32 the workgroup holds one wave.
- *                     Deflate launches of at most 512 chunks, and ZLIB
- *                     streams of as many, that set none of waves_per_block,
- *                     lit_table_bits, history_kib and chunk_ticks are
- *                     decoded by a workgroup of 8 or 16 waves per chunk with
- *                     a 32 KiB window.
+ *                     Deflate launches of at most 512 chunks and LZ4
+ *                     launches of at most 1024, and ORC streams of as many,
+ *                     that set none of waves_per_block, lit_table_bits,
+ *                     history_kib and chunk_ticks are decoded by a workgroup
+ *                     of 8 or 16 waves per chunk with a 32 KiB window.
  *   chunk_ticks       optional device array (n_chunks uint64): receives each
  *                     chunk's decode time in shader clock cycles.
  *   group_parallel    RLE codecs: 0 = automatic (RLE v1 launches of at

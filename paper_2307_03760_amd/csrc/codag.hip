@@ -221,6 +221,9 @@ int decompress(int codec, const uint8_t *comp_buf, const uint64_t *chunk_offsets
             return launch_plain<CODAG_RLE_V2, 10, 0>(comp_buf, chunk_offsets, out_buf, out_offsets,
                                                      n_chunks, wpb, chunk_status, ds->err, ticks, s);
         case CODAG_LZ4:
+            if (n_chunks <= kLzTeamMaxChunks && !ticks && !(opts && (opts->waves_per_block || opts->history_kib)))
+                return launch_lz4_team(comp_buf, chunk_offsets, out_buf, out_offsets, (uint32_t)n_chunks,
+                                       chunk_status, ds->err, s);
             return launch_lz4(comp_buf, chunk_offsets, out_buf, out_offsets, n_chunks, wpb, hist,
                               chunk_status, ds->err, ticks, s);
         default:

@@ -72,8 +72,13 @@ struct OrcMeta {
     uint64_t last;           // bytes the last chunk produced
 };
 
-// Decodes every ZLIB chunk of a stream with a workgroup of waves each.
-void launch_orc_frame_team(const uint8_t *framed, uint32_t block, uint8_t *out, uint64_t out_cap,
+// LZ4 the same way, for launches of up to kLzTeamMaxChunks chunks.
+int launch_lz4_team(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff, uint32_t n,
+                    int32_t *status, unsigned long long *err, hipStream_t s);
+constexpr uint32_t kLzTeamMaxChunks = 1024;
+
+// Decodes every compressed chunk of a stream with a workgroup of waves each.
+void launch_orc_frame_team(int codec, const uint8_t *framed, uint32_t block, uint8_t *out, uint64_t out_cap,
                            const OrcFrame *frames, uint32_t max_frames, OrcMeta *meta, hipStream_t s);
 
 // Byte RLE by one workgroup per chunk, on stream s, for launches of up to

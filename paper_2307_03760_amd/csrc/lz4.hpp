@@ -78,12 +78,13 @@ struct LinearIn {
 // A step's output in the making: literals are in the window, matches queued.
 struct Lz4Step {
     uint32_t start, made, nq;
+    uint32_t most;  // bytes it may take
 };
 
-// Room for a new step of up to kAppend bytes.
+// Room for a new step.
 template <uint32_t H>
 __device__ __forceinline__ void lz4_begin(LinearOut<H> &o, Lz4Step &s) {
-    o.make_room(LinearOut<H>::kAppend);
+    o.make_room(s.most);
     s.start = o.o0 + o.pos;
     s.made = s.nq = 0;
 }
@@ -118,7 +119,6 @@ enum : int { kLz4More = 1 };
 template <uint32_t H>
 __device__ __forceinline__ int lz4_sequence(LinearIn &in, LinearOut<H> &o, Lz4Lds<H> *lds, Lz4Step &s, uint32_t &p,
                                             uint32_t end, uint32_t cap) {
-    constexpr uint32_t kAppend = LinearOut<H>::kAppend;
     const uint32_t l = lane();
     const uint32_t tok = in.peek4(p) & 255;
     uint32_t lit = tok >> 4, q = p + 1;
@@ -130,7 +130,7 @@ __device__ __forceinline__ int lz4_sequence(LinearIn &in, LinearOut<H> &o, Lz4Ld
     if (lit > end - q) return CODAG_E_TRUNCATED;
     while (lit) {
         const uint32_t n = min(lit, 512u);  // eight bytes a lane
-        if (s.made + n > kAppend) {
+        if (s.made + n > s.most) {
             lz4_end(o, lds, s);
             lz4_begin(o, s);
         }
@@ -163,7 +163,7 @@ __device__ __forceinline__ int lz4_sequence(LinearIn &in, LinearOut<H> &o, Lz4Ld
     // change what it writes.
     while (mlen) {
         const uint32_t n = mlen > kMaxCopy ? kMaxCopy - 8 : mlen;
-        if (s.made + n > kAppend || s.nq == kCopyQueue) {
+        if (s.made + n > s.most || s.nq == kCopyQueue) {
             lz4_end(o, lds, s);
             lz4_begin(o, s);
         }
@@ -205,6 +205,7 @@ __device__ __forceinline__ int decode_lz4(LinearIn &in, uint8_t *out, uint32_t c
     uint32_t p = in.skip;
     int st = CODAG_OK;
     Lz4Step s;
+    s.most = kAppend;
     lz4_begin(o, s);
     for (;;) {
         if (p >= end) { st = CODAG_E_TRUNCATED; break; }

@@ -1,4 +1,4 @@
-// Deflate by one workgroup per chunk, for launches with few chunks.
+// Deflate and LZ4 by one workgroup per chunk, for launches with few chunks.
 //
 // One wave per chunk leaves most of the GPU idle when there are a few dozen
 // chunks, and each wave's time is a chain of dependent steps.  Here kTeam
@@ -10,13 +10,15 @@
 // a round costs about what a wave's round costs and takes kTeam times the
 // input.
 //
-// Measured against one wave per chunk: 48 chunks of 60 KB 624 to 187 us, 49
-// ORC blocks of 256 KiB 2.58 to 0.66 ms, 256 chunks of 64 KiB 689 to 195 us
+// Measured against one wave per chunk: 48 chunks of 60 KB 624 to 175 us, 49
+// ORC blocks of 256 KiB 2.58 to 0.63 ms, 256 chunks of 64 KiB 689 to 195 us
 // with teams of 16; 512 chunks of 64 KiB 727 to 302 us with teams of 8.  1,024
 // chunks fill the GPU a wave each (780 us against 899 in teams of 8), hence
-// the limits.  Of a 64 KiB text chunk's 405,000 cycles the passes take some
-// 130,000, the copies 80,000, the block header and its tables 55,000.
+// the limits.  Of a 64 KiB text chunk's 400,000 cycles the passes take some
+// 130,000, the copies 70,000, the block header and its tables 55,000.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "../../include/codag.h"
 #include "decode.hpp"
@@ -26,48 +28,10 @@ namespace codag {
 
 constexpr uint32_t kTeamH = 32768;  // output window
 
-// Decoding by kTeam waves (8 or 16).
-template <uint32_t kTeam>
-struct Team {
-static constexpr uint32_t kTeamThreads = kTeam * kWave;
-static constexpr uint32_t kTeamQueue = kTeam * 160;
-static constexpr uint32_t kTeamPieces = kTeamThreads * kLaneBits / 128 + 2;
-// Lanes off the track at the end of a pass pass it on; a longer line of them
-// is a little likelier with more lanes.
-static constexpr uint32_t kTeamPasses = kMaxPasses + 4;
-// A step always takes a segment: at most 32 copies, 258 bytes each.
-static_assert(LinearOut<kTeamH>::kAppend >= 32 * 258 && kTeamQueue >= 32, "a step fits a segment");
-
-struct Lds {
-    DeflateLds<9, kTeamH> d;  // tables, window, and wave 0's own lists
-    uint32_t in[4 * kTeamPieces];
-    uint32_t segs[kTeam * kRoundSegs];
-    uint64_t queue[kTeamQueue + 1];
-    // Wave 0's orders: rounds from bit p on, or no more; and its output state.
-    uint32_t go, p, pos, wlo, fa, room;
-    // What the waves tell each other: where the last lane of each ended
-    // (~0: it stopped), its first lane of interest, its sums.
-    uint32_t edge[kTeam], first[kTeam], stop[kTeam], sum_out[kTeam], sum_cop[kTeam];
-    uint32_t last_why, last_z, last_e, made, nq;
-    uint32_t bad_lane[kTeam], bad_st[kTeam], bad_r[kTeam], bad_dst[kTeam], bad_qi[kTeam];
-    unsigned long long made_bits[kTeamQueue / kWave];  // copies made, a bit each
-};
-
-// The smallest wave * 64 + v[wave] over the waves (v < 64, or 64 for none):
-// kTeamThreads when there is none.
-static __device__ __forceinline__ uint32_t first_lane(const uint32_t *v) {
-    uint32_t r = kTeamThreads;
-#pragma unroll
-    for (uint32_t w = 0; w < kTeam; w++) {
-        const uint32_t x = uni(v[w]);
-        if (x < kWave && w * kWave + x < r) r = w * kWave + x;
-    }
-    return r;
-}
-
 // Room for len <= kAppend more bytes, by the whole team (the same decision on
 // every wave).
-static __device__ __forceinline__ void room(LinearOut<kTeamH> &o, uint32_t len, uint32_t tid) {
+template <uint32_t kTeamThreads>
+__device__ __forceinline__ void team_room(LinearOut<kTeamH> &o, uint32_t len, uint32_t tid) {
     if (o.room >= len) return;
     constexpr uint32_t kBlock = LinearOut<kTeamH>::kBlock;
     const uint32_t at = o.o0 + o.pos;
@@ -95,7 +59,8 @@ static __device__ __forceinline__ void room(LinearOut<kTeamH> &o, uint32_t len, 
 
 // Copies whose output starts below offset x of the step (they are in output
 // order).
-static __device__ __forceinline__ uint32_t copies_below(const uint64_t *queue, uint32_t nq, uint32_t x) {
+template <uint32_t kTeamQueue>
+__device__ __forceinline__ uint32_t team_copies_below(const uint64_t *queue, uint32_t nq, uint32_t x) {
     uint32_t lo = 0;
 #pragma unroll
     for (uint32_t step = kTeamQueue >= 2048 ? 2048 : 1024; step; step >>= 1) {
@@ -111,38 +76,90 @@ static __device__ __forceinline__ uint32_t copies_below(const uint64_t *queue, u
 // source are -- found by bisection, and looked up in a bitmap of the copies
 // made -- so a step takes as many rounds as copies of copies are deep.  (With
 // every copy waiting for all the copies below its source's end, 1,100 copies
-// of text took 64,000 cycles.)
-static __device__ __forceinline__ void copies(const LinearOut<kTeamH> &o, Lds *s, uint32_t nq, uint32_t start,
-                                            uint32_t wave) {
+// of text took 64,000 cycles, this way 28,000.)
+//
+// With `hops` (one word per copy), depth is cut first: a copy whose source is
+// part of one earlier copy's output takes its bytes from that copy's source
+// instead, and from that one's in turn, each hop going as far as the copy
+// hopped to has come, so a chain of n copies takes about log2 n hops.  Words
+// of running text repeat their last occurrence, which repeats its last: 690
+// LZ4 matches took 93,000 cycles without hops and 18,000 with them.
+struct CopyHop {
+    // lo: source relative to the step's start + 2^19 | the copy its bytes come
+    // from << 20 (kNone: none); hi: first and one past the last copy that
+    // overlaps the source.
+    static constexpr uint32_t kNone = 0xfff, kBias = 1u << 19;
+};
+template <uint32_t kTeamThreads, uint32_t kTeamQueue>
+__device__ __forceinline__ void team_copies(const LinearOut<kTeamH> &o, const uint64_t *queue, uint64_t *hops,
+                                            unsigned long long *made_bits, uint32_t nq, uint32_t start, uint32_t wave) {
+    static_assert(kTeamQueue < CopyHop::kNone, "copies count in 12 bits");
     const uint32_t l = lane();
-    if (threadIdx.x < kTeamQueue / kWave) s->made_bits[threadIdx.x] = 0;
+    if (threadIdx.x < kTeamQueue / kWave) made_bits[threadIdx.x] = 0;
+    // Copies d0 .. d1 - 1 overlap the source [src, min(src + len, dst)) of copy
+    // k; `from` is that copy's hop.
+    auto overlaps = [&](uint64_t q, bool v, uint32_t &d0, uint32_t &d1, uint32_t &hop) {
+        const uint32_t len = (uint32_t)q & 0xffff, dist = (uint32_t)(q >> 32), at = ((uint32_t)q >> 16) & 0xffff;
+        const bool inside = v && at + len > dist;  // the source's end, from the step's start, is past it
+        d0 = d1 = 0;
+        hop = CopyHop::kNone;
+        if (!ballot(inside)) return;
+        const uint32_t from = at > dist ? at - dist : 0u, to = min(at, at - dist + len);
+        d1 = inside ? team_copies_below<kTeamQueue>(queue, nq, to) : 0u;
+        // Few copies fit between the source's ends: walk down to the first
+        // that reaches past `from`.
+        d0 = d1;
+        bool more = d0 != 0;
+        while (ballot(more)) {
+            const uint32_t p = (uint32_t)queue[d0 - (more ? 1 : 0)];
+            more = more && (p >> 16) + (p & 0xffff) > from;
+            d0 -= more ? 1u : 0u;
+            more = more && d0 != 0;
+        }
+        if (d1 - d0 == 1 && dist >= len && at >= dist) {
+            const uint64_t p = queue[d0];
+            const uint32_t pl = (uint32_t)p & 0xffff, pa = ((uint32_t)p >> 16) & 0xffff;
+            if (pa <= from && from + len <= pa + pl && (uint32_t)(p >> 32) >= pl) hop = d0;
+        }
+    };
+    if (hops) {
+        for (uint32_t k0 = wave * kWave; k0 < nq; k0 += kTeamThreads) {
+            const uint32_t k = k0 + l;
+            const uint64_t q = queue[min(k, kTeamQueue - 1)];
+            uint32_t d0, d1, hop;
+            overlaps(q, k < nq, d0, d1, hop);
+            const uint32_t rel = (((uint32_t)q >> 16) & 0xffff) - (uint32_t)(q >> 32);
+            if (k < nq) hops[k] = ((uint64_t)(d0 | (d1 << 16)) << 32) | (rel + CopyHop::kBias) | (hop << 20);
+        }
+    }
     __syncthreads();
     for (uint32_t k0 = wave * kWave; k0 < nq; k0 += kTeamThreads) {
         const uint32_t k = k0 + l;
         const bool v = k < nq;
-        const uint64_t q = s->queue[min(k, kTeamQueue - 1)];
+        const uint64_t q = queue[min(k, kTeamQueue - 1)];
         const uint32_t len = v ? (uint32_t)q & 0xffff : 0u, dist = (uint32_t)(q >> 32);
-        const uint32_t at = (uint32_t)q >> 16, dst = start + at, src = dst - dist;
-        const bool far = v && src < o.wlo;
+        const uint32_t at = ((uint32_t)q >> 16) & 0xffff, dst = start + at;
         const bool repeats = v && dist < len;  // its own output
-        // Copies d0 .. d1 - 1 overlap the source [src, min(src + len, dst)).
-        uint32_t d0 = 0, d1 = 0;
-        const bool inside = v && src + len > start;
-        if (ballot(inside)) {
-            const uint32_t from = inside && src > start ? src - start : 0u;
-            const uint32_t to = inside ? min(at, at - dist + len) : 0u;
-            d1 = inside ? copies_below(s->queue, nq, to) : 0u;
-            // Few copies fit between the source's ends: walk down to the first
-            // that reaches past `from`.
-            d0 = d1;
-            bool more = d0 != 0;
-            while (ballot(more)) {
-                const uint32_t p = (uint32_t)s->queue[d0 - (more ? 1 : 0)];
-                more = more && (p >> 16) + (p & 0xffff) > from;
-                d0 -= more ? 1u : 0u;
-                more = more && d0 != 0;
+        uint32_t src = dst - dist, d0, d1, hop;
+        if (hops) {
+            const uint64_t h = v ? hops[k] : (uint64_t)(CopyHop::kNone << 20);
+            hop = ((uint32_t)h >> 20) & 0xfff;
+            uint32_t over = (uint32_t)(h >> 32);
+            while (ballot(hop != CopyHop::kNone)) {
+                if (hop != CopyHop::kNone) {
+                    const uint64_t hp = hops[hop], qp = queue[hop];
+                    src += ((uint32_t)hp & 0xfffff) - CopyHop::kBias - (((uint32_t)qp >> 16) & 0xffff);
+                    hop = ((uint32_t)hp >> 20) & 0xfff;
+                    over = (uint32_t)(hp >> 32);
+                    hops[k] = ((uint64_t)over << 32) | (src - start + CopyHop::kBias) | (hop << 20);
+                }
             }
+            d0 = v ? over & 0xffff : 0u;
+            d1 = v ? over >> 16 : 0u;
+        } else {
+            overlaps(q, v, d0, d1, hop);
         }
+        const bool far = v && src < o.wlo;
         if (ballot(far)) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         uint64_t pend = ballot(v);
         const uint64_t all = pend;
@@ -153,7 +170,7 @@ static __device__ __forceinline__ void copies(const LinearOut<kTeamH> &o, Lds *s
                     uint64_t need = ~0ull;
                     if (64 * w < d0) need &= ~0ull << (d0 & 63);
                     if (64 * w + 64 > d1) need &= ~(~0ull << (d1 & 63));
-                    const uint64_t done = __hip_atomic_load(&s->made_bits[w], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    const uint64_t done = __hip_atomic_load(&made_bits[w], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
                     ready = (need & ~done) == 0;
                 }
             }
@@ -170,10 +187,50 @@ static __device__ __forceinline__ void copies(const LinearOut<kTeamH> &o, Lds *s
             pend &= ~rm;
             wave_sync();
             if (l == 0)
-                __hip_atomic_store(&s->made_bits[k0 / kWave], all & ~pend, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_store(&made_bits[k0 / kWave], all & ~pend, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     }
     __syncthreads();
+}
+
+// Decoding by kTeam waves (8 or 16).
+template <uint32_t kTeam>
+struct Team {
+static constexpr uint32_t kTeamThreads = kTeam * kWave;
+static constexpr uint32_t kTeamQueue = kTeam * 160;
+static constexpr bool kHops = kTeam == 16;  // a team of 8 shares its CU's LDS with another
+static constexpr uint32_t kTeamPieces = kTeamThreads * kLaneBits / 128 + 2;
+// Lanes off the track at the end of a pass pass it on; a longer line of them
+// is a little likelier with more lanes.
+static constexpr uint32_t kTeamPasses = kMaxPasses + 4;
+// A step always takes a segment: at most 32 copies, 258 bytes each.
+static_assert(LinearOut<kTeamH>::kAppend >= 32 * 258 && kTeamQueue >= 32, "a step fits a segment");
+
+struct Lds {
+    DeflateLds<9, kTeamH> d;  // tables, window, and wave 0's own lists
+    uint32_t in[4 * kTeamPieces];
+    uint32_t segs[kTeam * kRoundSegs];
+    uint64_t queue[kTeamQueue + 1], hops[kHops ? kTeamQueue : 1];
+    // Wave 0's orders: rounds from bit p on, or no more; and its output state.
+    uint32_t go, p, pos, wlo, fa, room;
+    // What the waves tell each other: where the last lane of each ended
+    // (~0: it stopped), its first lane of interest, its sums.
+    uint32_t edge[kTeam], first[kTeam], stop[kTeam], sum_out[kTeam], sum_cop[kTeam];
+    uint32_t last_why, last_z, last_e, made, nq;
+    uint32_t bad_lane[kTeam], bad_st[kTeam], bad_r[kTeam], bad_dst[kTeam], bad_qi[kTeam];
+    unsigned long long made_bits[kTeamQueue / kWave];  // copies made, a bit each
+};
+
+// The smallest wave * 64 + v[wave] over the waves (v < 64, or 64 for none):
+// kTeamThreads when there is none.
+static __device__ __forceinline__ uint32_t first_lane(const uint32_t *v) {
+    uint32_t r = kTeamThreads;
+#pragma unroll
+    for (uint32_t w = 0; w < kTeam; w++) {
+        const uint32_t x = uni(v[w]);
+        if (x < kWave && w * kWave + x < r) r = w * kWave + x;
+    }
+    return r;
 }
 
 // Rounds from bit p on until the block ends, an error, or something for wave
@@ -266,7 +323,7 @@ static __device__ __forceinline__ int rounds(const uint8_t *gbase, uint32_t gend
             }
             __syncthreads();
             uint32_t made = uni(s->made), nq = uni(s->nq);
-            room(o, made, tid);
+            team_room<kTeamThreads>(o, made, tid);
             const uint32_t start = o.o0 + o.pos, lim = o.o0 + o.cap;
             const bool tight = start + made > lim;  // the output range ends in this step
             uint32_t dst = start + io - so, qi = ic - sc;
@@ -298,7 +355,7 @@ static __device__ __forceinline__ int rounds(const uint8_t *gbase, uint32_t gend
                 nq = uni(s->bad_qi[fb / kWave]);
                 made = uni(s->bad_dst[fb / kWave]) - start;
             }
-            copies(o, s, nq, start, wave);
+            team_copies<kTeamThreads, kTeamQueue>(o, s->queue, kHops ? s->hops : nullptr, s->made_bits, nq, start, wave);
             o.pos += made;
             o.room -= made;
             if (fb < kTeamThreads) {
@@ -404,13 +461,293 @@ int launch_deflate_team(const uint8_t *comp, const uint64_t *coff, uint8_t *out,
     return hipGetLastError() == hipSuccess ? CODAG_OK : CODAG_E_HIP;
 }
 
+// ---- LZ4 -------------------------------------------------------------------
+//
+// A block is a chain of sequences of three bytes and more, and one wave spends
+// its time on the chain and on matches of matches.  A team takes the input in
+// windows of 3,072 byte positions: every thread parses the sequences that
+// would start at three of them (continuation bytes included, for literal runs
+// below 270 bytes and matches of up to 1,024), six rounds of link doubling in
+// LDS give where 64 sequences end, one read per 64 follows the real chain, and
+// each thread finds and parses one of its sequences.  A prefix sum places
+// them; literals go to the window and matches to the copy queue.  What the
+// parse leaves out (longer fields, the last sequence, every error) is one
+// general step of wave 0.
+//
+// Measured against one wave per block: 97 ORC blocks of 64 KiB 1,028 to 246 us,
+// one block of 64 KiB 840 to 174, 256 chunks 968 to 220, 1,024 chunks 1,025 to
+// 807; two teams fit neither a CU's LDS nor its waves, so from some 1,300
+// chunks on a wave each is faster.  Of a text window's 40,000 cycles the
+// copies take 18,000, the links 6,600, finding the sequences 7,700.
+constexpr uint32_t kLzTeam = 16, kLzThreads = kLzTeam * kWave;
+constexpr uint32_t kLzStep = 3 * kLzThreads;  // byte positions of a window: one sequence a thread at most
+constexpr uint32_t kLzPieces = kLzStep / 16 + 20;  // a sequence's fields and literals past the last position
+constexpr uint32_t kLzLevels = 7;             // links over 1, 2, ... 64 sequences
+constexpr uint32_t kLzMatch = 1024;           // longest match of a parsed sequence
+// Copies of up to kLzMatch bytes: as much more of what lies below the window
+// has to be in HBM (see LinearOut).
+constexpr uint32_t kLzMost = LinearOut<kTeamH>::kAppend - (kLzMatch - 512);
+
+struct LzTeamLds {
+    Lz4Lds<kTeamH> d;  // the window; wave 0's queue
+    uint32_t buf[2][4 * kLzPieces];
+    uint16_t link[kLzLevels][kLzStep];
+    uint64_t queue[kLzThreads], hops[kLzThreads];
+    unsigned long long made_bits[kLzThreads / kWave];
+    uint32_t unit[kLzTeam + 2], units, chain_end;
+    uint32_t sum[kLzTeam], first[kLzTeam], made, next;
+    uint32_t st, p, pos, wlo, fa, room;  // wave 0's general step
+};
+
+struct LzSeq {
+    uint32_t lit, at, off, mlen, next;  // at: its literals' first position
+    bool ok;
+};
+// The sequence at position x of a window, `room` positions before the chunk's
+// end: ok if a thread can take it.
+__device__ __forceinline__ LzSeq lz_parse(const uint8_t *bytes, uint32_t x, uint32_t room) {
+    LzSeq q;
+    const uint32_t tok = bytes[x];
+    q.lit = tok >> 4;
+    q.at = x + 1;
+    q.ok = true;
+    if (q.lit == 15) {
+        const uint32_t e = bytes[x + 1];
+        q.lit += e;
+        q.at++;
+        q.ok = e != 255;
+    }
+    const uint64_t f = *reinterpret_cast<const u64_any *>(bytes + q.at + q.lit);
+    q.off = (uint32_t)f & 0xffff;
+    q.mlen = (tok & 15) + 4;
+    q.next = q.at + q.lit + 2;
+    if ((tok & 15) == 15) {
+        const uint32_t full = (uint32_t)(__builtin_ctzll(~(f >> 16)) >> 3);  // continuation bytes of 255; 6 or more: too long
+        q.ok = q.ok && full < 6;
+        q.mlen += 255 * full + ((uint32_t)(f >> (16 + 8 * min(full, 5u))) & 255);
+        q.next += full + 1;
+    }
+    q.ok = q.ok && q.off != 0 && q.mlen <= kLzMatch && q.next <= room;
+    return q;
+}
+
+// One block by the workgroup; the same status on every wave.
+__device__ __forceinline__ int lz_team_chunk(const uint8_t *chunk, uint32_t len, uint8_t *out, uint32_t cap,
+                                             uint32_t *made_out, LzTeamLds *s, uint32_t *lin, uint32_t wave) {
+    const uint32_t l = lane(), tid = wave * kWave + l;
+    LinearOut<kTeamH> o;
+    o.init(out, cap, s->d.window);
+    LinearIn in;  // wave 0's
+    in.skip = (uint32_t)(reinterpret_cast<uintptr_t>(chunk) & 15);
+    in.gbase = chunk - in.skip;
+    in.gend = in.skip + len;
+    in.buf = lin;
+    in.a0 = 0;
+    if (wave == 0) in.load(0);
+    const uint32_t end = in.gend;
+    uint32_t p = in.skip;
+    uint32_t cur = ~0u, nxt = ~0u;  // the window in use, and one in (or on its way to) the other buffer
+    int st = CODAG_OK;
+    auto issue = [&](uint32_t w) {
+        const uint32_t at = w * kLzStep + 16 * tid;
+        if (tid < kLzPieces && at < end)
+            __builtin_amdgcn_global_load_lds(in.gbase + at, (lds_void *)(s->buf[w & 1] + 256 * wave), 16, 0, 0);
+    };
+    for (;;) {
+        if (p >= end) {
+            st = CODAG_E_TRUNCATED;
+            break;
+        }
+        const uint32_t w = p / kLzStep, W = w * kLzStep, room = end - W;
+        if (w != cur && w != nxt) {
+            wait_vm();  // a window not wanted any more may be landing
+            issue(w);
+        }
+        cur = w;
+        if (wave < (kLzPieces + kWave - 1) / kWave) wait_vm();
+        __syncthreads();
+        if (W + kLzStep < end && nxt != w + 1) {
+            issue(w + 1);
+            nxt = w + 1;
+        }
+        const uint8_t *const bytes = reinterpret_cast<const uint8_t *>(s->buf[w & 1]);
+        // Links; a position whose sequence no thread can take links to itself.
+        uint32_t to[3];
+#pragma unroll
+        for (uint32_t i = 0; i < 3; i++) {
+            const uint32_t x = tid + kLzThreads * i;
+            const LzSeq q = lz_parse(bytes, x, room);
+            to[i] = q.ok && x < room ? q.next : x;
+            s->link[0][x] = (uint16_t)to[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t k = 1; k < kLzLevels; k++) {
+#pragma unroll
+            for (uint32_t i = 0; i < 3; i++) {
+                const uint32_t f = s->link[k - 1][min(to[i], kLzStep - 1)];
+                if (to[i] < kLzStep) to[i] = f;
+                s->link[k][tid + kLzThreads * i] = (uint16_t)to[i];
+            }
+            __syncthreads();
+        }
+        // The chain, 64 sequences a step.
+        if (wave == 0) {
+            uint32_t x = p - W, u = 0;
+            while (x < kLzStep && u < kLzTeam + 2) {
+                if (l == 0) s->unit[u] = x;
+                const uint32_t f = uni((uint32_t)s->link[kLzLevels - 1][x]);
+                if (f == x) break;
+                u++;
+                x = f;
+            }
+            if (l == 0) {
+                s->units = u;
+                s->chain_end = x;
+            }
+        }
+        __syncthreads();
+        // One sequence a thread: wave u's are those of unit u.
+        const uint32_t units = uni(s->units), chain_end = uni(s->chain_end);
+        uint32_t x = wave < units ? s->unit[wave] : kLzStep;
+#pragma unroll
+        for (uint32_t k = kLzLevels - 1; k-- > 0;) {
+            const uint32_t f = s->link[k][min(x, kLzStep - 1)];
+            if (((l >> k) & 1) && x < kLzStep) x = f;
+        }
+        const LzSeq q = lz_parse(bytes, min(x, kLzStep - 1), room);
+        const bool valid = x < kLzStep && x < room && q.ok;
+        const uint32_t outl = valid ? q.lit + q.mlen : 0u;
+        uint32_t incl = wave_inclusive_sum32(outl);
+        if (l == kWave - 1) s->sum[wave] = incl;
+        __syncthreads();
+        for (uint32_t v = 0; v < wave; v++) incl += uni(s->sum[v]);
+        const uint32_t before = incl - outl, done = o.pos;
+        // Sequences up to the first that is not one, or breaks a bound.
+        const uint64_t no = ballot(!valid || incl > cap - done || q.off > done + before + q.lit);
+        if (l == 0) s->first[wave] = no ? (uint32_t)__builtin_ctzll(no) : kWave;
+        if (tid == 0) s->next = W + chain_end;
+        __syncthreads();
+        uint32_t cnt = kLzThreads;
+        for (uint32_t v = kLzTeam; v-- > 0;) {
+            const uint32_t fv = uni(s->first[v]);
+            if (fv < kWave) cnt = v * kWave + fv;
+        }
+        // A sequence left to the general step (a bound): the chain stops there.
+        if (tid == cnt && valid) s->next = W + x;
+        // Steps of at most kLzMost output bytes.
+        for (uint32_t g = 0, base = 0; g < cnt;) {
+            const uint64_t over = ballot(tid >= cnt || (tid >= g && incl - base > kLzMost));
+            __syncthreads();
+            if (l == 0) s->first[wave] = over ? (uint32_t)__builtin_ctzll(over) : kWave;
+            __syncthreads();
+            uint32_t g1 = cnt;
+            for (uint32_t v = kLzTeam; v-- > 0;) {
+                const uint32_t fv = uni(s->first[v]);
+                if (fv < kWave) g1 = min(g1, v * kWave + fv);
+            }
+            if (tid == g1 - 1) s->made = incl;
+            __syncthreads();
+            const uint32_t upto = uni(s->made), made = upto - base;
+            team_room<kLzThreads>(o, made, tid);
+            const uint32_t start = o.o0 + o.pos;
+            if (tid >= g && tid < g1) {
+                const uint32_t dl = before - base;
+                uint8_t *const dst = o.win + (start + dl - o.wlo);
+                const uint8_t *const src = bytes + q.at;
+                if (q.lit >= 8) {
+                    for (uint32_t j = 0; j < q.lit; j += 8) {
+                        const uint32_t k = min(j, q.lit - 8);
+                        *reinterpret_cast<u64_any *>(dst + k) = *reinterpret_cast<const u64_any *>(src + k);
+                    }
+                } else {
+                    for (uint32_t j = 0; j < q.lit; j++) dst[j] = src[j];
+                }
+                s->queue[tid - g] = copy_entry(q.mlen, dl + q.lit, q.off);
+            }
+            __syncthreads();
+            team_copies<kLzThreads, kLzThreads>(o, s->queue, s->hops, s->made_bits, g1 - g, start, wave);
+            o.pos += made;
+            o.room -= made;
+            base = upto;
+            g = g1;
+        }
+        __syncthreads();
+        p = uni(s->next);
+        if (p >= W + kLzStep) continue;
+        // The general step at p.
+        if (wave == 0) {
+            int r = CODAG_E_TRUNCATED;  // p >= end
+            if (p < end) {
+                Lz4Step step;
+                step.most = 2560;
+                lz4_begin(o, step);
+                r = lz4_sequence<kTeamH>(in, o, &s->d, step, p, end, cap);
+                lz4_end(o, &s->d, step);
+            }
+            wait_vm();  // what it wrote out is there for the others
+            if (l == 0) {
+                s->st = (uint32_t)r;
+                s->p = p;
+                s->pos = o.pos;
+                s->wlo = o.wlo;
+                s->fa = o.fa;
+                s->room = o.room;
+            }
+        }
+        __syncthreads();
+        st = (int)uni(s->st);
+        p = uni(s->p);
+        o.pos = uni(s->pos);
+        o.wlo = uni(s->wlo);
+        o.fa = uni(s->fa);
+        o.room = uni(s->room);
+        __syncthreads();
+        if (st != kLz4More) break;
+        st = CODAG_OK;
+    }
+    wait_vm();  // a window on its way
+    __syncthreads();
+    if (wave == 0) o.finish();
+    __syncthreads();
+    if (st) return st;
+    if (made_out) {
+        *made_out = o.pos;
+        return CODAG_OK;
+    }
+    return o.pos == cap ? CODAG_OK : CODAG_E_UNDERFLOW;
+}
+
+__global__ void __launch_bounds__(kLzThreads) __attribute__((amdgpu_waves_per_eu(4)))
+    lz4_team(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff, uint32_t n,
+             int32_t *status, unsigned long long *err) {
+    __shared__ __align__(16) LzTeamLds s;
+    __shared__ __align__(16) uint32_t s_lin[LinearIn::kLdsWords];
+    const uint32_t wave = uni(threadIdx.x / kWave), c = blockIdx.x;
+    if (c >= n) return;
+    const uint64_t i0 = coff[c], i1 = coff[c + 1], o0 = ooff[c], o1 = ooff[c + 1];
+    int st = CODAG_E_INVALID_ARGUMENT;
+    if ((((i1 - i0) | (o1 - o0)) >> 31) == 0)
+        st = lz_team_chunk(comp + i0, (uint32_t)(i1 - i0), out + o0, (uint32_t)(o1 - o0), nullptr, &s, s_lin, wave);
+    if (wave == 0) report(c, st, status, err);
+}
+
+int launch_lz4_team(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff, uint32_t n,
+                    int32_t *status, unsigned long long *err, hipStream_t s) {
+    hipLaunchKernelGGL(lz4_team, dim3(n), dim3(kLzThreads), 0, s, comp, coff, out, ooff, n, status, err);
+    return hipGetLastError() == hipSuccess ? CODAG_OK : CODAG_E_HIP;
+}
+
+// ---- compressed ORC streams
+
 // ORC chunk f into out + f * block, as orc_frame_decode with a team per chunk.
-template <uint32_t kTeam>
+template <int Codec, uint32_t kTeam>
 __global__ void __launch_bounds__(kTeam * kWave) __attribute__((amdgpu_waves_per_eu(4)))
     orc_frame_team(const uint8_t *framed, uint32_t block, uint8_t *out, uint64_t out_cap, const OrcFrame *frames,
                    OrcMeta *meta) {
-    __shared__ __align__(16) typename Team<kTeam>::Lds s;
+    __shared__ __align__(16) typename std::conditional<Codec == CODAG_LZ4, LzTeamLds, typename Team<kTeam>::Lds>::type s;
     __shared__ __align__(16) uint32_t s_ring[DirectRing<512>::kLdsWords];
+    static_assert(DirectRing<512>::kLdsWords >= LinearIn::kLdsWords, "wave 0's input");
     const uint32_t wave = uni(threadIdx.x / kWave);
     const uint32_t count = uni(meta->count), complete = uni(meta->complete);
     for (uint32_t f = blockIdx.x; f < count; f += gridDim.x) {
@@ -431,7 +768,10 @@ __global__ void __launch_bounds__(kTeam * kWave) __attribute__((amdgpu_waves_per
         } else if (len >= (1u << 28)) {
             st = CODAG_E_INVALID_ARGUMENT;
         } else {
-            st = Team<kTeam>::chunk(framed + src, len, out + at, room, &made, &s, s_ring, wave);
+            if constexpr (Codec == CODAG_LZ4)
+                st = lz_team_chunk(framed + src, len, out + at, room, &made, &s, s_ring, wave);
+            else
+                st = Team<kTeam>::chunk(framed + src, len, out + at, room, &made, &s, s_ring, wave);
         }
         if (st == CODAG_OK && !last && made != block) st = made < block ? CODAG_E_UNDERFLOW : CODAG_E_OVERFLOW;
         if (threadIdx.x == 0) {
@@ -441,14 +781,17 @@ __global__ void __launch_bounds__(kTeam * kWave) __attribute__((amdgpu_waves_per
     }
 }
 
-void launch_orc_frame_team(const uint8_t *framed, uint32_t block, uint8_t *out, uint64_t out_cap,
+void launch_orc_frame_team(int codec, const uint8_t *framed, uint32_t block, uint8_t *out, uint64_t out_cap,
                            const OrcFrame *frames, uint32_t max_frames, OrcMeta *meta, hipStream_t s) {
-    if (max_frames <= kBigTeamMaxChunks)
-        hipLaunchKernelGGL(orc_frame_team<16>, dim3(max_frames), dim3(16 * kWave), 0, s, framed, block, out, out_cap,
-                           frames, meta);
+    if (codec == CODAG_LZ4)
+        hipLaunchKernelGGL((orc_frame_team<CODAG_LZ4, kLzTeam>), dim3(max_frames), dim3(kLzThreads), 0, s, framed, block,
+                           out, out_cap, frames, meta);
+    else if (max_frames <= kBigTeamMaxChunks)
+        hipLaunchKernelGGL((orc_frame_team<CODAG_DEFLATE, 16>), dim3(max_frames), dim3(16 * kWave), 0, s, framed, block,
+                           out, out_cap, frames, meta);
     else
-        hipLaunchKernelGGL(orc_frame_team<8>, dim3(max_frames), dim3(8 * kWave), 0, s, framed, block, out, out_cap,
-                           frames, meta);
+        hipLaunchKernelGGL((orc_frame_team<CODAG_DEFLATE, 8>), dim3(max_frames), dim3(8 * kWave), 0, s, framed, block,
+                           out, out_cap, frames, meta);
 }
 
 }  // namespace codag

@@ -175,8 +175,8 @@ extern "C" int codag_orc_decompress_stream(int codec, const uint8_t *framed, uin
     OrcFrame *frames = reinterpret_cast<OrcFrame *>(static_cast<char *>(ws) + sizeof(OrcMeta));
     hipLaunchKernelGGL(orc_frames, dim3(1), dim3(kWave), 0, s, framed, framed_len, frames, max_frames, meta);
     const uint32_t grid = max_frames < 2048 ? max_frames : 2048;
-    if (codec == CODAG_DEFLATE && max_frames <= kTeamMaxChunks)
-        launch_orc_frame_team(framed, block_size, out, out_cap, frames, max_frames, meta, s);
+    if (max_frames <= (codec == CODAG_DEFLATE ? kTeamMaxChunks : kLzTeamMaxChunks))
+        launch_orc_frame_team(codec, framed, block_size, out, out_cap, frames, max_frames, meta, s);
     else if (codec == CODAG_DEFLATE)
         hipLaunchKernelGGL(orc_frame_decode<CODAG_DEFLATE>, dim3(grid), dim3(kWave), 0, s, framed,
                            block_size, out, out_cap, frames, meta);

@@ -135,10 +135,12 @@ struct LinearOut {
         if (dist >= len) {
             for (uint32_t i = lane(); i < len; i += kWave) to[i] = from[i];
         } else {
-            // Byte i is byte i mod dist of the period.  i (dist + 1) < 2^20,
-            // so with m at or up to 2 above 2^20 / dist the quotient is exact.
-            const uint32_t m = (uint32_t)(1048576.0f * __builtin_amdgcn_rcpf((float)dist)) + 2;
-            for (uint32_t i = lane(); i < len; i += kWave) to[i] = from[i - dist * ((i * m) >> 20)];
+            // Byte i is byte i mod dist of the period.  m is above 2^21 / dist
+            // by at most 1 (the reciprocal's error is below a quarter of the
+            // distance to the next multiple of 1 / dist), so with i and dist
+            // below 1,024 the quotient i m >> 21 is exact.
+            const uint32_t m = (uint32_t)(2097152.0f * __builtin_amdgcn_rcpf((float)dist)) + 1;
+            for (uint32_t i = lane(); i < len; i += kWave) to[i] = from[i - dist * ((i * m) >> 21)];
         }
         wave_sync();
     }
@@ -222,8 +224,8 @@ __device__ __forceinline__ void make_copies(const LinearOut<H> &o, bool ready, b
     for (uint64_t lm = ballot(ready && len > kLongCopy); lm; lm &= lm - 1) {
         const uint32_t k = (uint32_t)__builtin_ctzll(lm);
         const uint32_t cs = readlane(src, k), cd = readlane(dst, k), cl = readlane(len, k);
-        const uint32_t j = min(8 * l, cl - 8);
-        if (8 * l < cl) {
+        for (uint32_t i = 8 * l; i < cl; i += 8 * kWave) {
+            const uint32_t j = min(i, cl - 8);
             uint64_t a;
             if (cs < o.wlo) a = *reinterpret_cast<const u64_any *>(o.base + cs + j);
             else a = *reinterpret_cast<const u64_any *>(o.win + (cs - o.wlo) + j);

@@ -1,5 +1,5 @@
-"""GPU parity of the LZ4 decoder's steps: sequences at the edges of what a
-window parses itself, steps that end by bytes and by match count, matches
+"""GPU parity of the LZ4 decoders' steps: sequences at the edges of what a
+window parses itself, chains over window edges, steps that end by bytes and by match count, matches
 reading their own step, offsets past the LDS window."""
 import numpy as np
 import pytest
@@ -52,13 +52,15 @@ def _block(rng, lit_choices, match_choices, off_choices, total):
     ([0, 14, 15, 16, 269, 270, 600], [4, 18, 19, 20, 272, 273, 274, 275], [1, 8, 273, 4096, 30000]),
     ([1], [273], [1, 7, 272, 273, 274]),                            # steps that end by bytes
     ([0, 1, 5], [511, 512, 513, 514, 515, 516, 1017, 1018, 1025, 1026], [1, 4, 7, 600]),  # matches made in pieces
+    ([0, 14, 15, 268, 269, 270], [19, 273, 274, 528, 529, 1023, 1024, 1025, 1300], [1, 9, 1100, 20000]),
     ([0, 2000], [600, 1535, 1536, 2560, 9000], [1, 511, 512, 513, 6000]),
 ])
 def test_steps(dev, lits, matches, offs):
     rng = np.random.default_rng(len(lits) * 100 + len(matches))
-    blobs, sizes = zip(*[_block(rng, lits, matches, offs, total) for total in (1, 500, 2560, 9000, 100000)])
+    blobs, sizes = zip(*[_block(rng, lits, matches, offs, total) for total in (1, 500, 2560, 9000, 31000, 100000)])
     ch = workloads._pack([oracle.LZ4] * len(blobs), list(blobs), list(sizes))
-    assert (assert_parity(oracle.LZ4, ch, dev) == 0).all()
+    assert (assert_parity(oracle.LZ4, ch, dev) == 0).all()                      # a team a block
+    assert (assert_parity(oracle.LZ4, ch, dev, waves_per_block=1) == 0).all()   # a wave a block
     # The same blocks with an output range that ends inside a step, cut input
     # and an offset that reaches before the chunk.
     bad, caps = [], []
@@ -71,4 +73,5 @@ def test_steps(dev, lits, matches, offs):
         bad.append(_seq(b"ab", 9, 3) + b)
         caps.append(n + 11)
     ch = workloads._pack([oracle.LZ4] * len(bad), bad, caps)
-    assert (assert_parity(oracle.LZ4, ch, dev) != 0).all()
+    st = assert_parity(oracle.LZ4, ch, dev)
+    assert (st != 0).all() and (assert_parity(oracle.LZ4, ch, dev, waves_per_block=1) == st).all()
