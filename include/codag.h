@@ -75,8 +75,9 @@ enum {
  *                     most 256 chunks and RLE v2 launches of at most 2048
  *                     chunks, without chunk_ticks, are decoded
  *                     group-parallel, and byte RLE launches of at most 2048
- *                     chunks by a workgroup per chunk), 1 = one wave per
- *                     chunk,
+ *                     chunks and RLE v2 launches of at most 256 chunks, of
+ *                     any element type, by a workgroup per chunk without a
+ *                     workspace), 1 = one wave per chunk,
  *                     2 = group-parallel (not with chunk_ticks).
  *                     Group-parallel: an index pass finds where the groups
  *                     (RLE v1 runs and literal lists; RLE v2 runs) start,
@@ -118,8 +119,9 @@ enum {
  *                     ORC writes string lengths and other unsigned streams
  *                     so; the RLE v2 DELTA delta base stays signed).
  *                     Element types other than signed 8-byte values use the
- *                     one-wave-per-chunk decoder (group_parallel 2 and the
- *                     variants return CODAG_E_INVALID_ARGUMENT).
+ *                     one-wave-per-chunk decoder or the workgroup-per-chunk
+ *                     one above (group_parallel 2 and the variants return
+ *                     CODAG_E_INVALID_ARGUMENT).
  */
 enum {
     CODAG_VARIANT_DEFAULT = 0,

@@ -210,6 +210,9 @@ int decompress(int codec, const uint8_t *comp_buf, const uint64_t *chunk_offsets
                                                      n_chunks, wpb, chunk_status, ds->err, ticks, s);
         case CODAG_RLE_V2: {
             const int gp = opts ? opts->group_parallel : 0;
+            if (gp == 0 && !ticks && n_chunks <= kV2BlocksMaxChunks)
+                return launch_rle_v2_blocks(8, false, comp_buf, chunk_offsets, out_buf, out_offsets,
+                                            (uint32_t)n_chunks, chunk_status, ds->err, s);
             if (gp == 2 || (gp == 0 && !ticks && n_chunks <= kSplitV2MaxChunks)) {
                 if (noalloc && rle_v2_split_workspace((uint32_t)n_chunks) > kNoAllocScratchBytes)
                     return CODAG_E_INVALID_ARGUMENT;

@@ -42,6 +42,12 @@ int launch_rle_v2_split(const uint8_t *comp, const uint64_t *coff, uint8_t *out,
                         const uint64_t *ooff, uint32_t n, int32_t *status, unsigned long long *err,
                         hipStream_t s, void *workspace);
 size_t rle_v2_split_workspace(uint32_t n);
+
+// RLE v2 with a workgroup per chunk, any element type, on stream s, for
+// launches of up to kV2BlocksMaxChunks chunks.
+int launch_rle_v2_blocks(int elem_bytes, bool is_unsigned, const uint8_t *comp, const uint64_t *coff, uint8_t *out,
+                         const uint64_t *ooff, uint32_t n, int32_t *status, unsigned long long *err, hipStream_t s);
+constexpr uint32_t kV2BlocksMaxChunks = 256;
 constexpr uint64_t kSplitV2MaxChunks = 2048;
 // Per chunk: 8 range starts of 8 bytes, the stop value and padding (16
 // bytes), two 8-byte error keys.

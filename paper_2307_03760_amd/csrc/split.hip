@@ -437,21 +437,26 @@ using V2IndexRing = InRingT<4096>;
 // Where each range starts (byte position, first value) and the value at
 // which the index pass stopped (the chunk's value count, or the first value
 // of the run where it found an error).
-struct V2Split {
-    uint2 start[kV2Ranges];
+template <uint32_t R>
+struct V2SplitT {
+    static constexpr uint32_t kRanges = R;
+    uint2 start[R];
     uint32_t stop, pad[3];
 };
+using V2Split = V2SplitT<kV2Ranges>;
 static_assert(sizeof(V2Split) + 2 * sizeof(unsigned long long) == kSplitV2WorkspacePerChunk,
               "workspace layout");
 
+template <uint32_t R>
 __device__ __forceinline__ uint32_t v2_threshold(uint32_t cap, uint32_t j) {
-    return (uint32_t)((uint64_t)cap * j / kV2Ranges);
+    return (uint32_t)((uint64_t)cap * j / R);
 }
 
 // Ranges whose first value is at most nv start at the run at (pos, nv).
+template <class Split>
 __device__ __forceinline__ void v2_cut(uint32_t &j, uint32_t cap, uint32_t pos, uint32_t nv,
-                                       V2Split *sp) {
-    while (j < kV2Ranges && nv >= v2_threshold(cap, j)) {
+                                       Split *sp) {
+    while (j < Split::kRanges && nv >= v2_threshold<Split::kRanges>(cap, j)) {
         if (lane() == 0) sp->start[j] = make_uint2(pos, nv);
         j++;
     }
@@ -463,10 +468,11 @@ __device__ __forceinline__ void v2_cut(uint32_t &j, uint32_t cap, uint32_t pos, 
 // value (for the cuts).  Stops like the decoder: at the first header that is
 // not a SHORT_REPEAT, at the end of input, or with the output full.  On an
 // error, errnv is the first value of the failing run.
-template <class Ring>
+template <class Ring, class Split>
 __device__ __forceinline__ int v2_index_short_repeats(Ring &in, uint32_t &pos, uint32_t end,
                                                       uint32_t &nv, uint32_t cap, uint32_t &j,
-                                                      V2Split *sp, uint32_t &errnv) {
+                                                      Split *sp, uint32_t &errnv) {
+    constexpr uint32_t kV2Ranges = Split::kRanges;
     const uint32_t l = lane();
     for (;;) {
         in.ensure(pos + 72);
@@ -493,7 +499,7 @@ __device__ __forceinline__ int v2_index_short_repeats(Ring &in, uint32_t &pos, u
                 t = readlane(n8, t);
                 if (t >= kWave) break;
             }
-            if (acc <= cap && (j >= kV2Ranges || v2_threshold(cap, j) >= acc)) {
+            if (acc <= cap && (j >= kV2Ranges || v2_threshold<kV2Ranges>(cap, j) >= acc)) {
                 nv = acc;
                 if (t >= 128) {
                     t -= 128;
@@ -536,8 +542,8 @@ __device__ __forceinline__ int v2_index_short_repeats(Ring &in, uint32_t &pos, u
             fo = over ? (uint32_t)__builtin_ctzll(over) : kWave;
         }
         const uint32_t lim = min(ff, fo);
-        while (j < kV2Ranges && v2_threshold(cap, j) < n1) {
-            const uint64_t m = ballot(mine && l < lim && at >= v2_threshold(cap, j));
+        while (j < kV2Ranges && v2_threshold<kV2Ranges>(cap, j) < n1) {
+            const uint64_t m = ballot(mine && l < lim && at >= v2_threshold<kV2Ranges>(cap, j));
             if (!m) break;
             const uint32_t L = (uint32_t)__builtin_ctzll(m);
             const uint32_t a = uni(readlane(at, L));
@@ -612,35 +618,16 @@ __device__ __forceinline__ uint32_t v2_long_run(uint64_t x, uint64_t y, uint64_t
     return type == 1 ? 2 + data : type == 2 ? adv_p : adv_t;
 }
 
-// Index pass, one wave per chunk: the checks of the decoder's header parse,
-// in its order.
-__global__ void __launch_bounds__(kWave * kV2IndexWpb)
-    rle_v2_index(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff,
-                 uint32_t n, V2Split *split, unsigned long long *keys) {
-    __shared__ __align__(16) uint32_t s_ring[kV2IndexWpb][V2IndexRing::kLdsWords];
-    __shared__ __align__(16) uint32_t s_land[kV2IndexWpb][V2IndexRing::kLand];
-    const uint32_t wave = uni(threadIdx.x / kWave);
-    const uint32_t c = blockIdx.x * kV2IndexWpb + wave;
-    if (c >= n) return;
-    V2Split *sp = &split[c];
-    if (lane() == 0) keys[2 * c + 1] = ~0ull;  // the decode pass's key
-    const uint64_t i0 = coff[c], i1 = coff[c + 1], o0 = ooff[c], o1 = ooff[c + 1];
-    const uint32_t in_len = (uint32_t)(i1 - i0), out_len = (uint32_t)(o1 - o0);
-    if ((((i1 - i0) | (o1 - o0)) >> 31) != 0 || (out_len & 7) ||
-        (reinterpret_cast<uintptr_t>(out + o0) & 7)) {
-        if (lane() < kV2Ranges) sp->start[lane()] = make_uint2(0, 0);
-        if (lane() == 0) {
-            sp->stop = 0;
-            keys[2 * c] = error_key(0, CODAG_E_INVALID_ARGUMENT);
-        }
-        return;
-    }
-    V2IndexRing in;
-    in.init(comp + i0, in_len, s_ring[wave], s_land[wave]);
-    const uint32_t end = in.gend, cap = out_len / 8;
+// The index walk of one wave over a chunk of cap values: the checks of the
+// decoder's header parse, in its order.  Fills sp; returns the error key (all
+// ones when there is none).  publish(j): j range starts are known.
+template <class Ring, class Split, class Publish>
+__device__ __forceinline__ unsigned long long v2_index_chunk(Ring &in, uint32_t cap, Split *sp, Publish publish) {
+    const uint32_t end = in.gend;
     uint32_t pos = in.skip, nv = 0, j = 0, errnv = 0;
     int st = CODAG_OK;
     while (nv < cap) {
+        publish(j);
         if (pos >= end) {
             st = CODAG_E_TRUNCATED;
             errnv = nv;
@@ -666,7 +653,7 @@ __global__ void __launch_bounds__(kWave * kV2IndexWpb)
             uint32_t len;
             bool ok;
             const uint32_t adv = v2_long_run(x, y, z, len, ok);
-            const bool cut = j < kV2Ranges && nv >= v2_threshold(cap, j);
+            const bool cut = j < Split::kRanges && nv >= v2_threshold<Split::kRanges>(cap, j);
             if (ok && !cut && len <= cap - nv && adv <= end - pos) {
                 pos += adv;
                 nv += len;
@@ -728,12 +715,44 @@ __global__ void __launch_bounds__(kWave * kV2IndexWpb)
     }
     const uint32_t stop = st == CODAG_OK ? nv : errnv;
     // Ranges not started are empty.
-    for (uint32_t k = j; k < kV2Ranges; k++)
+    for (uint32_t k = j; k < Split::kRanges; k++)
         if (lane() == 0) sp->start[k] = make_uint2(pos, stop);
-    if (lane() == 0) {
-        sp->stop = stop;
-        keys[2 * c] = st == CODAG_OK ? ~0ull : error_key(errnv, st);
+    if (lane() == 0) sp->stop = stop;
+    return st == CODAG_OK ? ~0ull : error_key(errnv, st);
+}
+
+// What every RLE launch checks of a chunk: offsets in order and below 2 GiB,
+// whole values, aligned output.
+template <class E>
+__device__ __forceinline__ bool v2_layout_ok(uint64_t in_len, uint64_t out_len, const uint8_t *dst) {
+    return ((in_len | out_len) >> 31) == 0 && out_len % E::kBytes == 0 &&
+           reinterpret_cast<uintptr_t>(dst) % E::kBytes == 0;
+}
+
+// Index pass, one wave per chunk.
+__global__ void __launch_bounds__(kWave * kV2IndexWpb)
+    rle_v2_index(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff,
+                 uint32_t n, V2Split *split, unsigned long long *keys) {
+    __shared__ __align__(16) uint32_t s_ring[kV2IndexWpb][V2IndexRing::kLdsWords];
+    __shared__ __align__(16) uint32_t s_land[kV2IndexWpb][V2IndexRing::kLand];
+    const uint32_t wave = uni(threadIdx.x / kWave);
+    const uint32_t c = blockIdx.x * kV2IndexWpb + wave;
+    if (c >= n) return;
+    V2Split *sp = &split[c];
+    if (lane() == 0) keys[2 * c + 1] = ~0ull;  // the decode pass's key
+    const uint64_t i0 = coff[c], i1 = coff[c + 1], o0 = ooff[c], o1 = ooff[c + 1];
+    if (!v2_layout_ok<I64>(i1 - i0, o1 - o0, out + o0)) {
+        if (lane() < kV2Ranges) sp->start[lane()] = make_uint2(0, 0);
+        if (lane() == 0) {
+            sp->stop = 0;
+            keys[2 * c] = error_key(0, CODAG_E_INVALID_ARGUMENT);
+        }
+        return;
     }
+    V2IndexRing in;
+    in.init(comp + i0, (uint32_t)(i1 - i0), s_ring[wave], s_land[wave]);
+    const unsigned long long key = v2_index_chunk(in, (uint32_t)(o1 - o0) / 8, sp, [](uint32_t) {});
+    if (lane() == 0) keys[2 * c] = key;
     __builtin_amdgcn_s_waitcnt(0);
 }
 
@@ -783,6 +802,120 @@ int launch_rle_v2_split(const uint8_t *comp, const uint64_t *coff, uint8_t *out,
     hipError_t e = hipGetLastError();
     if (!workspace && hipFreeAsync(ws, s) != hipSuccess) return CODAG_E_HIP;
     return e == hipSuccess ? CODAG_OK : CODAG_E_HIP;
+}
+
+// ---- RLE v2 with a workgroup per chunk -----------------------------------
+//
+// For launches of at most kV2BlocksMaxChunks chunks, of any element type: wave
+// 0 walks the headers and kV2BlockRanges decoding waves start as soon as the
+// range after theirs is cut, so a chunk takes little more than its walk, in
+// one launch, without a workspace, a status pass or a copy of the range starts
+// through HBM.  Chunks of up to kV2BlockSmall values are decoded by wave 0 as
+// they are read: the walk and a second read of the input cost more there.
+//
+// The walk is what is left (some 30 of 38 us for a row group of 10,000
+// values).  Measured against the three passes: one row group 47 to 38 us, 256
+// of them 77 to 63 (90 by one wave each, as narrower types were decoded); 512
+// chunks of 32,768 values 164 both ways and 512 of 10,000 two-byte values 78
+// against 74 by one wave each, hence the limit.  With 15 ranges instead of 8:
+// 43 us for one row group, 255 for 512 chunks (waiting waves in the way).
+constexpr uint32_t kV2BlockRanges = 8, kV2BlockSmall = 1536;
+constexpr uint32_t kV2BlockThreads = kWave * (kV2BlockRanges + 1);
+
+template <class E>
+__global__ void __launch_bounds__(kV2BlockThreads)
+    rle_v2_blocks(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff, uint32_t n,
+                  int32_t *status, unsigned long long *err) {
+    __shared__ __align__(16) uint32_t s_iring[V2IndexRing::kLdsWords];
+    __shared__ __align__(16) uint32_t s_iland[V2IndexRing::kLand];
+    __shared__ __align__(16) uint32_t s_ring[kV2BlockRanges][kRingLdsWords];
+    __shared__ __align__(16) uint32_t s_land[kV2BlockRanges][kLandWords];
+    __shared__ V2SplitT<kV2BlockRanges> s_split;
+    __shared__ unsigned long long s_key[2];  // the walk's first error, the decoders'
+    __shared__ uint32_t s_known;             // range starts known; all and the stop: kV2BlockRanges + 1
+    const uint32_t wave = uni(threadIdx.x / kWave), c = blockIdx.x;
+    if (c >= n) return;
+    const uint64_t i0 = coff[c], i1 = coff[c + 1], o0 = ooff[c], o1 = ooff[c + 1];
+    if (!v2_layout_ok<E>(i1 - i0, o1 - o0, out + o0)) {
+        if (wave == 0) report(c, CODAG_E_INVALID_ARGUMENT, status, err);
+        return;
+    }
+    const uint32_t in_len = (uint32_t)(i1 - i0), cap = (uint32_t)(o1 - o0) / E::kBytes;
+    if (cap <= kV2BlockSmall) {
+        if (wave == 0) {
+            InRing in;
+            in.init(comp + i0, in_len, s_ring[0], s_land[0]);
+            const int st = decode_rle_v2<E>(in, reinterpret_cast<typename E::T *>(out + o0), cap);
+            __builtin_amdgcn_s_waitcnt(0);
+            report(c, st, status, err);
+        }
+        return;
+    }
+    if (threadIdx.x == 0) {
+        s_key[1] = ~0ull;
+        s_known = 0;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        __builtin_amdgcn_s_setprio(3);
+        V2IndexRing in;
+        in.init(comp + i0, in_len, s_iring, s_iland);
+        uint32_t told = 0;
+        const unsigned long long key = v2_index_chunk(in, cap, &s_split, [&](uint32_t j) {
+            if (j != told) {
+                if (lane() == 0) lds_store_release(&s_known, j);
+                told = j;
+            }
+        });
+        if (lane() == 0) {
+            s_key[0] = key;
+            lds_store_release(&s_known, kV2BlockRanges + 1);
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+    } else {
+        const uint32_t j = wave - 1;
+        // The next range's start is this one's end.  (The walk always ends.)
+        while (lds_load_acquire(&s_known) < j + 2) __builtin_amdgcn_s_sleep(4);
+        uint32_t pos = uni(s_split.start[j].x), nv = uni(s_split.start[j].y);
+        const uint32_t e = uni(j + 1 < kV2BlockRanges ? s_split.start[j + 1].y : s_split.stop);
+        if (nv < e) {
+            InRing in;
+            in.init_at(comp + i0, in_len, s_ring[j], s_land[j], pos);
+            typename E::T *dst = reinterpret_cast<typename E::T *>(out + o0);
+            const int st = decode_rle_v2_runs<E>(in, pos, in.gend, dst, nv, e);
+            if (st != CODAG_OK && lane() == 0) atomicMin(&s_key[1], error_key(nv, st));
+            __builtin_amdgcn_s_waitcnt(0);
+        }
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const unsigned long long k = min(s_key[0], s_key[1]);
+        report(c, k == ~0ull ? CODAG_OK : -(int)(k & 15), status, err);
+    }
+}
+
+template <class E>
+static int launch_v2_blocks(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff, uint32_t n,
+                            int32_t *status, unsigned long long *err, hipStream_t s) {
+    hipLaunchKernelGGL(rle_v2_blocks<E>, dim3(n), dim3(kV2BlockThreads), 0, s, comp, coff, out, ooff, n, status, err);
+    return hipGetLastError() == hipSuccess ? CODAG_OK : CODAG_E_HIP;
+}
+
+template <bool SIGNED>
+static int launch_v2_blocks_width(int eb, const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff,
+                                  uint32_t n, int32_t *status, unsigned long long *err, hipStream_t s) {
+    switch (eb) {
+        case 1: return launch_v2_blocks<Elem<1, SIGNED>>(comp, coff, out, ooff, n, status, err, s);
+        case 2: return launch_v2_blocks<Elem<2, SIGNED>>(comp, coff, out, ooff, n, status, err, s);
+        case 4: return launch_v2_blocks<Elem<4, SIGNED>>(comp, coff, out, ooff, n, status, err, s);
+        default: return launch_v2_blocks<Elem<8, SIGNED>>(comp, coff, out, ooff, n, status, err, s);
+    }
+}
+
+int launch_rle_v2_blocks(int elem_bytes, bool is_unsigned, const uint8_t *comp, const uint64_t *coff, uint8_t *out,
+                         const uint64_t *ooff, uint32_t n, int32_t *status, unsigned long long *err, hipStream_t s) {
+    return is_unsigned ? launch_v2_blocks_width<false>(elem_bytes, comp, coff, out, ooff, n, status, err, s)
+                       : launch_v2_blocks_width<true>(elem_bytes, comp, coff, out, ooff, n, status, err, s);
 }
 
 }  // namespace codag

@@ -52,6 +52,8 @@ int launch_typed(int codec, int elem_bytes, bool is_unsigned, const uint8_t *com
                  unsigned long long *err, uint64_t *ticks, bool one_wave, hipStream_t s) {
     if (codec == CODAG_BYTE_RLE && !one_wave && !ticks && n <= kByteBlocksMaxChunks)
         return launch_byte_rle_blocks(comp, coff, out, ooff, n, status, err, s);
+    if (codec == CODAG_RLE_V2 && !one_wave && !ticks && n <= kV2BlocksMaxChunks)
+        return launch_rle_v2_blocks(elem_bytes, is_unsigned, comp, coff, out, ooff, n, status, err, s);
     if (codec == CODAG_BYTE_RLE)
         return launch_t<CODAG_BYTE_RLE, I64>(comp, coff, out, ooff, n, status, err, ticks, s);
     if (codec == CODAG_RLE_V1)
