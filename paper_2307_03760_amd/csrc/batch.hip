@@ -104,7 +104,7 @@ namespace {
 
 constexpr uint32_t kLdsPerCu = 160 * 1024;
 constexpr int kBatchTB = 9;  // default Deflate literal/length table bits in the batched kernel
-constexpr int kVgprWavesPerSimd = 5;  // the decoders use up to 92 VGPRs
+constexpr int kVgprWavesPerSimd = 3;  // decode_batch uses up to 136 VGPRs
 
 template <int TB>
 uint32_t lds_per_wave_tb(int hist_kib) {

@@ -98,7 +98,9 @@ struct BuildResult {
 
 // Builds the lookup table (2^tb entries) of the canonical code whose lengths
 // are lens[0..n) (n <= 320), lane-parallel: per-length counts and each
-// symbol's rank come from ballots, then every symbol fills its table slots.
+// symbol's rank come from ballots, then every slot of the table decodes its
+// own index.  (13,000 cycles for a literal/length table, 14,000 to 35,000 with
+// the symbols filling their slots; 5,000 instead of 11,000 for distances.)
 __device__ __forceinline__ BuildResult build_table(const uint8_t *lens, uint32_t n, uint32_t tb,
                                                    int use, uint32_t *tab, uint16_t *sorted,
                                                    CodeMeta *meta) {
@@ -109,9 +111,10 @@ __device__ __forceinline__ BuildResult build_table(const uint8_t *lens, uint32_t
     uint32_t rank[5];
 #pragma unroll
     for (int p = 0; p < 5; p++) {
+        rank[p] = 0;
+        if (64u * p >= n) break;
         uint32_t s = 64 * p + l;
         uint32_t m = s < n ? lens[s] : 0;
-        rank[p] = 0;
 #pragma unroll
         for (int len = 1; len < 16; len++) {
             uint64_t b = ballot(m == (uint32_t)len);
@@ -148,27 +151,30 @@ __device__ __forceinline__ BuildResult build_table(const uint8_t *lens, uint32_t
             meta->base[l] = (uint16_t)base;
         }
     }
-    if (left > 0) {  // incomplete: codes not in the set are invalid
-        for (uint32_t i = l; i < (1u << tb); i += kWave) tab[i] = kEntInvalid;
-    }
     wave_sync();
 #pragma unroll
     for (int p = 0; p < 5; p++) {
+        if (64u * p >= n) break;
         uint32_t s = 64 * p + l;
         uint32_t m = s < n ? lens[s] : 0;
         if (m != 0) {
             // The first code of length m is the limit below it at m bits.
             const uint32_t code = ((uint32_t)meta->lim[m - 1] >> (15 - m)) + rank[p];
             sorted[(uint16_t)(meta->base[m] + code)] = (uint16_t)s;
-            if (m <= tb) {
-                uint32_t rev = __builtin_bitreverse32(code) >> (32 - m);
-                const uint32_t e = table_entry(use, s, m);
-                for (uint32_t k = 0; k < (1u << (tb - m)); k++) tab[rev | (k << m)] = e;
-            } else {
-                uint32_t prefix = code >> (m - tb);
-                tab[__builtin_bitreverse32(prefix) >> (32 - tb)] = kEntSlow;
-            }
         }
+    }
+    wave_sync();
+    // Every slot decodes its own index: the same work for every code, where a
+    // symbol filling its own slots takes up to 2^tb / 2 stores on one lane.
+    for (uint32_t i = l; i < (1u << tb); i += kWave) {
+        const uint32_t rev = __builtin_bitreverse32(i) >> 17;
+        uint32_t len = 1;
+#pragma unroll
+        for (uint32_t k = 1; k < 16; k++) len += rev >= meta->lim[k] ? 1u : 0u;
+        uint32_t e = kEntInvalid;  // past the last code of an incomplete set
+        if (len <= tb) e = table_entry(use, sorted[(uint16_t)(meta->base[len] + (rev >> (15 - len)))], len);
+        else if (len < 16) e = kEntSlow;
+        tab[i] = e;
     }
     wave_sync();
     return r;
@@ -213,7 +219,7 @@ struct DeflateLds : DeflateTables<TB> {
         uint8_t lens[320];          // while a block's tables are built
         uint32_t segs[kRoundSegs];  // while its symbols decode
     };
-    uint64_t queue[kCopyQueue + 1];  // pending copies, and a spare
+    uint64_t queue[kCopyQueue];  // pending copies
     __attribute__((aligned(16))) uint8_t window[H];
     uint8_t window_pad[16];  // eight-byte reads may pass the window's end
 };
@@ -820,14 +826,17 @@ constexpr uint32_t kMaxPasses = 20;
 // stops) is behind one branch that the wave takes when any lane needs it.
 template <int TB>
 struct LaneToken {
-    const uint8_t *at;  // the stretch's first byte (LDS)
+    const uint8_t *at;    // the stretch's first byte (LDS)
+    const uint8_t *idle;  // where lanes with nothing to decode read: one place (each reading its own
+                          // kept LDS busy 54% of the time instead of 47; 5.75 to 5.52 ms, 16,384 chunks)
     uint32_t r, x;      // next token's first bit in the stretch; its TB bits
     uint32_t e, d;      // its entries; d is 0 for a literal
     uint64_t raw;
 
     __device__ __forceinline__ void read() { raw = *reinterpret_cast<const u64_any *>(at + (r >> 3)); }
-    __device__ __forceinline__ void start(const uint8_t *stretch, uint32_t bit) {
+    __device__ __forceinline__ void start(const uint8_t *stretch, uint32_t bit, const uint8_t *nothing) {
         at = stretch;
+        idle = nothing;
         r = bit;
         read();
         x = (uint32_t)(raw >> (r & 7));
@@ -838,9 +847,11 @@ struct LaneToken {
     // Looks the token up; true if some lane's needs resolve().
     __device__ __forceinline__ bool look(const DeflateTables<TB> *lds, bool on) {
         e = lds->tab[on ? x & ((1u << TB) - 1) : DeflateTables<TB>::kIdle];
-        read();
-        const uint32_t d0 = lds->dist()[(bits() >> ent_bits(e)) & ((1u << kDistBits) - 1)];
-        d = d0 & (uint32_t)((int32_t)e >> 31);
+        raw = *reinterpret_cast<const u64_any *>(on ? at + (r >> 3) : idle);
+        // (A bit field's position is e's low five bits.  Lanes without a copy
+        // all look one entry up.)
+        const uint32_t m = (uint32_t)((int32_t)e >> 31);
+        d = lds->dist()[bit_field(bits(), e, kDistBits) & m] & m;
         return ballot(((e | d) & (kEntSlow | kEntStop)) != 0) != 0;
     }
     // Codes longer than the tables; true if the lane's token is a stop.
@@ -856,10 +867,10 @@ struct LaneToken {
         return ((e | d) & kEntStop) != 0;
     }
     __device__ __forceinline__ uint32_t length() const {
-        return ent_len(e) + ((bits() >> ent_cl(e)) & ((1u << ent_lex(e)) - 1));
+        return ent_len(e) + bit_field(bits(), ent_cl(e), ent_lex(e));
     }
     __device__ __forceinline__ uint32_t distance() const {
-        return ent_dist(d) + ((uint32_t)(raw >> ((r & 7) + ent_bits(e) + ent_cl(d))) & ((1u << ent_ex(d)) - 1));
+        return ent_dist(d) + bit_field((uint32_t)(raw >> ((r & 7) + ent_bits(e) + ent_cl(d))), 0, ent_ex(d));
     }
     // Past the token.  Of raw's 57 bits from r on, the longest token leaves
     // nine.
@@ -881,10 +892,10 @@ struct LaneToken {
 // kWhyEob, ...; 0: it did not); segs gets its segments' first tokens, output
 // bytes << 12 and copies << 6.
 template <int TB>
-__device__ __forceinline__ void lane_pass(const DeflateTables<TB> *lds, uint32_t *segs, const uint8_t *mine, bool need,
-                                          uint32_t rs, uint32_t &tried, uint32_t &re, uint32_t &rz, uint32_t &why) {
+__device__ __forceinline__ void lane_pass(const DeflateTables<TB> *lds, uint32_t *segs, const uint8_t *inb,
+                                          const uint8_t *mine, bool need, uint32_t rs, uint32_t &tried, uint32_t &re, uint32_t &rz, uint32_t &why) {
     LaneToken<TB> t;
-    t.start(mine, rs);
+    t.start(mine, rs, inb);
     bool on = need;
     uint32_t sp = rs, acc = 0;
     if (need) {
@@ -914,12 +925,12 @@ __device__ __forceinline__ void lane_pass(const DeflateTables<TB> *lds, uint32_t
 }
 
 // Writes the looked-up token of an emitting lane: a literal into the window, a
-// copy into the queue at qi (its last entry, queue[spare_at], takes the other
-// lanes' stores).  A token whose distance reaches before the chunk or whose
+// copy into the queue at qi.  (The other lanes' stores sent to a spare place
+// instead would spare two branches, but stores of many lanes to one address
+// are serialised.)  A token whose distance reaches before the chunk or whose
 // output passes its end sets bad and stops the lane.
 template <int TB, uint32_t H>
-__device__ __forceinline__ void emit_token(LaneToken<TB> &t, const LinearOut<H> &o, uint64_t *queue, uint32_t spare_at,
-                                           uint8_t *spare, uint32_t start, uint32_t lim, bool tight, bool &on,
+__device__ __forceinline__ void emit_token(LaneToken<TB> &t, const LinearOut<H> &o, uint64_t *queue, uint32_t start, uint32_t lim, bool tight, bool &on,
                                            uint32_t er, uint32_t &dst, uint32_t &qi, int &bad) {
     const uint32_t len = t.length();
     const bool copy = (int32_t)t.e < 0;
@@ -929,10 +940,9 @@ __device__ __forceinline__ void emit_token(LaneToken<TB> &t, const LinearOut<H> 
         if (copy && dist > dst - o.o0) bad = CODAG_E_CORRUPT;
     }
     const bool lit = on && !copy && !bad;
-    uint8_t *const to = lit ? o.win + (dst - o.wlo) : spare;
-    *to = (uint8_t)ent_byte(t.e);
+    if (lit) o.win[dst - o.wlo] = (uint8_t)ent_byte(t.e);
     const bool queued = copy && !bad;
-    queue[queued ? qi : spare_at] = copy_entry(len, dst - start, dist);
+    if (queued) queue[qi] = copy_entry(len, dst - start, dist);
     qi += queued ? 1u : 0u;
     dst += bad ? 0u : len;
     t.next();
@@ -945,7 +955,6 @@ __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &
     static_assert(Ring::kLdsWords <= kRoundInWords, "the round's input takes the ring's place");
     const uint32_t l = lane();
     uint8_t *const inb = reinterpret_cast<uint8_t *>(in.ring);
-    uint8_t *const spare = reinterpret_cast<uint8_t *>(&lds->queue[kCopyQueue]);
     const uint32_t endbit = 8 * in.gend;
     uint32_t p = 8 * bi.next - bi.cnt;  // bit position of the next code
     for (;;) {
@@ -977,7 +986,7 @@ __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &
                 poor = true;
                 break;
             }
-            lane_pass<TB>(lds, lds->segs + kLaneSegs * l, mine, need, rs, tried, re, rz, why);
+            lane_pass<TB>(lds, lds->segs + kLaneSegs * l, inb, mine, need, rs, tried, re, rz, why);
             // Start over where the lane before ended (if it did not stop).
             const uint32_t ue = wave_shift_up1(why ? ~0u : re);
             if (l != 0 && l < live && ue != ~0u) rs = ue - kLaneBits;
@@ -1009,7 +1018,7 @@ __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &
             const bool tight = start + made > lim;  // the output range ends in this step
             int bad = CODAG_OK;
             LaneToken<TB> t;
-            t.start(inb + ofs + (kSegBits / 8) * min(g, nseg - 1), c & (kSegBits - 1));
+            t.start(inb + ofs + (kSegBits / 8) * min(g, nseg - 1), c & (kSegBits - 1), inb);
             bool on = l < cnt && t.r < er;
             while (ballot(on)) {
                 if (t.look(lds, on)) t.resolve(lds);
@@ -1017,7 +1026,7 @@ __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &
                     t.e = t.d = 0;  // the step is full
                     on = false;
                 }
-                emit_token<TB, H>(t, o, lds->queue, kCopyQueue, spare, start, lim, tight, on, er, dst, qi, bad);
+                emit_token<TB, H>(t, o, lds->queue, start, lim, tight, on, er, dst, qi, bad);
             }
             const uint32_t r = t.r;
             wave_sync();

@@ -210,7 +210,7 @@ struct Lds {
     DeflateLds<9, kTeamH> d;  // tables, window, and wave 0's own lists
     uint32_t in[4 * kTeamPieces];
     uint32_t segs[kTeam * kRoundSegs];
-    uint64_t queue[kTeamQueue + 1], hops[kHops ? kTeamQueue : 1];
+    uint64_t queue[kTeamQueue], hops[kHops ? kTeamQueue : 1];
     // Wave 0's orders: rounds from bit p on, or no more; and its output state.
     uint32_t go, p, pos, wlo, fa, room;
     // What the waves tell each other: where the last lane of each ended
@@ -241,7 +241,6 @@ static __device__ __forceinline__ int rounds(const uint8_t *gbase, uint32_t gend
     constexpr uint32_t kAppend = LinearOut<kTeamH>::kAppend;
     const uint32_t l = lane(), tid = wave * kWave + l;
     uint8_t *const inb = reinterpret_cast<uint8_t *>(s->in);
-    uint8_t *const spare = reinterpret_cast<uint8_t *>(&s->queue[kTeamQueue]);
     const uint32_t endbit = 8 * gend;
     for (;;) {
         if (p >= endbit) return CODAG_E_TRUNCATED;
@@ -259,7 +258,7 @@ static __device__ __forceinline__ int rounds(const uint8_t *gbase, uint32_t gend
         for (uint32_t pass = 0;; pass++) {
             const bool need = tid < live && rs != tried;
             if (ballot(need))
-                lane_pass<9>(&s->d, s->segs + kLaneSegs * tid, mine, need, rs, tried, re, rz, why);
+                lane_pass<9>(&s->d, s->segs + kLaneSegs * tid, inb, mine, need, rs, tried, re, rz, why);
             if (l == kWave - 1) s->edge[wave] = why ? ~0u : re;
             __syncthreads();
             uint32_t ue = wave_shift_up1(why ? ~0u : re);
@@ -330,11 +329,11 @@ static __device__ __forceinline__ int rounds(const uint8_t *gbase, uint32_t gend
             const uint32_t er = whyl && g == nseg - 1 ? zl & (kSegBits - 1) : kSegBits;
             int bad = CODAG_OK;
             LaneToken<9> t;
-            t.start(inb + ofs + (kSegBits / 8) * min(g, nseg - 1), c & (kSegBits - 1));
+            t.start(inb + ofs + (kSegBits / 8) * min(g, nseg - 1), c & (kSegBits - 1), inb);
             bool on = tid < cnt && t.r < er;
             while (ballot(on)) {
                 if (t.look(&s->d, on)) t.resolve(&s->d);
-                emit_token<9, kTeamH>(t, o, s->queue, kTeamQueue, spare, start, lim, tight, on, er, dst, qi, bad);
+                emit_token<9, kTeamH>(t, o, s->queue, start, lim, tight, on, er, dst, qi, bad);
             }
             const uint64_t badm = ballot(bad != CODAG_OK);
             if (badm) {

@@ -31,6 +31,12 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, uint32_t l) {
     return ((uint64_t)readlane((uint32_t)(v >> 32), l) << 32) | readlane((uint32_t)v, l);
 }
 
+// n (below 32) bits of x from bit `from` on; only the low five bits of either
+// count.
+__device__ __forceinline__ uint32_t bit_field(uint32_t x, uint32_t from, uint32_t n) {
+    return __builtin_amdgcn_ubfe(x, from, n);
+}
+
 // Orders LDS accesses of this wave's lanes: those before it are visible to
 // every lane after it (DS operations of one wave execute in order, so only
 // the compiler needs telling).
