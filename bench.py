@@ -334,7 +334,7 @@ def launch_description(codec: int, n_chunks: int) -> str:
     if codec == 3:
         return "decode_plain<DEFLATE>: one wave64 per chunk, 1 wave per workgroup, 4 KiB LDS window"
     if codec == 5:
-        return "decode_plain<LZ4>: one wave64 per chunk, 1 wave per workgroup, 2 KiB LDS window"
+        return "decode_plain<LZ4>: one wave64 per chunk, 1 wave per workgroup, 4 KiB LDS window"
     return "decode_plain: one wave64 per chunk, 4 waves per workgroup"
 
 
