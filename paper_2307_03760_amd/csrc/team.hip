@@ -23,6 +23,7 @@
 #include "../../include/codag.h"
 #include "decode.hpp"
 #include "internal.hpp"
+#include "share.hpp"
 
 namespace codag {
 
@@ -760,8 +761,8 @@ __global__ void __launch_bounds__(kTeam * kWave) __attribute__((amdgpu_waves_per
             if (len > room) {
                 st = CODAG_E_OVERFLOW;
             } else {
-                const uint32_t share = (len / kTeam + 1023) & ~1023u, a = min(len, wave * share);
-                wave_stream(out + at + a, framed + src + a, min(len - a, share));
+                const WavePiece mine = wave_piece(len, wave, kTeam);
+                wave_stream(out + at + mine.begin, framed + src + mine.begin, mine.size);
                 made = len;
             }
         } else if (len >= (1u << 28)) {
