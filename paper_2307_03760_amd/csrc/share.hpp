@@ -1,5 +1,4 @@
-// How the waves of a workgroup share a run of bytes (host code too: no HIP
-// here).
+// Index arithmetic of the copies (host code too: no HIP here).
 #pragma once
 
 #include <stdint.h>
@@ -19,5 +18,10 @@ constexpr WavePiece wave_piece(uint32_t len, uint32_t wave, uint32_t waves) {
     const uint32_t begin = from < len ? (uint32_t)from : len;
     return {begin, len - begin < share ? len - begin : share};
 }
+
+// Where a thread reads the 16 bytes that an output window of H bytes moves
+// towards its front: x is their place, or, past the window's end (a slide's last
+// trip is a full one), the window's last 16 bytes, which are not wanted there.
+constexpr uint32_t slide_from(uint32_t x, uint32_t H) { return x < H - 16 ? x : H - 16; }
 
 }  // namespace codag

@@ -47,7 +47,7 @@ __device__ __forceinline__ void team_room(LinearOut<kTeamH> &o, uint32_t len, ui
     const uint32_t lo = (at + len - kTeamH + kBlock - 1) & ~(kBlock - 1), d = lo - o.wlo;
     static_assert(kTeamH % (16 * kTeamThreads) == 0, "a slide's steps end at the window's end");
     for (uint32_t i = 0; i < at - lo; i += 16 * kTeamThreads) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(o.win + d + i + 16 * tid);
+        const uint4 v = *reinterpret_cast<const uint4 *>(o.win + slide_from(d + i + 16 * tid, kTeamH));
         __syncthreads();
         *reinterpret_cast<uint4 *>(o.win + i + 16 * tid) = v;
         __syncthreads();

@@ -4,6 +4,7 @@
 #pragma once
 
 #include "../../include/codag.h"
+#include "share.hpp"
 #include "stream.hpp"
 
 namespace codag {
@@ -97,10 +98,10 @@ struct LinearOut {
         }
         while (fa + kBlock <= at) flush_block(o0 + cap);
         const uint32_t lo = (at + len - H + kBlock - 1) & ~(kBlock - 1), d = lo - wlo;
-        // (A step's reads are at or past its writes; the last may take up to
-        // a block past the window, which lands past the output.)
+        // (A step's reads are at or past its writes; what the last one reads
+        // past the output lands past the output.)
         for (uint32_t i = 0; i < at - lo; i += 1024) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(win + d + i + 16 * lane());
+            const uint4 v = *reinterpret_cast<const uint4 *>(win + slide_from(d + i + 16 * lane(), H));
             wave_sync();
             *reinterpret_cast<uint4 *>(win + i + 16 * lane()) = v;
         }
