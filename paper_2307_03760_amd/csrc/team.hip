@@ -88,8 +88,17 @@ __device__ __forceinline__ uint32_t team_copies_below(const uint64_t *queue, uin
 struct CopyHop {
     // lo: source relative to the step's start + 2^19 | the copy its bytes come
     // from << 20 (kNone: none); hi: first and one past the last copy that
-    // overlaps the source.
+    // overlaps the source.  Other waves read a copy's word while its lane
+    // hops, and need its halves from one write: the words are only accessed
+    // by load and store.
     static constexpr uint32_t kNone = 0xfff, kBias = 1u << 19;
+
+    static __device__ __forceinline__ uint64_t load(const uint64_t *w) {
+        return __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    static __device__ __forceinline__ void store(uint64_t *w, uint32_t lo, uint32_t hi) {
+        __hip_atomic_store(w, ((uint64_t)hi << 32) | lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
 };
 template <uint32_t kTeamThreads, uint32_t kTeamQueue>
 __device__ __forceinline__ void team_copies(const LinearOut<kTeamH> &o, const uint64_t *queue, uint64_t *hops,
@@ -130,7 +139,7 @@ __device__ __forceinline__ void team_copies(const LinearOut<kTeamH> &o, const ui
             uint32_t d0, d1, hop;
             overlaps(q, k < nq, d0, d1, hop);
             const uint32_t rel = (((uint32_t)q >> 16) & 0xffff) - (uint32_t)(q >> 32);
-            if (k < nq) hops[k] = ((uint64_t)(d0 | (d1 << 16)) << 32) | (rel + CopyHop::kBias) | (hop << 20);
+            if (k < nq) CopyHop::store(&hops[k], (rel + CopyHop::kBias) | (hop << 20), d0 | (d1 << 16));
         }
     }
     __syncthreads();
@@ -143,16 +152,16 @@ __device__ __forceinline__ void team_copies(const LinearOut<kTeamH> &o, const ui
         const bool repeats = v && dist < len;  // its own output
         uint32_t src = dst - dist, d0, d1, hop;
         if (hops) {
-            const uint64_t h = v ? hops[k] : (uint64_t)(CopyHop::kNone << 20);
+            const uint64_t h = v ? CopyHop::load(&hops[k]) : (uint64_t)(CopyHop::kNone << 20);
             hop = ((uint32_t)h >> 20) & 0xfff;
             uint32_t over = (uint32_t)(h >> 32);
             while (ballot(hop != CopyHop::kNone)) {
                 if (hop != CopyHop::kNone) {
-                    const uint64_t hp = hops[hop], qp = queue[hop];
+                    const uint64_t hp = CopyHop::load(&hops[hop]), qp = queue[hop];
                     src += ((uint32_t)hp & 0xfffff) - CopyHop::kBias - (((uint32_t)qp >> 16) & 0xffff);
                     hop = ((uint32_t)hp >> 20) & 0xfff;
                     over = (uint32_t)(hp >> 32);
-                    hops[k] = ((uint64_t)over << 32) | (src - start + CopyHop::kBias) | (hop << 20);
+                    CopyHop::store(&hops[k], (src - start + CopyHop::kBias) | (hop << 20), over);
                 }
             }
             d0 = v ? over & 0xffff : 0u;
