@@ -332,7 +332,7 @@ def launch_description(codec: int, n_chunks: int) -> str:
         return ("group-parallel: rle_v1_index (a 16-wave workgroup per chunk finds group starts "
                 "and cuts 32 ranges) + rle_v1_groups (one wave per range) + split_finish")
     if codec == 3:
-        return "decode_plain<DEFLATE>: one wave64 per chunk, 4 waves per workgroup, 4 KiB LDS window"
+        return "decode_plain<DEFLATE>: one wave64 per chunk, 1 wave per workgroup, 4 KiB LDS window"
     if codec == 5:
         return "decode_plain<LZ4>: one wave64 per chunk, 1 wave per workgroup, 4 KiB LDS window"
     return "decode_plain: one wave64 per chunk, 4 waves per workgroup"

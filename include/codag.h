@@ -54,11 +54,9 @@ enum {
 
 /*
  * Tuning knobs; a zeroed struct (or NULL) selects the defaults.
- *   waves_per_block   wavefronts per workgroup: 1, 2 or 4 (default 4 for RLE
- *                     and for Deflate launches of more than 512 chunks with
- *                     a 4 KiB window, 1 otherwise); waves never synchronize
- *                     with each other, so this only shapes occupancy and
- *                     dispatch.
+ *   waves_per_block   wavefronts per workgroup: 1, 2 or 4 (default 1 for
+ *                     Deflate and LZ4, 4 for RLE); waves never synchronize with each
+ *                     other, so this only shapes occupancy and dispatch.
  *   lit_table_bits    Deflate literal/length lookup-table bits, 9 or 10
  *                     (default 9); longer codes take a slower path.
  *   history_kib       Deflate and LZ4 output window kept in LDS per wave: 2,

@@ -170,15 +170,14 @@ int decompress(int codec, const uint8_t *comp_buf, const uint64_t *chunk_offsets
     if (n_chunks == 0) return CODAG_OK;
     if (!comp_buf || !chunk_offsets || !out_buf || !out_offsets) return CODAG_E_INVALID_ARGUMENT;
     if (n_chunks >= (1ull << 32) - 64) return CODAG_E_INVALID_ARGUMENT;
-    // Defaults: RLE waves share a workgroup, and so do Deflate waves where
-    // there are enough chunks for every SIMD to hold the same number of them
-    // (12 waves per CU in workgroups of 4 take 5.1 ms for 16,384 chunks of 64
-    // KiB, 13 in workgroups of one 5.4; 4,096 chunks 1.63 and 1.69, 768 even);
-    // LZ4 waves, of which more fit, and larger windows go one per workgroup
-    // (4,096 LZ4 chunks 1.37 ms against 1.48).
-    int wpb = opts && opts->waves_per_block ? opts->waves_per_block
-              : lz77 && (codec == CODAG_LZ4 || n_chunks <= kTeamMaxChunks || (opts && opts->history_kib > 4)) ? 1
-                                                                          : 4;
+    // Defaults: RLE waves share a workgroup; Deflate and LZ4 waves go one
+    // per workgroup with a small window (and table), for the most resident
+    // waves and because a workgroup keeps the LDS of its finished waves until
+    // its longest chunk ends (four Deflate waves a workgroup against one:
+    // 16,384 different chunks of 64 KiB 5.26 against 4.54 ms, 20,000
+    // log-normal ones 18.7 against 13.6; 80 chunks repeated in a fixed cycle
+    // 5.1 against 5.4).
+    int wpb = opts && opts->waves_per_block ? opts->waves_per_block : lz77 ? 1 : 4;
     int tb = opts && opts->lit_table_bits ? opts->lit_table_bits : 9;
     int hist = opts && opts->history_kib ? opts->history_kib : 4;
     if (opts && (opts->group_parallel < 0 || opts->group_parallel > 2)) return CODAG_E_INVALID_ARGUMENT;

@@ -1,0 +1,71 @@
+"""The launch that a call selects by itself is not much slower than one that its
+options select, on inputs that it is not at its best with.  Times are the best of
+several, taken in turn; the bounds leave a wide margin."""
+import zlib
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2307_03760_amd as codag
+    codag.lib()
+    return torch.device("cuda:0")
+
+
+def _best(calls):
+    import torch
+    best = [float("inf")] * len(calls)
+    for _ in range(7):
+        for i, call in enumerate(calls):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            call()
+            a.record()
+            for _ in range(4):
+                call()
+            b.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b))
+    return best
+
+
+def _ratio(dev, codec, blobs, sizes, **other):
+    """Time by default over time with the options `other`."""
+    import torch
+    import paper_2307_03760_amd as codag
+    comp = torch.from_numpy(np.frombuffer(b"".join(blobs) + b"\0" * 64, np.uint8).copy()).to(dev)
+    co, oo = (torch.from_numpy(np.concatenate([[0], np.cumsum(k)]).astype(np.int64)).to(dev)
+              for k in ([len(b) for b in blobs], sizes))
+    out = torch.empty(int(sum(sizes)), dtype=torch.uint8, device=dev)
+    st = torch.zeros(len(blobs), dtype=torch.int32, device=dev)
+    own, theirs = _best([lambda: codag.decompress(codec, comp, co, out, oo, status=st),
+                         lambda: codag.decompress(codec, comp, co, out, oo, status=st, **other)])
+    assert not st.any()
+    return own / theirs
+
+
+def _deflate(data):
+    c = zlib.compressobj(6, zlib.DEFLATED, -15)
+    return c.compress(data) + c.flush()
+
+
+def _text(size, seed):
+    return workloads.zipf_text(size, np.random.default_rng(seed), workloads._vocab(0))
+
+
+def test_deflate_chunks_of_uneven_sizes(dev):
+    """One chunk in four long, in no order: workgroups of several waves would keep
+    the LDS of those that are done."""
+    data = [_text(65536 if k % 4 == 0 else 4096, k) for k in range(64)]
+    blobs, sizes = [_deflate(d) for d in data], [len(d) for d in data]
+    pick = np.random.default_rng(1).integers(0, 64, 10240)
+    assert _ratio(dev, oracle.DEFLATE, [blobs[k] for k in pick], [sizes[k] for k in pick], waves_per_block=1) < 1.15
