@@ -286,6 +286,8 @@ struct BitIn {
     __device__ __forceinline__ uint32_t peek(uint32_t n) const {
         return (uint32_t)(buf & ((1ull << n) - 1));
     }
+    // Bit position of the next unconsumed bit.
+    __device__ __forceinline__ uint32_t pos() const { return 8 * next - cnt; }
     // Byte position of the next unconsumed bit (on a byte boundary).
     __device__ __forceinline__ uint32_t byte_pos() const { return next - cnt / 8; }
 };
@@ -346,7 +348,7 @@ __device__ __forceinline__ int read_code_lengths(Ring &in, BitIn &bi, uint32_t *
     // before it -- is left to the loop below.
     for (uint32_t s = l; s < 320; s += kWave) lens[s] = 0;
     wave_sync();
-    uint32_t p = 8 * bi.next - bi.cnt;
+    uint32_t p = bi.pos();
     while (idx < total && p + 128 <= 8 * in.gend) {
         in.ensure((p >> 3) + 24);
         const uint32_t a = p + l;
@@ -554,9 +556,10 @@ __device__ __forceinline__ uint32_t walk_word(uint32_t info) {
     return (info & kTokStop) ? kWalkStop : ((info >> 8) & 63) + ((((info >> 16) & 511) + 12) << 8);
 }
 
+// Returns kMore once a batch ends at bit position `until` or past it.
 template <int TB, uint32_t H, class Ring>
 __device__ __forceinline__ int inflate_batched(Ring &in, BitIn &bi, LinearOut<H> &o,
-                                               DeflateLds<TB, H> *lds) {
+                                               DeflateLds<TB, H> *lds, uint32_t until) {
     const uint32_t l = lane();
     // Candidates are decoded for fixed 64-bit windows of the input (lane l:
     // the token at bit 64 w + l).  The walk's tokens are staged, as packed
@@ -565,7 +568,7 @@ __device__ __forceinline__ int inflate_batched(Ring &in, BitIn &bi, LinearOut<H>
     uint32_t *stage = reinterpret_cast<uint32_t *>(lds->lens);
     constexpr uint32_t kStageSpare = 64;  // 16 words no batch uses (at most 60 tokens)
     static_assert(sizeof(lds->lens) >= 4 * (kStageSpare + 16), "staging space");
-    uint32_t p = 8 * bi.next - bi.cnt;  // bit position of the next code
+    uint32_t p = bi.pos();  // bit position of the next code
     // Input words [cend - 64, cend), one per lane, read from the ring once
     // per 240 bytes or so; a window takes its four words out with readlane.
     uint32_t cache = 0, cend = 0;
@@ -768,9 +771,10 @@ __device__ __forceinline__ int inflate_batched(Ring &in, BitIn &bi, LinearOut<H>
             o.pos += bout;
             o.room -= bout;
         }
-        if (stop == 1) continue;
+        if (stop == 1 && p < until) continue;
         bi.seek(in, p >> 3);
         bi.skip(p & 7);
+        if (stop == 1) return kMore;
         if (stop == 2) return bi.remain < 0 ? CODAG_E_TRUNCATED : CODAG_OK;
         return kOneSymbol;
     }
@@ -949,14 +953,16 @@ __device__ __forceinline__ void emit_token(LaneToken<TB> &t, const LinearOut<H> 
     on = on && t.r < er && !bad;
 }
 
+// Returns kMore once a round ends at bit position `until` or past it, and where
+// the block is for the window-by-window decoder (windows).
 template <int TB, uint32_t H, class Ring>
 __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &o, DeflateLds<TB, H> *lds,
-                                             bool &windows) {
+                                             uint32_t until, bool &windows) {
     static_assert(Ring::kLdsWords <= kRoundInWords, "the round's input takes the ring's place");
     const uint32_t l = lane();
     uint8_t *const inb = reinterpret_cast<uint8_t *>(in.ring);
     const uint32_t endbit = 8 * in.gend;
-    uint32_t p = 8 * bi.next - bi.cnt;  // bit position of the next code
+    uint32_t p = bi.pos();  // bit position of the next code
     for (;;) {
         // Bits past the end read as zero; a block that goes on there is cut
         // off, whatever they decode to.
@@ -1054,12 +1060,12 @@ __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &
                 g0 += cnt;
             }
         }
-        if (!whyl && !poor) continue;
+        if (!whyl && !poor && p < until) continue;
         in.restart(p >> 3);
         bi.seek(in, p >> 3);
         bi.skip(p & 7);
         if (whyl == kWhyEob) return p > endbit ? CODAG_E_TRUNCATED : CODAG_OK;
-        windows = !whyl;
+        windows = !whyl && poor;
         return whyl ? kOneSymbol : kMore;
     }
 }
@@ -1073,7 +1079,7 @@ __device__ __forceinline__ int inflate_lanes(Ring &in, BitIn &bi, LinearOut<H> &
 template <int TB, uint32_t H, class Ring>
 __device__ __forceinline__ int inflate_leader(Ring &in, BitIn &bi, LinearOut<H> &o,
                                               DeflateLds<TB, H> *lds) {
-    uint32_t p = 8 * bi.next - bi.cnt;  // bit position of the next code
+    uint32_t p = bi.pos();  // bit position of the next code
     uint32_t *slot = reinterpret_cast<uint32_t *>(lds->lens);  // free while symbols decode
     for (;;) {
         const uint32_t wi = p >> 5;
@@ -1109,7 +1115,7 @@ __device__ __forceinline__ int inflate_leader(Ring &in, BitIn &bi, LinearOut<H> 
         bi.skip(p & 7);
         const int st = inflate_symbol<TB, H>(in, bi, o, lds);
         if (st != kMore) return st;
-        p = 8 * bi.next - bi.cnt;
+        p = bi.pos();
     }
 }
 
@@ -1223,25 +1229,56 @@ __device__ __forceinline__ int inflate_chunk(Ring &in, LinearOut<H> &o, DeflateL
     return o.pos == cap ? CODAG_OK : CODAG_E_UNDERFLOW;
 }
 
+// How long a Huffman block of a chunk is likely to be, in bits: the longer of
+// the two before it (a flush may leave an empty block between two others), or
+// what is left of the chunk.
+struct BlockLength {
+    uint32_t last = ~0u, before = ~0u;
+
+    __device__ __forceinline__ uint32_t expect(uint32_t rest) const {
+        return min(rest, last == ~0u ? ~0u : before == ~0u ? last : max(last, before));
+    }
+    __device__ __forceinline__ void ended(uint32_t bits) {
+        before = last;
+        last = bits;
+    }
+};
+
+// Blocks that are likely to be shorter than this are decoded window by window:
+// a round's passes take as long for a few lanes' input as for all.  One block
+// of text with its tables, window by window and in a round: 181 bytes 36 and
+// 49 us, 313 bytes 49 and 61, 399 bytes 56 and 49; of 4-byte integers, 316
+// bytes 37 and 67, 498 bytes 68 and 58.  Streams flushed every 100 bytes take
+// 3.5 ms per 64 KiB, 18.9 in rounds.  A block that goes on past this goes on
+// in rounds.
+constexpr uint32_t kShortBits = 3072;
+
 template <int TB, uint32_t H, int MODE = kAllLanes, class Ring>
 __device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t cap,
                                               DeflateLds<TB, H> *lds, uint32_t *made = nullptr) {
     LinearOut<H> o;
     o.init(out, cap, lds->window);
+    BlockLength blocks;
     return inflate_chunk<TB, H>(in, o, lds, made, [&](BitIn &bi) {
         if constexpr (MODE == kLeaderLane) {
             return inflate_leader<TB, H>(in, bi, o, lds);
         } else {
             int st;
-            bool windows = !Ring::kLaneRounds;
+            const uint32_t p0 = bi.pos();
+            uint32_t until = ~0u;  // window by window up to here
+            if constexpr (Ring::kLaneRounds)
+                until = blocks.expect(8 * in.gend - p0) < kShortBits ? p0 + kShortBits : 0u;
             do {
-                if constexpr (Ring::kLaneRounds)
-                    st = windows ? inflate_batched<TB, H>(in, bi, o, lds)
-                                 : inflate_lanes<TB, H>(in, bi, o, lds, windows);
-                else
-                    st = inflate_batched<TB, H>(in, bi, o, lds);
+                if (bi.pos() < until) {
+                    st = inflate_batched<TB, H>(in, bi, o, lds, until);
+                } else if constexpr (Ring::kLaneRounds) {
+                    bool windows = false;
+                    st = inflate_lanes<TB, H>(in, bi, o, lds, ~0u, windows);
+                    if (windows) until = ~0u;
+                }
                 if (st == kOneSymbol) st = inflate_symbol<TB, H>(in, bi, o, lds);
             } while (st == kMore);
+            blocks.ended(bi.pos() - p0);
             return st;
         }
     });

@@ -28,6 +28,11 @@
 namespace codag {
 
 constexpr uint32_t kTeamH = 32768;  // output window
+// Blocks likely to be shorter than this are wave 0's alone: they fit a round of
+// one wave, and a team's round has its input and its barriers besides (blocks
+// of 800 bytes of output 3.6 against 4.9 ms per 64 KiB; a chunk of 16,384 bits
+// is faster by the team, 89 us against 109).
+constexpr uint32_t kAloneBits = 8192;
 
 // Room for len <= kAppend more bytes, by the whole team (the same decision on
 // every wave).
@@ -407,14 +412,21 @@ static __device__ __forceinline__ int chunk(const uint8_t *chunk, uint32_t len, 
         }
         return CODAG_OK;
     }
+    BlockLength blocks;
     const int st = inflate_chunk<9, kTeamH>(in, o, &s->d, made, [&](BitIn &bi) {
         int r;
-        bool windows = false;
+        const uint32_t p0 = bi.pos(), expect = blocks.expect(8 * in.gend - p0);
+        // Window by window up to here, then in rounds of one wave, then the team's.
+        uint32_t until = expect < kShortBits ? p0 + kShortBits : 0u;
+        const uint32_t alone = expect < kAloneBits ? p0 + kAloneBits : 0u;
         do {
-            if (windows) {
-                r = inflate_batched<9, kTeamH>(in, bi, o, &s->d);
+            bool windows = false;
+            if (bi.pos() < until) {
+                r = inflate_batched<9, kTeamH>(in, bi, o, &s->d, until);
+            } else if (bi.pos() < alone) {
+                r = inflate_lanes<9, kTeamH>(in, bi, o, &s->d, alone, windows);
             } else {
-                uint32_t p = 8 * bi.next - bi.cnt;
+                uint32_t p = bi.pos();
                 if (lane() == 0) {
                     s->go = 1;
                     s->p = p;
@@ -431,8 +443,10 @@ static __device__ __forceinline__ int chunk(const uint8_t *chunk, uint32_t len, 
                 bi.seek(in, p >> 3);
                 bi.skip(p & 7);
             }
+            if (windows) until = ~0u;
             if (r == kOneSymbol) r = inflate_symbol<9, kTeamH>(in, bi, o, &s->d);
         } while (r == kMore);
+        blocks.ended(bi.pos() - p0);
         return r;
     });
     if (lane() == 0) s->go = 0;
@@ -451,7 +465,7 @@ __global__ void __launch_bounds__(kTeam * kWave) __attribute__((amdgpu_waves_per
     deflate_team(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff, uint32_t n,
                  int32_t *status, unsigned long long *err) {
     __shared__ __align__(16) typename Team<kTeam>::Lds s;
-    __shared__ __align__(16) uint32_t s_ring[DirectRing<512>::kLdsWords];
+    __shared__ __align__(16) uint32_t s_ring[kRoundInWords];
     const uint32_t wave = uni(threadIdx.x / kWave), c = blockIdx.x;
     if (c >= n) return;
     const uint64_t i0 = coff[c], i1 = coff[c + 1], o0 = ooff[c], o1 = ooff[c + 1];
@@ -755,8 +769,8 @@ __global__ void __launch_bounds__(kTeam * kWave) __attribute__((amdgpu_waves_per
     orc_frame_team(const uint8_t *framed, uint32_t block, uint8_t *out, uint64_t out_cap, const OrcFrame *frames,
                    OrcMeta *meta) {
     __shared__ __align__(16) typename std::conditional<Codec == CODAG_LZ4, LzTeamLds, typename Team<kTeam>::Lds>::type s;
-    __shared__ __align__(16) uint32_t s_ring[DirectRing<512>::kLdsWords];
-    static_assert(DirectRing<512>::kLdsWords >= LinearIn::kLdsWords, "wave 0's input");
+    __shared__ __align__(16) uint32_t s_ring[kRoundInWords];
+    static_assert(kRoundInWords >= LinearIn::kLdsWords, "wave 0's input");
     const uint32_t wave = uni(threadIdx.x / kWave);
     const uint32_t count = uni(meta->count), complete = uni(meta->complete);
     for (uint32_t f = blockIdx.x; f < count; f += gridDim.x) {

@@ -1,0 +1,65 @@
+"""GPU parity of Deflate blocks around the lengths at which the decoder changes:
+window by window, rounds of one wave, rounds of a team; alone in a chunk, after
+blocks of other lengths, with flushes in between, cut off and with too small an
+output."""
+import zlib
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from gpu_util import assert_parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2307_03760_amd as codag
+    codag.lib()
+    return torch.device("cuda:0")
+
+
+def _stream(data, cuts, flushes, level=6, strategy=zlib.Z_DEFAULT_STRATEGY):
+    c, out, a = zlib.compressobj(level, zlib.DEFLATED, -15, 8, strategy), [], 0
+    for k, n in enumerate(cuts):
+        out.append(c.compress(data[a:a + n]) + c.flush(flushes[k % len(flushes)]))
+        a += n
+    return b"".join(out) + c.compress(data[a:]) + c.flush()
+
+
+@pytest.mark.parametrize("strategy", [zlib.Z_DEFAULT_STRATEGY, zlib.Z_FIXED, zlib.Z_HUFFMAN_ONLY])
+def test_blocks_of_every_length(dev, strategy):
+    rng = np.random.default_rng(21)
+    vocab = workloads._vocab(0)
+    blobs, sizes = [], []
+
+    def add(data, cuts, flushes):
+        blobs.append(_stream(data, cuts, flushes, 6, strategy))
+        sizes.append(len(data))
+
+    for n in list(range(0, 40)) + list(range(300, 1000, 20)) + [1500, 2500, 4000]:
+        add(workloads.zipf_text(n, rng, vocab) if n else b"", [], [])
+    kinds = [zlib.Z_SYNC_FLUSH, zlib.Z_PARTIAL_FLUSH, zlib.Z_BLOCK, zlib.Z_FULL_FLUSH]
+    for per in (1, 10, 50, 200, 700, 900, 1200, 3000):
+        data = workloads.zipf_text(12 * per + 7, rng, vocab)
+        for f in kinds:
+            add(data, [per] * 12, [f])
+    for _ in range(12):  # short after long, long after short
+        cuts = [int(c) for c in rng.choice([5, 60, 400, 1100, 5000, 30000], 8)]
+        add(workloads.zipf_text(sum(cuts) + 100, rng, vocab), cuts, [kinds[int(rng.integers(4))], zlib.Z_SYNC_FLUSH])
+    add(bytes(70000), [], [])
+    for waves in (0, 1):  # teams where the launch is small, one wave a chunk
+        ch = workloads._pack([oracle.DEFLATE] * len(blobs), blobs, sizes)
+        assert (assert_parity(oracle.DEFLATE, ch, dev, waves_per_block=waves) == 0).all()
+    bad, caps = [], []
+    for b, n in zip(blobs[::3], sizes[::3]):
+        bad += [b[:len(b) // 2], b[:-1], b, b]
+        caps += [n, n, n // 2, n + 1]
+    for waves in (0, 1):
+        ch = workloads._pack([oracle.DEFLATE] * len(bad), bad, caps)
+        assert_parity(oracle.DEFLATE, ch, dev, waves_per_block=waves)

@@ -69,3 +69,15 @@ def test_deflate_chunks_of_uneven_sizes(dev):
     blobs, sizes = [_deflate(d) for d in data], [len(d) for d in data]
     pick = np.random.default_rng(1).integers(0, 64, 10240)
     assert _ratio(dev, oracle.DEFLATE, [blobs[k] for k in pick], [sizes[k] for k in pick], waves_per_block=1) < 1.15
+
+
+@pytest.mark.parametrize("n", [64, 600])
+def test_deflate_short_blocks(dev, n):
+    """Blocks of some 50 to 100 bytes, against the window-by-window decoder."""
+    blobs = []
+    for k in range(16):
+        c, data = zlib.compressobj(6, zlib.DEFLATED, -15), _text(16384, k)
+        blobs.append(b"".join(c.compress(data[i:i + 100]) + c.flush(zlib.Z_SYNC_FLUSH) for i in range(0, 16384, 100))
+                     + c.flush())
+    pick = np.random.default_rng(2).integers(0, 16, n)
+    assert _ratio(dev, oracle.DEFLATE, [blobs[k] for k in pick], [16384] * n, variant=2) < 1.5
