@@ -9,6 +9,7 @@ import pytest
 
 import oracle
 import workloads
+from deflate_bits import DIST_BASE, BitWriter, fixed_copy, fixed_litlen
 from gpu_util import assert_parity
 
 pytestmark = pytest.mark.gpu
@@ -63,3 +64,38 @@ def test_blocks_of_every_length(dev, strategy):
     for waves in (0, 1):
         ch = workloads._pack([oracle.DEFLATE] * len(bad), bad, caps)
         assert_parity(oracle.DEFLATE, ch, dev, waves_per_block=waves)
+
+
+@pytest.mark.parametrize("bits", [0, 9, 10])
+def test_every_symbol_of_the_fixed_code(dev, bits):
+    blobs, sizes = [], []
+    for end in [None, 286, 287, (257, 30), (257, 31)]:  # a good block; symbols that may not appear
+        for rounds in (1, 140):  # short, and long enough for the rounds
+            w = BitWriter()
+            w.put(1, 1)
+            w.put(1, 2)
+            n = 0
+            for _ in range(rounds):
+                for s in range(256):
+                    fixed_litlen(w, s)
+                n += 256
+            for length in range(3, 259):
+                fixed_copy(w, length, 1 + length % 256)
+                n += length
+            for d in DIST_BASE:
+                if d <= n:
+                    fixed_copy(w, 3, d)
+                    n += 3
+            if end is None:
+                fixed_litlen(w, 256)
+            elif isinstance(end, int):
+                fixed_litlen(w, end)
+            else:
+                fixed_litlen(w, end[0])
+                w.put_code(end[1], 5)
+            w.put(0, 40)
+            blobs.append(w.getvalue())
+            sizes.append(n)
+    ch = workloads._pack([oracle.DEFLATE] * len(blobs), blobs, sizes)
+    st = assert_parity(oracle.DEFLATE, ch, dev, lit_table_bits=bits)
+    assert (st[:2] == 0).all() and (st[2:] == oracle.E_CORRUPT).all()
