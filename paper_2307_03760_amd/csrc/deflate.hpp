@@ -596,7 +596,7 @@ __device__ __forceinline__ int inflate_batched(Ring &in, BitIn &bi, LinearOut<H>
     uint32_t cur = 0, walk = 0;  // packed token and walk word of this lane's candidate in window wk
     bool have = false;
     for (;;) {
-        o.make_room(kBatchOut);
+        o.make_room(kBatchOut, H / 2);
         // ---- collect a batch of tokens
         uint32_t ntok = 0;
         uint32_t stop = 0;  // 1 full, 2 end of block, 3 one symbol the slow way
