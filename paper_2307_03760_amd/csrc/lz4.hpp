@@ -98,16 +98,23 @@ __device__ __forceinline__ void lz4_end(LinearOut<H> &o, const Lz4Lds<H> *lds, L
     s.made = s.nq = 0;
 }
 
-// Adds continuation bytes from position q on to len (a nibble was 15):
-// returns the position after the last one, or 0 if the chunk ends first.
+// Adds continuation bytes from position q on to len (a nibble was 15), 64 at a
+// time: returns the position after the last one, or 0 if the chunk ends first.
+// (One at a time the 257 of a 64 KiB field took 20 us.)
 __device__ __forceinline__ uint32_t lz4_more(LinearIn &in, uint32_t q, uint32_t end, uint32_t &len) {
     for (;;) {
         if (q >= end) return 0;
-        const uint32_t b = in.peek4(q++) & 255;
+        in.ensure(q, kWave);
+        const uint32_t b = in.at(q)[lane()];
+        const uint64_t m = ballot(b != 255);
+        const uint32_t full = m ? (uint32_t)__builtin_ctzll(m) : (uint32_t)kWave;
+        if (full >= end - q) return 0;  // (bytes past the end are not 255)
         // A run over 2^32 cannot fit any output range; saturate instead of
         // wrapping so the range check still fails.
-        len = len + b < len ? 0xffffffffu : len + b;
-        if (b != 255) return q;
+        const uint32_t more = 255 * full + (m ? readlane(b, full) : 0u);
+        len = len + more < len ? 0xffffffffu : len + more;
+        if (m) return q + full + 1;
+        q += kWave;
     }
 }
 
