@@ -68,7 +68,9 @@ enum {
  *                     launches of at most 1024, and ORC streams of as many,
  *                     that set none of waves_per_block, lit_table_bits,
  *                     history_kib and chunk_ticks are decoded by a workgroup
- *                     of 8 or 16 waves per chunk with a 32 KiB window.
+ *                     of 8 or 16 waves per chunk with a 32 KiB window (LZ4
+ *                     launches of more than 256 chunks by 256 workgroups,
+ *                     each taking up to 4 chunks in turn).
  *   chunk_ticks       optional device array (n_chunks uint64): receives each
  *                     chunk's decode time in shader clock cycles.
  *   group_parallel    RLE codecs: 0 = automatic (RLE v1 launches of at

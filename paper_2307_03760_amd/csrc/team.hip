@@ -494,12 +494,12 @@ int launch_deflate_team(const uint8_t *comp, const uint64_t *coff, uint8_t *out,
 // LDS give where 64 sequences end, one read per 64 follows the real chain, and
 // each thread finds and parses one of its sequences.  A prefix sum places
 // them; literals go to the window and matches to the copy queue.  What the
-// parse leaves out (longer fields, the last sequence, every error) is one
-// general step of wave 0.
+// parse leaves out (longer fields, the last sequence, every error) is a
+// general step of wave 0; blocks with little else are set aside for one wave.
 //
 // Measured against one wave per block: 97 ORC blocks of 64 KiB 1,028 to 246 us,
 // one block of 64 KiB 840 to 174, 256 chunks 968 to 220, 1,024 chunks 1,025 to
-// 807; two teams fit neither a CU's LDS nor its waves, so from some 1,300
+// 690; two teams fit neither a CU's LDS nor its waves, so from some 1,300
 // chunks on a wave each is faster.  Of a text window's 40,000 cycles the
 // copies take 18,000, the links 6,600, finding the sequences 7,700.
 constexpr uint32_t kLzTeam = 16, kLzThreads = kLzTeam * kWave;
@@ -511,6 +511,82 @@ constexpr uint32_t kLzMatch = 1024;           // longest match of a parsed seque
 // has to be in HBM (see LinearOut).
 constexpr uint32_t kLzMost = LinearOut<kTeamH>::kAppend - (kLzMatch - 512);
 
+// Workgroups of a launch, one a CU: they take more blocks than that in turn.
+constexpr uint32_t kLzGrid = 256, kLzGroup = kLzTeamMaxChunks / kLzGrid;
+
+// Which blocks a workgroup of a launch of n takes: with more than one each, the
+// blocks in order of what they are likely to cost (cost(i) of block i, from its
+// lengths, to a quarter of an octave) are dealt out forth and back.  Every
+// workgroup finds the same order, by counting, in about 1 us.  1,024 blocks of
+// log-normal sizes take 1,143 us, 1,335 with a workgroup each as CUs come free
+// and 1,844 with every 256th block; 300 ORC blocks of 64 KiB 324, 479 and 542.
+struct LzDeal {
+    uint32_t count[kLzTeam][kWave];  // blocks of each class, by the wave that looked at them
+    uint32_t mine[kLzGroup];
+};
+template <class Cost>
+__device__ __forceinline__ uint32_t lz_deal(LzDeal *s, uint32_t n, uint32_t b, Cost cost) {
+    static_assert(kLzTeamMaxChunks <= kLzThreads, "a thread a block");
+    const uint32_t t = threadIdx.x, wave = uni(t / kWave), l = lane();
+    if (n <= kLzGrid) {  // (a stream's chunks may be fewer than its capacity's)
+        if (t == 0) s->mine[0] = b;
+        __syncthreads();
+        return 1;
+    }
+    // Class 0 is the costliest (2^23 and more), 63 the cheapest (below 320).
+    const uint32_t v = max(t < n ? cost(t) : 0u, 256u), e = 31 - (uint32_t)__builtin_clz(v);
+    const uint32_t cls = 95 - min(4 * e + ((v >> (e - 2)) & 3), 95u);
+    uint64_t same = ballot(t < n);  // lanes of this one's class
+#pragma unroll
+    for (uint32_t i = 0; i < 6; i++) {
+        const uint64_t m = ballot((cls >> i) & 1);
+        same &= (cls >> i) & 1 ? m : ~m;
+    }
+    s->count[wave][l] = 0;
+    __syncthreads();
+    const uint32_t earlier = count_below(same);
+    if (t < n && earlier == 0) s->count[wave][cls] = (uint32_t)__builtin_popcountll(same);
+    __syncthreads();
+    // Lane l: blocks of class l in all waves and in those before this one.
+    uint32_t all = 0, before = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kLzTeam; w++) {
+        const uint32_t c = s->count[w][l];
+        all += c;
+        before += w < wave ? c : 0u;
+    }
+    const uint32_t rank = lane_pull(wave_inclusive_sum32(all) - all + before, cls) + earlier;
+    // Rank r goes to workgroup r mod 256 in even turns, 255 minus that in odd ones.
+    const uint32_t turn = rank / kLzGrid, at = rank % kLzGrid;
+    if (t < n && (turn & 1 ? kLzGrid - 1 - at : at) == b) s->mine[turn] = t;
+    __syncthreads();
+    const uint32_t turns = n / kLzGrid, rest = n % kLzGrid;
+    return turns + ((turns & 1 ? kLzGrid - 1 - b : b) < rest ? 1 : 0);
+}
+// A block that hardly compressed is literals mostly.
+__device__ __forceinline__ uint32_t lz_cost(uint32_t in, uint32_t out) {
+    return in + in / 16 < out ? in : in / 16;
+}
+
+// Blocks that a team is no better at than one wave are set aside, and when the
+// workgroup is done with the others its waves decode one each, side by side:
+// blocks of at most kLzTiny compressed bytes, and those whose general steps
+// would take the team longer than its share of the waves takes for everything,
+// by the costs below (hundreds of cycles).  Literal runs of 300 to 2,000 bytes,
+// 64 blocks 147 us (484 with every run a turn of the team, 133 by a wave each in
+// a launch of their own), 1,024 blocks 231 (1,872; 159); 1,024 blocks of 200
+// bytes 18.5 (50; 14.4).
+constexpr uint32_t kLzTiny = 256;
+constexpr uint32_t kLzTurnCost = 130, kLzLinkCost = 100;  // a turn of a team's loop; a window's links
+constexpr uint32_t kLzFastCost = 2, kLzSlowCost = 30;     // a sequence by one wave: parsed by a lane, or general (18 bytes and more on average)
+constexpr uint32_t kLzHuge = 8192;  // fields this long are wave 0's work for longer than all of these
+enum : int { kLzAside = 2 };        // not a status
+
+struct LzAloneLds {
+    Lz4Lds<4096> d;
+    uint32_t in[LinearIn::kLdsWords];
+};
+
 struct LzTeamLds {
     Lz4Lds<kTeamH> d;  // the window; wave 0's queue
     uint32_t buf[2][4 * kLzPieces];
@@ -520,6 +596,12 @@ struct LzTeamLds {
     uint32_t unit[kLzTeam + 2], units, chain_end;
     uint32_t sum[kLzTeam], first[kLzTeam], made, next;
     uint32_t st, p, pos, wlo, fa, room;  // wave 0's general step
+};
+
+// A workgroup's LDS: a team's, then that of the waves with a block each.
+union LzLds {
+    LzTeamLds t;
+    LzAloneLds a[kLzGroup];
 };
 
 struct LzSeq {
@@ -554,9 +636,22 @@ __device__ __forceinline__ LzSeq lz_parse(const uint8_t *bytes, uint32_t x, uint
     return q;
 }
 
-// One block by the workgroup; the same status on every wave.
+// Whether the general sequence at p has a field of kLzHuge bytes or more.
+__device__ __forceinline__ bool lz_huge(LinearIn &in, uint32_t p, uint32_t end) {
+    const uint32_t tok = in.peek4(p) & 255;
+    uint32_t lit = tok >> 4, mlen = tok & 15, q = p + 1;
+    if (lit == 15) q = lz4_more(in, q, end, lit);
+    if (!q || lit >= kLzHuge || lit > end - q) return q != 0 && lit >= kLzHuge;
+    q += lit + 2;
+    return mlen == 15 && q < end && lz4_more(in, q, end, mlen) && mlen >= kLzHuge;
+}
+
+// One block by the workgroup; the same status on every wave.  kLzAside: it is
+// for one wave, from its start (`group` blocks, at most, are the workgroup's).
 __device__ __forceinline__ int lz_team_chunk(const uint8_t *chunk, uint32_t len, uint8_t *out, uint32_t cap,
-                                             uint32_t *made_out, LzTeamLds *s, uint32_t *lin, uint32_t wave) {
+                                             uint32_t *made_out, LzTeamLds *s, uint32_t *lin, uint32_t wave,
+                                             uint32_t group) {
+    if (len <= kLzTiny) return kLzAside;
     const uint32_t l = lane(), tid = wave * kWave + l;
     LinearOut<kTeamH> o;
     o.init(out, cap, s->d.window);
@@ -570,6 +665,8 @@ __device__ __forceinline__ int lz_team_chunk(const uint8_t *chunk, uint32_t len,
     const uint32_t end = in.gend;
     uint32_t p = in.skip;
     uint32_t cur = ~0u, nxt = ~0u;  // the window in use, and one in (or on its way to) the other buffer
+    uint32_t turns = 0, linked = 0;    // turns of the loop, windows linked
+    uint32_t general = 0, alone = 0;   // general steps (wave 0's count); what one wave would have taken for the rest
     int st = CODAG_OK;
     auto issue = [&](uint32_t w) {
         const uint32_t at = w * kLzStep + 16 * tid;
@@ -582,37 +679,41 @@ __device__ __forceinline__ int lz_team_chunk(const uint8_t *chunk, uint32_t len,
             break;
         }
         const uint32_t w = p / kLzStep, W = w * kLzStep, room = end - W;
-        if (w != cur && w != nxt) {
-            wait_vm();  // a window not wanted any more may be landing
-            issue(w);
-        }
-        cur = w;
-        if (wave < (kLzPieces + kWave - 1) / kWave) wait_vm();
-        __syncthreads();
-        if (W + kLzStep < end && nxt != w + 1) {
-            issue(w + 1);
-            nxt = w + 1;
-        }
         const uint8_t *const bytes = reinterpret_cast<const uint8_t *>(s->buf[w & 1]);
-        // Links; a position whose sequence no thread can take links to itself.
-        uint32_t to[3];
-#pragma unroll
-        for (uint32_t i = 0; i < 3; i++) {
-            const uint32_t x = tid + kLzThreads * i;
-            const LzSeq q = lz_parse(bytes, x, room);
-            to[i] = q.ok && x < room ? q.next : x;
-            s->link[0][x] = (uint16_t)to[i];
-        }
-        __syncthreads();
-#pragma unroll
-        for (uint32_t k = 1; k < kLzLevels; k++) {
+        turns++;
+        if (w != cur) {  // (after a general step the window and its links may still be there)
+            if (w != nxt) {
+                wait_vm();  // a window not wanted any more may be landing
+                issue(w);
+            }
+            cur = w;
+            linked++;
+            if (wave < (kLzPieces + kWave - 1) / kWave) wait_vm();
+            __syncthreads();
+            if (W + kLzStep < end && nxt != w + 1) {
+                issue(w + 1);
+                nxt = w + 1;
+            }
+            // Links; a position whose sequence no thread can take links to itself.
+            uint32_t to[3];
 #pragma unroll
             for (uint32_t i = 0; i < 3; i++) {
-                const uint32_t f = s->link[k - 1][min(to[i], kLzStep - 1)];
-                if (to[i] < kLzStep) to[i] = f;
-                s->link[k][tid + kLzThreads * i] = (uint16_t)to[i];
+                const uint32_t x = tid + kLzThreads * i;
+                const LzSeq q = lz_parse(bytes, x, room);
+                to[i] = q.ok && x < room ? q.next : x;
+                s->link[0][x] = (uint16_t)to[i];
             }
             __syncthreads();
+#pragma unroll
+            for (uint32_t k = 1; k < kLzLevels; k++) {
+#pragma unroll
+                for (uint32_t i = 0; i < 3; i++) {
+                    const uint32_t f = s->link[k - 1][min(to[i], kLzStep - 1)];
+                    if (to[i] < kLzStep) to[i] = f;
+                    s->link[k][tid + kLzThreads * i] = (uint16_t)to[i];
+                }
+                __syncthreads();
+            }
         }
         // The chain, 64 sequences a step.
         if (wave == 0) {
@@ -696,16 +797,28 @@ __device__ __forceinline__ int lz_team_chunk(const uint8_t *chunk, uint32_t len,
             g = g1;
         }
         __syncthreads();
+        const uint32_t from = p;
         p = uni(s->next);
+        alone += cnt * (p - from >= 18 * cnt ? kLzSlowCost : kLzFastCost);
         if (p >= W + kLzStep) continue;
-        // The general step at p.
+        // General steps from p on: one, and more while literal runs that no
+        // thread parses follow.
         if (wave == 0) {
             int r = CODAG_E_TRUNCATED;  // p >= end
             if (p < end) {
+                const uint32_t team = kLzTurnCost * turns + kLzLinkCost * linked;
                 Lz4Step step;
                 step.most = 2560;
                 lz4_begin(o, step);
-                r = lz4_sequence<kTeamH>(in, o, &s->d, step, p, end, cap);
+                do {
+                    if ((general >= 4 && team > (alone + kLzSlowCost * general) / group) ||
+                        (group > 1 && lz_huge(in, p, end))) {
+                        r = kLzAside;
+                        break;
+                    }
+                    r = lz4_sequence<kTeamH>(in, o, &s->d, step, p, end, cap);
+                    general++;
+                } while (r == kLz4More && p < end && (in.peek4(p) & 0xfff0) == 0xfff0);
                 lz4_end(o, &s->d, step);
             }
             wait_vm();  // what it wrote out is there for the others
@@ -741,43 +854,96 @@ __device__ __forceinline__ int lz_team_chunk(const uint8_t *chunk, uint32_t len,
     return o.pos == cap ? CODAG_OK : CODAG_E_UNDERFLOW;
 }
 
+// A block set aside, by the calling wave.
+__device__ __forceinline__ int lz_alone(const uint8_t *chunk, uint32_t len, uint8_t *out, uint32_t cap, uint32_t *made,
+                                        LzAloneLds *s) {
+    LinearIn in;
+    in.init(chunk, len, s->in, nullptr);
+    return decode_lz4<4096>(in, out, cap, &s->d, made);
+}
+
+// Grouped: launches of more blocks than workgroups.
+template <bool Grouped>
 __global__ void __launch_bounds__(kLzThreads) __attribute__((amdgpu_waves_per_eu(4)))
     lz4_team(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff, uint32_t n,
              int32_t *status, unsigned long long *err) {
-    __shared__ __align__(16) LzTeamLds s;
+    __shared__ __align__(16) LzLds s;
     __shared__ __align__(16) uint32_t s_lin[LinearIn::kLdsWords];
-    const uint32_t wave = uni(threadIdx.x / kWave), c = blockIdx.x;
-    if (c >= n) return;
-    const uint64_t i0 = coff[c], i1 = coff[c + 1], o0 = ooff[c], o1 = ooff[c + 1];
-    int st = CODAG_E_INVALID_ARGUMENT;
-    if ((((i1 - i0) | (o1 - o0)) >> 31) == 0)
-        st = lz_team_chunk(comp + i0, (uint32_t)(i1 - i0), out + o0, (uint32_t)(o1 - o0), nullptr, &s, s_lin, wave);
-    if (wave == 0) report(c, st, status, err);
+    __shared__ LzDeal s_deal;
+    const uint32_t wave = uni(threadIdx.x / kWave);
+    if (blockIdx.x >= n) return;
+    uint32_t group = 1;
+    if constexpr (Grouped)
+        group = lz_deal(&s_deal, n, blockIdx.x, [&](uint32_t i) {
+            return lz_cost((uint32_t)min(coff[i + 1] - coff[i], (uint64_t)1 << 31),
+                           (uint32_t)min(ooff[i + 1] - ooff[i], (uint64_t)1 << 31));
+        });
+    uint32_t aside = 0;  // a bit per block set aside
+    for (uint32_t k = 0; k < group; k++) {
+        const uint32_t c = Grouped ? uni(s_deal.mine[k]) : blockIdx.x;
+        const uint64_t i0 = coff[c], i1 = coff[c + 1], o0 = ooff[c], o1 = ooff[c + 1];
+        int st = CODAG_E_INVALID_ARGUMENT;
+        if ((((i1 - i0) | (o1 - o0)) >> 31) == 0)
+            st = lz_team_chunk(comp + i0, (uint32_t)(i1 - i0), out + o0, (uint32_t)(o1 - o0), nullptr, &s.t, s_lin, wave,
+                               group);
+        if (st == kLzAside) aside |= 1u << k;
+        else if (wave == 0) report(c, st, status, err);
+    }
+    if (!aside) return;
+    __syncthreads();  // the team's LDS is done with
+    if (wave < kLzGroup && ((aside >> wave) & 1)) {
+        const uint32_t c = Grouped ? uni(s_deal.mine[wave]) : blockIdx.x;
+        const uint64_t i0 = coff[c], o0 = ooff[c];
+        report(c, lz_alone(comp + i0, (uint32_t)(coff[c + 1] - i0), out + o0, (uint32_t)(ooff[c + 1] - o0), nullptr,
+                           &s.a[wave]), status, err);
+    }
 }
 
 int launch_lz4_team(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff, uint32_t n,
                     int32_t *status, unsigned long long *err, hipStream_t s) {
-    hipLaunchKernelGGL(lz4_team, dim3(n), dim3(kLzThreads), 0, s, comp, coff, out, ooff, n, status, err);
+    static_assert(kLzGrid * kLzGroup >= kLzTeamMaxChunks && kLzGroup <= kLzTeam, "a wave for every block set aside");
+    if (n <= kLzGrid)
+        hipLaunchKernelGGL(lz4_team<false>, dim3(n), dim3(kLzThreads), 0, s, comp, coff, out, ooff, n, status, err);
+    else
+        hipLaunchKernelGGL(lz4_team<true>, dim3(kLzGrid), dim3(kLzThreads), 0, s, comp, coff, out, ooff, n, status, err);
     return hipGetLastError() == hipSuccess ? CODAG_OK : CODAG_E_HIP;
 }
 
 // ---- compressed ORC streams
 
 // ORC chunk f into out + f * block, as orc_frame_decode with a team per chunk.
-template <int Codec, uint32_t kTeam>
+// (Grouped: LZ4 streams that may have more chunks than a launch has workgroups.)
+template <int Codec, uint32_t kTeam, bool Grouped = false>
 __global__ void __launch_bounds__(kTeam * kWave) __attribute__((amdgpu_waves_per_eu(4)))
     orc_frame_team(const uint8_t *framed, uint32_t block, uint8_t *out, uint64_t out_cap, const OrcFrame *frames,
                    OrcMeta *meta) {
-    __shared__ __align__(16) typename std::conditional<Codec == CODAG_LZ4, LzTeamLds, typename Team<kTeam>::Lds>::type s;
+    __shared__ __align__(16) typename std::conditional<Codec == CODAG_LZ4, LzLds, typename Team<kTeam>::Lds>::type s;
     __shared__ __align__(16) uint32_t s_ring[kRoundInWords];
     static_assert(kRoundInWords >= LinearIn::kLdsWords, "wave 0's input");
     const uint32_t wave = uni(threadIdx.x / kWave);
     const uint32_t count = uni(meta->count), complete = uni(meta->complete);
-    for (uint32_t f = blockIdx.x; f < count; f += gridDim.x) {
+    if (blockIdx.x >= count) return;
+    __shared__ LzDeal s_deal;
+    uint32_t group = 1;
+    if constexpr (Grouped)
+        group = lz_deal(&s_deal, count, blockIdx.x, [&](uint32_t i) {
+            return frames[i].original ? frames[i].len / 64 : lz_cost(frames[i].len, block);
+        });
+    auto room_of = [&](uint32_t f) {
+        const uint64_t at = (uint64_t)f * block;
+        return at >= out_cap ? 0u : (uint32_t)min((uint64_t)block, out_cap - at);
+    };
+    auto done = [&](uint32_t f, int st, uint32_t made) {  // by one lane
+        const bool last = f + 1 == count && complete;     // the chunk that ends the stream
+        if (st == CODAG_OK && !last && made != block) st = made < block ? CODAG_E_UNDERFLOW : CODAG_E_OVERFLOW;
+        if (st != CODAG_OK) atomicMin(&meta->key, (unsigned long long)error_key(f, st));
+        else if (last) meta->last = made;
+    };
+    uint32_t aside = 0;  // a bit per LZ4 block set aside
+    for (uint32_t k = 0; k < group; k++) {
+        const uint32_t f = Grouped ? uni(s_deal.mine[k]) : blockIdx.x;
         const uint64_t at = (uint64_t)f * block, src = uni64(frames[f].src);
-        const uint32_t len = uni(frames[f].len), original = uni(frames[f].original);
-        const bool last = f + 1 == count && complete;  // the chunk that ends the stream
-        const uint32_t room = at >= out_cap ? 0u : (uint32_t)min((uint64_t)block, out_cap - at);
+        const uint32_t len = uni(frames[f].len), original = uni(frames[f].original), room = room_of(f);
         int st = CODAG_OK;
         uint32_t made = 0;
         if (original) {
@@ -792,23 +958,34 @@ __global__ void __launch_bounds__(kTeam * kWave) __attribute__((amdgpu_waves_per
             st = CODAG_E_INVALID_ARGUMENT;
         } else {
             if constexpr (Codec == CODAG_LZ4)
-                st = lz_team_chunk(framed + src, len, out + at, room, &made, &s, s_ring, wave);
+                st = lz_team_chunk(framed + src, len, out + at, room, &made, &s.t, s_ring, wave, group);
             else
                 st = Team<kTeam>::chunk(framed + src, len, out + at, room, &made, &s, s_ring, wave);
         }
-        if (st == CODAG_OK && !last && made != block) st = made < block ? CODAG_E_UNDERFLOW : CODAG_E_OVERFLOW;
-        if (threadIdx.x == 0) {
-            if (st != CODAG_OK) atomicMin(&meta->key, (unsigned long long)error_key(f, st));
-            else if (last) meta->last = made;
+        if (Codec == CODAG_LZ4 && st == kLzAside) aside |= 1u << k;
+        else if (threadIdx.x == 0) done(f, st, made);
+    }
+    if constexpr (Codec == CODAG_LZ4) {
+        if (!aside) return;
+        __syncthreads();  // the team's LDS is done with
+        if (wave < kLzGroup && ((aside >> wave) & 1)) {
+            const uint32_t f = Grouped ? uni(s_deal.mine[wave]) : blockIdx.x;
+            uint32_t made = 0;
+            const int st = lz_alone(framed + uni64(frames[f].src), uni(frames[f].len), out + (uint64_t)f * block,
+                                    room_of(f), &made, &s.a[wave]);
+            if (lane() == 0) done(f, st, made);
         }
     }
 }
 
 void launch_orc_frame_team(int codec, const uint8_t *framed, uint32_t block, uint8_t *out, uint64_t out_cap,
                            const OrcFrame *frames, uint32_t max_frames, OrcMeta *meta, hipStream_t s) {
-    if (codec == CODAG_LZ4)
+    if (codec == CODAG_LZ4 && max_frames <= kLzGrid)
         hipLaunchKernelGGL((orc_frame_team<CODAG_LZ4, kLzTeam>), dim3(max_frames), dim3(kLzThreads), 0, s, framed, block,
                            out, out_cap, frames, meta);
+    else if (codec == CODAG_LZ4)
+        hipLaunchKernelGGL((orc_frame_team<CODAG_LZ4, kLzTeam, true>), dim3(kLzGrid), dim3(kLzThreads), 0, s, framed,
+                           block, out, out_cap, frames, meta);
     else if (max_frames <= kBigTeamMaxChunks)
         hipLaunchKernelGGL((orc_frame_team<CODAG_DEFLATE, 16>), dim3(max_frames), dim3(16 * kWave), 0, s, framed, block,
                            out, out_cap, frames, meta);

@@ -81,3 +81,29 @@ def test_deflate_short_blocks(dev, n):
                      + c.flush())
     pick = np.random.default_rng(2).integers(0, 16, n)
     assert _ratio(dev, oracle.DEFLATE, [blobs[k] for k in pick], [16384] * n, variant=2) < 1.5
+
+
+def _lz4_long_runs(seed):
+    """Literal runs of 300 to 2,000 bytes between short matches."""
+    rng, out, n = np.random.default_rng(seed), [], 0
+    while n < 64000:
+        k, m = int(rng.integers(300, 2001)), int(rng.integers(4, 18))
+        off = int(rng.integers(1, min(n + k, 60000) + 1))
+        out.append(bytes([0xF0 | (m - 4)]) + b"\xff" * ((k - 15) // 255) + bytes([(k - 15) % 255]) + rng.bytes(k)
+                   + off.to_bytes(2, "little"))
+        n += k + m
+    return b"".join(out) + b"\x50tails", n + 5
+
+
+@pytest.mark.parametrize("n", [64, 300, 1024])
+def test_lz4_long_literal_runs(dev, n):
+    blobs, sizes = zip(*[_lz4_long_runs(k) for k in range(16)])
+    pick = np.random.default_rng(3).integers(0, 16, n)
+    assert _ratio(dev, oracle.LZ4, [blobs[k] for k in pick], [sizes[k] for k in pick], waves_per_block=1) < 2
+
+
+@pytest.mark.parametrize("size", [200, 4096])
+def test_lz4_small_blocks(dev, size):
+    blobs = [workloads.lz4_block(_text(size, k)) for k in range(16)]
+    pick = np.random.default_rng(4).integers(0, 16, 1024)
+    assert _ratio(dev, oracle.LZ4, [blobs[k] for k in pick], [size] * 1024, waves_per_block=1) < 2
