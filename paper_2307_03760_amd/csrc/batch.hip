@@ -24,27 +24,43 @@
 
 namespace codag {
 
-__global__ void reset_queue(uint32_t *head) {
-    if (threadIdx.x == 0) *head = 0;
+// head[0]: the queue's next position; head[1]: the launch has RLE chunks only.
+constexpr uint32_t kResetThreads = 1024;
+__global__ void __launch_bounds__(kResetThreads) reset_queue(uint32_t *head, const uint8_t *codecs, uint32_t n) {
+    __shared__ uint32_t s_lz77;
+    const uint32_t t = threadIdx.x;
+    if (t == 0) s_lz77 = 0;
+    __syncthreads();
+    bool lz77 = false;
+    auto is_lz77 = [](uint32_t c) { return c == CODAG_DEFLATE || c == CODAG_LZ4; };
+    for (uint64_t i = 16 * t; i + 16 <= n; i += 16 * kResetThreads) {
+        const u128_any v = *reinterpret_cast<const u128_any *>(codecs + i);
+#pragma unroll
+        for (uint32_t k = 0; k < 16; k++) lz77 = lz77 || is_lz77((v[k / 4] >> (8 * (k & 3))) & 255);
+    }
+    const uint32_t tail = (n & ~15u) + t;
+    if (t < 16 && tail < n) lz77 = lz77 || is_lz77(codecs[tail]);
+    if (ballot(lz77) && lane() == 0) s_lz77 = 1;  // the same value from every wave
+    __syncthreads();
+    if (t == 0) {
+        head[0] = 0;
+        head[1] = s_lz77 ? 0 : 1;
+    }
 }
 
 // One input buffer for every codec's ring.
 constexpr uint32_t kBatchRingWords = kRingLdsWords > kRoundInWords ? kRingLdsWords : kRoundInWords;
 
-// Each wave claims `claim` consecutive queue positions at a time (one
-// atomic add for several small chunks) until the queue is empty.  Every
-// store of a per-chunk result is made by all lanes with the same value (a
-// one-lane branch inside this loop would make the compiler treat the loop
-// as divergent).
-template <int TB, uint32_t H, int WPB>
-__global__ void __launch_bounds__(kWave * WPB)
-    decode_batch(const uint8_t *codecs, const uint8_t *comp, const uint64_t *coff, uint8_t *out,
-                 const uint64_t *ooff, uint32_t n, const uint32_t *order, uint32_t *head,
-                 uint32_t claim, int32_t *status, unsigned long long *err, uint64_t *ticks) {
-    __shared__ __align__(16) uint32_t s_ring[WPB][kBatchRingWords];
-    __shared__ __align__(16) uint32_t s_land[WPB][kLandWords];
-    __shared__ __align__(16) WaveScratch<CODAG_DEFLATE, TB, H> s_scratch[WPB];
-    const uint32_t wave = uni(threadIdx.x / kWave);
+// One wave's share of a batch.  Each wave claims `claim` consecutive queue
+// positions at a time (one atomic add for several small chunks) until the queue
+// is empty.  Every store of a per-chunk result is made by all lanes with the
+// same value (a one-lane branch inside this loop would make the compiler treat
+// the loop as divergent).  RleOnly: the launch has no Deflate or LZ4 chunk.
+template <bool RleOnly, int TB, uint32_t H>
+__device__ __forceinline__ void batch_wave(const uint8_t *codecs, const uint8_t *comp, const uint64_t *coff, uint8_t *out,
+                                           const uint64_t *ooff, uint32_t n, const uint32_t *order, uint32_t *head,
+                                           uint32_t claim, int32_t *status, unsigned long long *err, uint64_t *ticks,
+                                           uint32_t *ring, uint32_t *land, WaveScratch<CODAG_DEFLATE, TB, H> *scratch) {
     uint32_t idx = 0, last = 0;
     for (;;) {
         if (idx == last) {
@@ -62,29 +78,56 @@ __global__ void __launch_bounds__(kWave * WPB)
         }
         uint32_t codec = uni((uint32_t)codecs[c]);
         uint64_t t0 = __builtin_amdgcn_s_memtime();
-        int st;
-        if (codec == CODAG_RLE_V1)
-            st = decode_one<CODAG_RLE_V1, TB, H>(
-                comp, coff, out, ooff, c, s_ring[wave], s_land[wave],
-                reinterpret_cast<WaveScratch<CODAG_RLE_V1, TB, H> *>(&s_scratch[wave]));
-        else if (codec == CODAG_RLE_V2)
-            st = decode_one<CODAG_RLE_V2, TB, H>(
-                comp, coff, out, ooff, c, s_ring[wave], s_land[wave],
-                reinterpret_cast<WaveScratch<CODAG_RLE_V2, TB, H> *>(&s_scratch[wave]));
-        else if (codec == CODAG_DEFLATE)
-            st = decode_one<CODAG_DEFLATE, TB, H>(comp, coff, out, ooff, c, s_ring[wave],
-                                                  s_land[wave], &s_scratch[wave]);
-        else if (codec == CODAG_LZ4)
-            st = decode_one<CODAG_LZ4, TB, H>(
-                comp, coff, out, ooff, c, s_ring[wave], s_land[wave],
-                reinterpret_cast<WaveScratch<CODAG_LZ4, TB, H> *>(&s_scratch[wave]));
-        else
-            st = CODAG_E_INVALID_ARGUMENT;
+        int st = CODAG_E_INVALID_ARGUMENT;
+        if (codec == CODAG_RLE_V1) {
+            st = decode_one<CODAG_RLE_V1, TB, H>(comp, coff, out, ooff, c, ring, land,
+                                                 reinterpret_cast<WaveScratch<CODAG_RLE_V1, TB, H> *>(scratch));
+        } else if (codec == CODAG_RLE_V2) {
+            st = decode_one<CODAG_RLE_V2, TB, H>(comp, coff, out, ooff, c, ring, land,
+                                                 reinterpret_cast<WaveScratch<CODAG_RLE_V2, TB, H> *>(scratch));
+        } else if constexpr (!RleOnly) {
+            if (codec == CODAG_DEFLATE)
+                st = decode_one<CODAG_DEFLATE, TB, H>(comp, coff, out, ooff, c, ring, land, scratch);
+            else if (codec == CODAG_LZ4)
+                st = decode_one<CODAG_LZ4, TB, H>(comp, coff, out, ooff, c, ring, land,
+                                                  reinterpret_cast<WaveScratch<CODAG_LZ4, TB, H> *>(scratch));
+        }
         uint64_t t1 = __builtin_amdgcn_s_memtime();
         if (ticks) ticks[c] = t1 - t0;
         if (status) status[c] = st;
         if (st != CODAG_OK) atomicMin(err, (unsigned long long)error_key(c, st));
     }
+}
+
+template <int TB, uint32_t H, int WPB>
+__global__ void __launch_bounds__(kWave * WPB)
+    decode_batch(const uint8_t *codecs, const uint8_t *comp, const uint64_t *coff, uint8_t *out,
+                 const uint64_t *ooff, uint32_t n, const uint32_t *order, uint32_t *head,
+                 uint32_t claim, int32_t *status, unsigned long long *err, uint64_t *ticks) {
+    __shared__ __align__(16) uint32_t s_ring[WPB][kBatchRingWords];
+    __shared__ __align__(16) uint32_t s_land[WPB][kLandWords];
+    __shared__ __align__(16) WaveScratch<CODAG_DEFLATE, TB, H> s_scratch[WPB];
+    const uint32_t wave = uni(threadIdx.x / kWave);
+    if (uni(head[1])) return;  // decode_batch_rle has them all
+    batch_wave<false, TB, H>(codecs, comp, coff, out, ooff, n, order, head, claim, status, err, ticks, s_ring[wave],
+                             s_land[wave], &s_scratch[wave]);
+}
+
+// Launches of RLE chunks only: 3 KiB of LDS and fewer registers a wave let 16 run
+// on a CU where the Deflate decoder's 13 KiB allow 12 (4,000 chunks of 16,384
+// values: RLE v1 494 against 577 us, RLE v2 271 against 319; one chunk 267 and
+// 295, 118 and 151).  Other launches leave here, which takes them 2 us.
+constexpr int kRleWpb = 4, kRleWavesPerCu = 16;
+__global__ void __launch_bounds__(kWave * kRleWpb)
+    decode_batch_rle(const uint8_t *codecs, const uint8_t *comp, const uint64_t *coff, uint8_t *out,
+                     const uint64_t *ooff, uint32_t n, const uint32_t *order, uint32_t *head,
+                     uint32_t claim, int32_t *status, unsigned long long *err, uint64_t *ticks) {
+    __shared__ __align__(16) uint32_t s_ring[kRleWpb][kRingLdsWords];
+    __shared__ __align__(16) uint32_t s_land[kRleWpb][kLandWords];
+    const uint32_t wave = uni(threadIdx.x / kWave);
+    if (!uni(head[1])) return;
+    batch_wave<true, 9, 4096>(codecs, comp, coff, out, ooff, n, order, head, claim, status, err, ticks, s_ring[wave],
+                              s_land[wave], nullptr);
 }
 
 template <int TB, uint32_t H>
@@ -187,7 +230,7 @@ void launch_decode_tb(codag_plan *p, const BatchArgs &a, const uint32_t *order,
 
 // Enqueue the whole sequence on s.
 int enqueue(codag_plan *p, const BatchArgs &a, unsigned long long *err, hipStream_t s) {
-    hipLaunchKernelGGL(reset_queue, dim3(1), dim3(kWave), 0, s, p->head);
+    hipLaunchKernelGGL(reset_queue, dim3(1), dim3(kResetThreads), 0, s, p->head, a.codecs, (uint32_t)a.n);
     const uint32_t *order = nullptr;
     if (p->opts.order == CODAG_ORDER_GIVEN) {
         order = a.order;
@@ -201,6 +244,15 @@ int enqueue(codag_plan *p, const BatchArgs &a, unsigned long long *err, hipStrea
         if (st) return st;
         order = p->sched.order;
     }
+    // As many RLE waves as fit, unless the plan's options or the autotuner ask
+    // for fewer waves than its Deflate decoder allows.
+    const codag_batch_opts &o = p->opts;
+    const int per_cu = o.waves_per_cu == max_waves_per_cu(o.history_kib, o.lit_table_bits, o.waves_per_block)
+                           ? kRleWavesPerCu : o.waves_per_cu;
+    const uint64_t wanted = (a.n + kRleWpb * o.chunks_per_claim - 1) / (kRleWpb * o.chunks_per_claim);
+    const uint64_t blocks = std::max<uint64_t>(1, std::min<uint64_t>(wanted, (uint64_t)p->num_cus * per_cu / kRleWpb));
+    hipLaunchKernelGGL(decode_batch_rle, dim3((uint32_t)blocks), dim3(kWave * kRleWpb), 0, s, a.codecs, a.comp, a.coff,
+                       a.out, a.ooff, (uint32_t)a.n, order, p->head, (uint32_t)o.chunks_per_claim, a.status, err, a.ticks);
     if (p->opts.lit_table_bits == 10)
         launch_decode_tb<10>(p, a, order, err, s);
     else
@@ -321,7 +373,7 @@ int codag_plan_create(codag_plan **plan, const codag_batch_opts *opts) {
         delete p;
         return st;
     }
-    if (hipMalloc(&p->head, sizeof(uint32_t)) != hipSuccess ||
+    if (hipMalloc(&p->head, 2 * sizeof(uint32_t)) != hipSuccess ||
         hipStreamCreateWithFlags(&p->capture, hipStreamNonBlocking) != hipSuccess) {
         codag_plan_destroy(p);
         return CODAG_E_HIP;

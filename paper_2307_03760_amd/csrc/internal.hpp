@@ -120,7 +120,7 @@ struct codag_plan {
     int device = 0;
     int num_cus = 0;
     codag_batch_opts opts{};
-    uint32_t *head = nullptr;  // queue position counter
+    uint32_t *head = nullptr;  // queue position counter; whether a launch has RLE chunks only
     hipStream_t capture = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
