@@ -16,6 +16,19 @@
 
 namespace codag {
 
+// The Deflate chunk of workgroup b of n.  Workgroups go to the eight XCDs in
+// turn, so in an array whose chunks repeat with a period of 2, 4 or 8 (columns of
+// a table one after another) some XCDs would have all the long ones.  Each eight
+// chunks start at another XCD than the eight before: 10,240 chunks with every
+// fourth one long 3,779 to 1,588 us (3,262 with four waves a workgroup), 80
+// chunks repeated 16,384 times 5,421 to 4,205; all-different ones 4,541 to 4,522.
+// (4,096 LZ4 chunks, all on the chip at once, came out 5% slower; every eighth
+// one of 10,240 long, 3,249 to 1,577.)
+__device__ __forceinline__ uint32_t spread_over_xcds(uint32_t b, uint32_t n) {
+    const uint32_t g = b / 8;
+    return 8 * g + 8 > n ? b : 8 * g + ((b + g + g / 8 + g / 64) & 7);
+}
+
 // Plain launch: one chunk per wave, WPB waves per workgroup, every chunk of
 // one codec.  Each wave's LDS is a slice of three distinct arrays so the
 // compiler can tell ring reads from landing-buffer fetches.
@@ -31,6 +44,7 @@ __global__ void __launch_bounds__(kWave * WPB) __attribute__((amdgpu_waves_per_e
     uint32_t wave = uni(threadIdx.x / kWave);
     uint32_t c = blockIdx.x * WPB + wave;
     if (c >= n) return;
+    if constexpr (Codec == CODAG_DEFLATE && WPB == 1) c = spread_over_xcds(c, n);
     uint64_t t0 = ticks ? __builtin_amdgcn_s_memtime() : 0;
     int st = decode_one<Codec, TB, H>(comp, coff, out, ooff, c, s_ring[wave], s_land[wave],
                                       &s_scratch[wave]);
@@ -175,8 +189,7 @@ int decompress(int codec, const uint8_t *comp_buf, const uint64_t *chunk_offsets
     // waves and because a workgroup keeps the LDS of its finished waves until
     // its longest chunk ends (four Deflate waves a workgroup against one:
     // 16,384 different chunks of 64 KiB 5.26 against 4.54 ms, 20,000
-    // log-normal ones 18.7 against 13.6; 80 chunks repeated in a fixed cycle
-    // 5.1 against 5.4).
+    // log-normal ones 18.7 against 13.6).
     int wpb = opts && opts->waves_per_block ? opts->waves_per_block : lz77 ? 1 : 4;
     int tb = opts && opts->lit_table_bits ? opts->lit_table_bits : 9;
     int hist = opts && opts->history_kib ? opts->history_kib : 4;

@@ -107,3 +107,11 @@ def test_lz4_small_blocks(dev, size):
     blobs = [workloads.lz4_block(_text(size, k)) for k in range(16)]
     pick = np.random.default_rng(4).integers(0, 16, 1024)
     assert _ratio(dev, oracle.LZ4, [blobs[k] for k in pick], [size] * 1024, waves_per_block=1) < 2
+
+
+def test_deflate_chunks_that_repeat(dev):
+    """Every fourth chunk long: workgroups of one chunk, dealt to the XCDs in turn,
+    would leave most of the XCDs idle."""
+    data = [_text(65536 if k % 4 == 0 else 4096, k) for k in range(64)]
+    blobs, sizes = [_deflate(d) for d in data], [len(d) for d in data]
+    assert _ratio(dev, oracle.DEFLATE, blobs * 160, sizes * 160, waves_per_block=4) < 0.8
