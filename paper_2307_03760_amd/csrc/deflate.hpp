@@ -1242,29 +1242,39 @@ __device__ __forceinline__ int inflate_chunk(Ring &in, LinearOut<H> &o, DeflateL
     return o.pos == cap ? CODAG_OK : CODAG_E_UNDERFLOW;
 }
 
-// How long a Huffman block of a chunk is likely to be, in bits: the longer of
-// the two before it (a flush may leave an empty block between two others), or
-// what is left of the chunk.
-struct BlockLength {
-    uint32_t last = ~0u, before = ~0u;
+// Blocks that are likely to be shorter than this many bits are decoded window by
+// window: a round's passes take as long for a few lanes' input as for all.  One
+// block of text with its tables, window by window and in a round: 181 bytes 36
+// and 49 us, 313 bytes 49 and 61, 399 bytes 56 and 49; of 4-byte integers, 316
+// bytes 37 and 67, 498 bytes 68 and 58.  Streams flushed every 100 bytes take
+// 3.4 ms per 64 KiB, 18.9 in rounds.  A block that goes on past this goes on
+// in rounds.
+//
+// Blocks with much output for their bits are copies mostly, which rounds make
+// many at a time: runs of integers, 8 KiB from 2,372 bits 70 and 72 us, 16 KiB
+// from 4,263 bits 132 and 89; but not where every copy repeats the one before:
+// 64 KiB of zeros from 624 bits 190 and 299.
+constexpr uint32_t kShortBits = 3072, kShortOut = 8192, kRepeatsPerBit = 32;
 
-    __device__ __forceinline__ uint32_t expect(uint32_t rest) const {
-        return min(rest, last == ~0u ? ~0u : before == ~0u ? last : max(last, before));
+// How long a Huffman block of a chunk is likely to be, in bits and in output
+// bytes: as the longer of the two before it (a flush may leave an empty block
+// between two others), or what is left of the chunk.
+struct BlockLength {
+    uint32_t last = ~0u, before = 0, last_out = ~0u, before_out = 0;
+
+    __device__ __forceinline__ uint32_t likely() const { return max(last, before); }
+    __device__ __forceinline__ bool is_short(uint32_t rest, uint32_t rest_out) const {
+        const uint32_t bits = min(rest, likely()), out = min(rest_out, max(last_out, before_out));
+        return bits < kShortBits && (out <= kShortOut || out > kRepeatsPerBit * bits);
     }
-    __device__ __forceinline__ void ended(uint32_t bits) {
-        before = last;
+    __device__ __forceinline__ void ended(uint32_t bits, uint32_t out) {
+        const bool first = last == ~0u;
+        before = first ? 0u : last;
+        before_out = first ? 0u : last_out;
         last = bits;
+        last_out = out;
     }
 };
-
-// Blocks that are likely to be shorter than this are decoded window by window:
-// a round's passes take as long for a few lanes' input as for all.  One block
-// of text with its tables, window by window and in a round: 181 bytes 36 and
-// 49 us, 313 bytes 49 and 61, 399 bytes 56 and 49; of 4-byte integers, 316
-// bytes 37 and 67, 498 bytes 68 and 58.  Streams flushed every 100 bytes take
-// 3.5 ms per 64 KiB, 18.9 in rounds.  A block that goes on past this goes on
-// in rounds.
-constexpr uint32_t kShortBits = 3072;
 
 template <int TB, uint32_t H, int MODE = kAllLanes, class Ring>
 __device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t cap,
@@ -1277,10 +1287,10 @@ __device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t c
             return inflate_leader<TB, H>(in, bi, o, lds);
         } else {
             int st;
-            const uint32_t p0 = bi.pos();
+            const uint32_t p0 = bi.pos(), out0 = o.pos;
             uint32_t until = ~0u;  // window by window up to here
             if constexpr (Ring::kLaneRounds)
-                until = blocks.expect(8 * in.gend - p0) < kShortBits ? p0 + kShortBits : 0u;
+                until = blocks.is_short(8 * in.gend - p0, o.cap - out0) ? p0 + kShortBits : 0u;
             do {
                 if (bi.pos() < until) {
                     st = inflate_batched<TB, H>(in, bi, o, lds, until);
@@ -1291,7 +1301,7 @@ __device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t c
                 }
                 if (st == kOneSymbol) st = inflate_symbol<TB, H>(in, bi, o, lds);
             } while (st == kMore);
-            blocks.ended(bi.pos() - p0);
+            blocks.ended(bi.pos() - p0, o.pos - out0);
             return st;
         }
     });

@@ -28,10 +28,12 @@
 namespace codag {
 
 constexpr uint32_t kTeamH = 32768;  // output window
-// Blocks likely to be shorter than this are wave 0's alone: they fit a round of
-// one wave, and a team's round has its input and its barriers besides (blocks
-// of 800 bytes of output 3.6 against 4.9 ms per 64 KiB; a chunk of 16,384 bits
-// is faster by the team, 89 us against 109).
+// Blocks in the middle of a chunk that are likely to be shorter than this are
+// wave 0's alone: they fit a round of one wave, and a team's round would take its
+// 32 KiB of input, and its passes over the blocks after, for each (64 KiB
+// flushed every 2,000 bytes, 48 chunks 1.76 against 2.04 ms).  The last block of
+// a chunk is the team's however short: 24 KiB of runs from 5,846 bits 98 us
+// against 124.
 constexpr uint32_t kAloneBits = 8192;
 
 // Room for len <= kAppend more bytes, by the whole team (the same decision on
@@ -415,10 +417,10 @@ static __device__ __forceinline__ int chunk(const uint8_t *chunk, uint32_t len, 
     BlockLength blocks;
     const int st = inflate_chunk<9, kTeamH>(in, o, &s->d, made, [&](BitIn &bi) {
         int r;
-        const uint32_t p0 = bi.pos(), expect = blocks.expect(8 * in.gend - p0);
+        const uint32_t p0 = bi.pos(), out0 = o.pos, rest = 8 * in.gend - p0;
         // Window by window up to here, then in rounds of one wave, then the team's.
-        uint32_t until = expect < kShortBits ? p0 + kShortBits : 0u;
-        const uint32_t alone = expect < kAloneBits ? p0 + kAloneBits : 0u;
+        uint32_t until = blocks.is_short(rest, o.cap - out0) ? p0 + kShortBits : 0u;
+        const uint32_t alone = blocks.likely() < kAloneBits && rest >= kAloneBits ? p0 + kAloneBits : 0u;
         do {
             bool windows = false;
             if (bi.pos() < until) {
@@ -446,7 +448,7 @@ static __device__ __forceinline__ int chunk(const uint8_t *chunk, uint32_t len, 
             if (windows) until = ~0u;
             if (r == kOneSymbol) r = inflate_symbol<9, kTeamH>(in, bi, o, &s->d);
         } while (r == kMore);
-        blocks.ended(bi.pos() - p0);
+        blocks.ended(bi.pos() - p0, o.pos - out0);
         return r;
     });
     if (lane() == 0) s->go = 0;

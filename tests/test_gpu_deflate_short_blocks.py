@@ -99,3 +99,22 @@ def test_every_symbol_of_the_fixed_code(dev, bits):
     ch = workloads._pack([oracle.DEFLATE] * len(blobs), blobs, sizes)
     st = assert_parity(oracle.DEFLATE, ch, dev, lit_table_bits=bits)
     assert (st[:2] == 0).all() and (st[2:] == oracle.E_CORRUPT).all()
+
+
+@pytest.mark.parametrize("waves", [0, 1])
+def test_short_blocks_of_much_output(dev, waves):
+    """Few bits and many bytes: runs of integers, repeated bytes and phrases, alone
+    and as blocks of a stream among short ones."""
+    rng = np.random.default_rng(23)
+    blobs, sizes = [], []
+    for n in (100, 3000, 8192, 8193, 16000, 24000, 40000, 70000):
+        runs = workloads.int32_column(n, rng, run_heavy=True)
+        for data in (runs, bytes(n), (runs[:40] * (n // 40 + 1))[:n]):
+            blobs.append(_stream(data, [], []))
+            sizes.append(n)
+            blobs.append(_stream(b"a few words" + data + data[:500], [11, n, 200, 200], [zlib.Z_BLOCK, zlib.Z_SYNC_FLUSH]))
+            sizes.append(11 + n + min(n, 500))
+            blobs.append(_stream(data * 3, [n, n, n], [zlib.Z_FULL_FLUSH]))
+            sizes.append(3 * n)
+    ch = workloads._pack([oracle.DEFLATE] * len(blobs), blobs, sizes)
+    assert (assert_parity(oracle.DEFLATE, ch, dev, waves_per_block=waves) == 0).all()
