@@ -51,16 +51,21 @@ __global__ void __launch_bounds__(kResetThreads) reset_queue(uint32_t *head, con
 // One input buffer for every codec's ring.
 constexpr uint32_t kBatchRingWords = kRingLdsWords > kRoundInWords ? kRingLdsWords : kRoundInWords;
 
-// One wave's share of a batch.  Each wave claims `claim` consecutive queue
-// positions at a time (one atomic add for several small chunks) until the queue
-// is empty.  Every store of a per-chunk result is made by all lanes with the
-// same value (a one-lane branch inside this loop would make the compiler treat
-// the loop as divergent).  RleOnly: the launch has no Deflate or LZ4 chunk.
-template <bool RleOnly, int TB, uint32_t H>
-__device__ __forceinline__ void batch_wave(const uint8_t *codecs, const uint8_t *comp, const uint64_t *coff, uint8_t *out,
-                                           const uint64_t *ooff, uint32_t n, const uint32_t *order, uint32_t *head,
-                                           uint32_t claim, int32_t *status, unsigned long long *err, uint64_t *ticks,
-                                           uint32_t *ring, uint32_t *land, WaveScratch<CODAG_DEFLATE, TB, H> *scratch) {
+// Each wave claims `claim` consecutive queue positions at a time (one
+// atomic add for several small chunks) until the queue is empty.  Every
+// store of a per-chunk result is made by all lanes with the same value (a
+// one-lane branch inside this loop would make the compiler treat the loop
+// as divergent).
+template <int TB, uint32_t H, int WPB>
+__global__ void __launch_bounds__(kWave * WPB)
+    decode_batch(const uint8_t *codecs, const uint8_t *comp, const uint64_t *coff, uint8_t *out,
+                 const uint64_t *ooff, uint32_t n, const uint32_t *order, uint32_t *head,
+                 uint32_t claim, int32_t *status, unsigned long long *err, uint64_t *ticks) {
+    __shared__ __align__(16) uint32_t s_ring[WPB][kBatchRingWords];
+    __shared__ __align__(16) uint32_t s_land[WPB][kLandWords];
+    __shared__ __align__(16) WaveScratch<CODAG_DEFLATE, TB, H> s_scratch[WPB];
+    const uint32_t wave = uni(threadIdx.x / kWave);
+    if (uni(head[1])) return;  // decode_batch_rle has them all
     uint32_t idx = 0, last = 0;
     for (;;) {
         if (idx == last) {
@@ -78,20 +83,24 @@ __device__ __forceinline__ void batch_wave(const uint8_t *codecs, const uint8_t 
         }
         uint32_t codec = uni((uint32_t)codecs[c]);
         uint64_t t0 = __builtin_amdgcn_s_memtime();
-        int st = CODAG_E_INVALID_ARGUMENT;
-        if (codec == CODAG_RLE_V1) {
-            st = decode_one<CODAG_RLE_V1, TB, H>(comp, coff, out, ooff, c, ring, land,
-                                                 reinterpret_cast<WaveScratch<CODAG_RLE_V1, TB, H> *>(scratch));
-        } else if (codec == CODAG_RLE_V2) {
-            st = decode_one<CODAG_RLE_V2, TB, H>(comp, coff, out, ooff, c, ring, land,
-                                                 reinterpret_cast<WaveScratch<CODAG_RLE_V2, TB, H> *>(scratch));
-        } else if constexpr (!RleOnly) {
-            if (codec == CODAG_DEFLATE)
-                st = decode_one<CODAG_DEFLATE, TB, H>(comp, coff, out, ooff, c, ring, land, scratch);
-            else if (codec == CODAG_LZ4)
-                st = decode_one<CODAG_LZ4, TB, H>(comp, coff, out, ooff, c, ring, land,
-                                                  reinterpret_cast<WaveScratch<CODAG_LZ4, TB, H> *>(scratch));
-        }
+        int st;
+        if (codec == CODAG_RLE_V1)
+            st = decode_one<CODAG_RLE_V1, TB, H>(
+                comp, coff, out, ooff, c, s_ring[wave], s_land[wave],
+                reinterpret_cast<WaveScratch<CODAG_RLE_V1, TB, H> *>(&s_scratch[wave]));
+        else if (codec == CODAG_RLE_V2)
+            st = decode_one<CODAG_RLE_V2, TB, H>(
+                comp, coff, out, ooff, c, s_ring[wave], s_land[wave],
+                reinterpret_cast<WaveScratch<CODAG_RLE_V2, TB, H> *>(&s_scratch[wave]));
+        else if (codec == CODAG_DEFLATE)
+            st = decode_one<CODAG_DEFLATE, TB, H>(comp, coff, out, ooff, c, s_ring[wave],
+                                                  s_land[wave], &s_scratch[wave]);
+        else if (codec == CODAG_LZ4)
+            st = decode_one<CODAG_LZ4, TB, H>(
+                comp, coff, out, ooff, c, s_ring[wave], s_land[wave],
+                reinterpret_cast<WaveScratch<CODAG_LZ4, TB, H> *>(&s_scratch[wave]));
+        else
+            st = CODAG_E_INVALID_ARGUMENT;
         uint64_t t1 = __builtin_amdgcn_s_memtime();
         if (ticks) ticks[c] = t1 - t0;
         if (status) status[c] = st;
@@ -99,24 +108,11 @@ __device__ __forceinline__ void batch_wave(const uint8_t *codecs, const uint8_t 
     }
 }
 
-template <int TB, uint32_t H, int WPB>
-__global__ void __launch_bounds__(kWave * WPB)
-    decode_batch(const uint8_t *codecs, const uint8_t *comp, const uint64_t *coff, uint8_t *out,
-                 const uint64_t *ooff, uint32_t n, const uint32_t *order, uint32_t *head,
-                 uint32_t claim, int32_t *status, unsigned long long *err, uint64_t *ticks) {
-    __shared__ __align__(16) uint32_t s_ring[WPB][kBatchRingWords];
-    __shared__ __align__(16) uint32_t s_land[WPB][kLandWords];
-    __shared__ __align__(16) WaveScratch<CODAG_DEFLATE, TB, H> s_scratch[WPB];
-    const uint32_t wave = uni(threadIdx.x / kWave);
-    if (uni(head[1])) return;  // decode_batch_rle has them all
-    batch_wave<false, TB, H>(codecs, comp, coff, out, ooff, n, order, head, claim, status, err, ticks, s_ring[wave],
-                             s_land[wave], &s_scratch[wave]);
-}
-
-// Launches of RLE chunks only: 3 KiB of LDS and fewer registers a wave let 16 run
-// on a CU where the Deflate decoder's 13 KiB allow 12 (4,000 chunks of 16,384
-// values: RLE v1 494 against 577 us, RLE v2 271 against 319; one chunk 267 and
-// 295, 118 and 151).  Other launches leave here, which takes them 2 us.
+// Launches of RLE chunks only, the same way: 3 KiB of LDS and fewer registers a
+// wave let 16 run on a CU where the Deflate decoder's 13 KiB allow 12 (4,000
+// chunks of 16,384 values: RLE v1 494 against 577 us, RLE v2 271 against 319; one
+// chunk 267 and 295, 118 and 151).  Other launches leave here, which takes them
+// 2 us.
 constexpr int kRleWpb = 4, kRleWavesPerCu = 16;
 __global__ void __launch_bounds__(kWave * kRleWpb)
     decode_batch_rle(const uint8_t *codecs, const uint8_t *comp, const uint64_t *coff, uint8_t *out,
@@ -126,8 +122,33 @@ __global__ void __launch_bounds__(kWave * kRleWpb)
     __shared__ __align__(16) uint32_t s_land[kRleWpb][kLandWords];
     const uint32_t wave = uni(threadIdx.x / kWave);
     if (!uni(head[1])) return;
-    batch_wave<true, 9, 4096>(codecs, comp, coff, out, ooff, n, order, head, claim, status, err, ticks, s_ring[wave],
-                              s_land[wave], nullptr);
+    uint32_t idx = 0, last = 0;
+    for (;;) {
+        if (idx == last) {
+            idx = uni(atomicAdd(head, lane() == 0 ? claim : 0u));
+            if (idx >= n) break;
+            last = min(idx + claim, n);
+        }
+        const uint32_t q = idx++;
+        uint32_t c = order ? uni(order[q]) : q;
+        if (c >= n) {  // not a permutation: report the queue position
+            atomicMin(err, (unsigned long long)error_key(q, CODAG_E_INVALID_ARGUMENT));
+            continue;
+        }
+        uint32_t codec = uni((uint32_t)codecs[c]);
+        uint64_t t0 = __builtin_amdgcn_s_memtime();
+        int st;
+        if (codec == CODAG_RLE_V1)
+            st = decode_one<CODAG_RLE_V1, 9, 4096>(comp, coff, out, ooff, c, s_ring[wave], s_land[wave], nullptr);
+        else if (codec == CODAG_RLE_V2)
+            st = decode_one<CODAG_RLE_V2, 9, 4096>(comp, coff, out, ooff, c, s_ring[wave], s_land[wave], nullptr);
+        else
+            st = CODAG_E_INVALID_ARGUMENT;
+        uint64_t t1 = __builtin_amdgcn_s_memtime();
+        if (ticks) ticks[c] = t1 - t0;
+        if (status) status[c] = st;
+        if (st != CODAG_OK) atomicMin(err, (unsigned long long)error_key(c, st));
+    }
 }
 
 template <int TB, uint32_t H>

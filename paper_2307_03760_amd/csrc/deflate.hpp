@@ -241,7 +241,10 @@ struct DeflateLds : DeflateTables<TB> {
     };
     uint64_t queue[kCopyQueue];  // pending copies
     __attribute__((aligned(16))) uint8_t window[H];
-    uint8_t window_pad[16];  // eight-byte reads may pass the window's end
+    union {
+        uint8_t window_pad[16];  // eight-byte reads may pass the window's end; nothing is written here
+        uint32_t block[4];       // BlockLength's
+    };
 };
 
 // Wave-uniform LSB-first bit reader over the ring.
@@ -1257,22 +1260,31 @@ __device__ __forceinline__ int inflate_chunk(Ring &in, LinearOut<H> &o, DeflateL
 constexpr uint32_t kShortBits = 3072, kShortOut = 8192, kRepeatsPerBit = 32;
 
 // How long a Huffman block of a chunk is likely to be, in bits and in output
-// bytes: as the longer of the two before it (a flush may leave an empty block
-// between two others), or what is left of the chunk.
+// bytes: as long as the one before it or half as long as was likely for that
+// (long and short ones may alternate), or what is left of the chunk.  Kept in
+// LDS: in scalar registers its four words cost the loops of the batched kernel
+// 2%.
 struct BlockLength {
-    uint32_t last = ~0u, before = 0, last_out = ~0u, before_out = 0;
+    uint32_t *w;  // likely bits and output (~0: none yet), the block's first bit and output position
 
-    __device__ __forceinline__ uint32_t likely() const { return max(last, before); }
-    __device__ __forceinline__ bool is_short(uint32_t rest, uint32_t rest_out) const {
-        const uint32_t bits = min(rest, likely()), out = min(rest_out, max(last_out, before_out));
-        return bits < kShortBits && (out <= kShortOut || out > kRepeatsPerBit * bits);
+    __device__ __forceinline__ void init(uint32_t *words) {
+        w = words;
+        w[0] = w[1] = ~0u;
     }
-    __device__ __forceinline__ void ended(uint32_t bits, uint32_t out) {
-        const bool first = last == ~0u;
-        before = first ? 0u : last;
-        before_out = first ? 0u : last_out;
-        last = bits;
-        last_out = out;
+    __device__ __forceinline__ uint32_t likely() const { return uni(w[0]); }
+    // A block starts at bit p and output position out, with so much left.
+    __device__ __forceinline__ bool is_short(uint32_t p, uint32_t rest, uint32_t out, uint32_t rest_out) {
+        w[2] = p;
+        w[3] = out;
+        const uint32_t b = min(rest, likely()), n = min(rest_out, uni(w[1]));
+        return b < kShortBits && (n <= kShortOut || n > kRepeatsPerBit * b);
+    }
+    __device__ __forceinline__ void ended(uint32_t p, uint32_t out) {
+        const uint32_t b = p - uni(w[2]), n = out - uni(w[3]);
+        if (b < 16) return;  // a flush's empty block
+        const bool first = likely() == ~0u;
+        w[0] = first ? b : max(b, likely() / 2);
+        w[1] = first ? n : max(n, uni(w[1]) / 2);
     }
 };
 
@@ -1282,15 +1294,15 @@ __device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t c
     LinearOut<H> o;
     o.init(out, cap, lds->window);
     BlockLength blocks;
+    blocks.init(lds->block);
     return inflate_chunk<TB, H>(in, o, lds, made, [&](BitIn &bi) {
         if constexpr (MODE == kLeaderLane) {
             return inflate_leader<TB, H>(in, bi, o, lds);
         } else {
             int st;
-            const uint32_t p0 = bi.pos(), out0 = o.pos;
             uint32_t until = ~0u;  // window by window up to here
             if constexpr (Ring::kLaneRounds)
-                until = blocks.is_short(8 * in.gend - p0, o.cap - out0) ? p0 + kShortBits : 0u;
+                until = blocks.is_short(bi.pos(), 8 * in.gend - bi.pos(), o.pos, o.cap - o.pos) ? bi.pos() + kShortBits : 0u;
             do {
                 if (bi.pos() < until) {
                     st = inflate_batched<TB, H>(in, bi, o, lds, until);
@@ -1301,7 +1313,9 @@ __device__ __forceinline__ int decode_deflate(Ring &in, uint8_t *out, uint32_t c
                 }
                 if (st == kOneSymbol) st = inflate_symbol<TB, H>(in, bi, o, lds);
             } while (st == kMore);
-            blocks.ended(bi.pos() - p0, o.pos - out0);
+            if constexpr (Ring::kLaneRounds) {
+                if (8 * in.gend - bi.pos() >= 16) blocks.ended(bi.pos(), o.pos);  // not after the chunk's last block
+            }
             return st;
         }
     });

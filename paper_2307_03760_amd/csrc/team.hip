@@ -415,11 +415,12 @@ static __device__ __forceinline__ int chunk(const uint8_t *chunk, uint32_t len, 
         return CODAG_OK;
     }
     BlockLength blocks;
+    blocks.init(s->d.block);
     const int st = inflate_chunk<9, kTeamH>(in, o, &s->d, made, [&](BitIn &bi) {
         int r;
-        const uint32_t p0 = bi.pos(), out0 = o.pos, rest = 8 * in.gend - p0;
+        const uint32_t p0 = bi.pos(), rest = 8 * in.gend - p0;
         // Window by window up to here, then in rounds of one wave, then the team's.
-        uint32_t until = blocks.is_short(rest, o.cap - out0) ? p0 + kShortBits : 0u;
+        uint32_t until = blocks.is_short(p0, rest, o.pos, o.cap - o.pos) ? p0 + kShortBits : 0u;
         const uint32_t alone = blocks.likely() < kAloneBits && rest >= kAloneBits ? p0 + kAloneBits : 0u;
         do {
             bool windows = false;
@@ -448,7 +449,7 @@ static __device__ __forceinline__ int chunk(const uint8_t *chunk, uint32_t len, 
             if (windows) until = ~0u;
             if (r == kOneSymbol) r = inflate_symbol<9, kTeamH>(in, bi, o, &s->d);
         } while (r == kMore);
-        blocks.ended(bi.pos() - p0, o.pos - out0);
+        blocks.ended(bi.pos(), o.pos);
         return r;
     });
     if (lane() == 0) s->go = 0;
