@@ -323,16 +323,27 @@ def time_workload(name, ch, steps, warmup, dev, flush_buf=None):
 
 
 def launch_description(codec: int, n_chunks: int) -> str:
-    """What codag_decompress enqueues for this codec and chunk count with
-    default options."""
+    """What codag_decompress enqueues for this codec (signed 8-byte values for
+    RLE) and chunk count with default options."""
+    if codec == 2 and n_chunks <= 256:
+        return ("rle_v2_blocks: a workgroup per chunk, one wave walks its run headers and 8 decode "
+                "(chunks of up to 1,536 values by one wave)")
     if codec == 2 and n_chunks <= 2048:
         return ("group-parallel: rle_v2_index (one wave per chunk parses run headers and cuts the "
                 "chunk into 8 ranges) + rle_v2_ranges (one wave per range) + split_finish")
     if codec == 1 and n_chunks <= 256:
         return ("group-parallel: rle_v1_index (a 16-wave workgroup per chunk finds group starts "
                 "and cuts 32 ranges) + rle_v1_groups (one wave per range) + split_finish")
+    if codec == 3 and n_chunks <= 512:
+        return f"deflate_team: a workgroup of {16 if n_chunks <= 256 else 8} waves per chunk, 32 KiB LDS window"
     if codec == 3:
         return "decode_plain<DEFLATE>: one wave64 per chunk, 1 wave per workgroup, 4 KiB LDS window"
+    if codec == 4 and n_chunks <= 2048:
+        return f"byte_rle_blocks: a workgroup of {1024 if n_chunks <= 512 else 512} threads per chunk"
+    if codec == 5 and n_chunks <= 1024:
+        return ("lz4_team: " + ("a workgroup" if n_chunks <= 256 else "256 workgroups")
+                + " of 16 waves" + (" per chunk" if n_chunks <= 256 else ", up to 4 chunks each in turn")
+                + ", 32 KiB LDS window (small blocks and long literal runs by one wave)")
     if codec == 5:
         return "decode_plain<LZ4>: one wave64 per chunk, 1 wave per workgroup, 4 KiB LDS window"
     return "decode_plain: one wave64 per chunk, 4 waves per workgroup"
