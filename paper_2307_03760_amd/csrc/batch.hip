@@ -3,7 +3,8 @@
 // The grid holds a fixed number of resident waves per CU; each wave takes
 // the next position of a device-side work queue (one atomic add per chunk),
 // maps it through an optional order array, and decodes that chunk with the
-// chunk's codec using the same per-wave decoders as the plain launch.  The
+// chunk's codec using the same per-wave decoders as the plain launch (a batch
+// that holds RLE chunks only by a kernel of its own, decode_batch_rle).  The
 // queue order is the scheduler's lever: with chunks of very uneven cost, the
 // order decides how much idle time the last waves leave at the end.  The
 // sequence (queue reset, optional scheduling kernels, decode) can be captured
@@ -168,7 +169,7 @@ namespace {
 
 constexpr uint32_t kLdsPerCu = 160 * 1024;
 constexpr int kBatchTB = 9;  // default Deflate literal/length table bits in the batched kernel
-constexpr int kVgprWavesPerSimd = 3;  // decode_batch uses up to 136 VGPRs
+constexpr int kBatchWavesPerSimd = 3;  // decode_batch: its 13 KiB of LDS a wave allow three, its 113 VGPRs four
 
 template <int TB>
 uint32_t lds_per_wave_tb(int hist_kib) {
@@ -183,7 +184,7 @@ uint32_t lds_per_wave(int hist_kib, int tb) {
 
 int max_waves_per_cu(int hist_kib, int tb, int wpb) {
     int by_lds = (int)(kLdsPerCu / (lds_per_wave(hist_kib, tb) * wpb)) * wpb;
-    return std::max(wpb, std::min({by_lds, 4 * kVgprWavesPerSimd, 16}));
+    return std::max(wpb, std::min({by_lds, 4 * kBatchWavesPerSimd, 16}));
 }
 
 }  // namespace

@@ -4,8 +4,9 @@
 // the decompression unit); a workgroup holds `waves_per_block` independent
 // waves that never synchronize with each other, so workgroups are only a
 // dispatch and LDS-allocation unit.  Chunk i of the plain launch is handled
-// by wave (blockIdx.x * waves_per_block + wave) and the hardware dispatcher
-// balances uneven chunks by handing out workgroups as slots free up.
+// by wave (blockIdx.x * waves_per_block + wave), Deflate's in a changed order
+// (spread_over_xcds), and the hardware dispatcher balances uneven chunks by
+// handing out workgroups as slots free up.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -177,8 +178,8 @@ int decompress(int codec, const uint8_t *comp_buf, const uint64_t *chunk_offsets
     const int eb = opts && opts->elem_bytes ? opts->elem_bytes : 8;
     const int uns = opts ? opts->unsigned_values : 0;
     if ((eb != 1 && eb != 2 && eb != 4 && eb != 8) || (uns != 0 && uns != 1)) return CODAG_E_INVALID_ARGUMENT;
-    // Byte RLE, and RLE element types other than signed 8-byte values, take
-    // the one-wave-per-chunk typed decoder.
+    // Byte RLE, and RLE element types other than signed 8-byte values: a
+    // workgroup per chunk where launch_typed has one, else one wave per chunk.
     const bool typed = codec == CODAG_BYTE_RLE || (!lz77 && (eb != 8 || uns));
     if (typed && opts && (opts->variant || opts->group_parallel == 2)) return CODAG_E_INVALID_ARGUMENT;
     if (n_chunks == 0) return CODAG_OK;

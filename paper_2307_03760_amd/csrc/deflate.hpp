@@ -830,8 +830,9 @@ __device__ __forceinline__ int inflate_batched(Ring &in, BitIn &bi, LinearOut<H>
 // 4.6 but 4 KiB of input and two KiB of segment notes per wave.  Segments are
 // 64 bits because the output window bounds one step to about 340 tokens.
 // Measured against the window-by-window decoder: 16,384 chunks of 64 KiB
-// 12.6 to 5.6 ms, 48 chunks of 60 KB (one wave each, nothing else running)
-// 1,814 to 624 us, a learned batch of 2,000 chunks 16.3 to 4.7 ms.
+// 12.5 to 4.2 ms, 48 chunks of 60 KB (one wave each, nothing else
+// running) 1,814 to 624 us, a learned batch of 2,000 chunks 15.8 to 4.4 ms.
+// Chunks and blocks too short for it are decoded window by window (kShortBits).
 // A wave holds 12 KiB of LDS instead of 8 (13 instead of 20 waves per CU),
 // which the shorter work more than pays for.  Smaller footprints measured
 // over 20,480 chunks: 14 waves (a 3 KiB window, 128 copies) 6.81 against 6.96
@@ -1142,10 +1143,9 @@ __device__ __forceinline__ int inflate_leader(Ring &in, BitIn &bi, LinearOut<H> 
     }
 }
 
-// MODE kAllLanes: the batched token decoder above (every lane decodes a
-// candidate token); kLeaderLane: lane 0 alone decodes each token and hands
-// it to the wave through LDS (the single-thread decoding CODAG compares
-// against, Section V-E).
+// MODE kAllLanes: the decoders above, rounds or windows; kLeaderLane: lane 0
+// alone decodes each token and hands it to the wave through LDS (the
+// single-thread decoding CODAG compares against, Section V-E).
 enum : int { kAllLanes = 0, kLeaderLane = 1 };
 
 // With `made` non-null the output range is a capacity: a final block that

@@ -78,7 +78,8 @@ struct OrcMeta {
     uint64_t last;           // bytes the last chunk produced
 };
 
-// LZ4 the same way, for launches of up to kLzTeamMaxChunks chunks.
+// LZ4 the same way (above 256 chunks a workgroup takes several in turn), for
+// launches of up to kLzTeamMaxChunks chunks.
 int launch_lz4_team(const uint8_t *comp, const uint64_t *coff, uint8_t *out, const uint64_t *ooff, uint32_t n,
                     int32_t *status, unsigned long long *err, hipStream_t s);
 constexpr uint32_t kLzTeamMaxChunks = 1024;

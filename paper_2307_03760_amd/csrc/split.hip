@@ -813,12 +813,13 @@ int launch_rle_v2_split(const uint8_t *comp, const uint64_t *coff, uint8_t *out,
 // through HBM.  Chunks of up to kV2BlockSmall values are decoded by wave 0 as
 // they are read: the walk and a second read of the input cost more there.
 //
-// The walk is what is left (some 30 of 38 us for a row group of 10,000
-// values).  Measured against the three passes: one row group 47 to 38 us, 256
-// of them 77 to 63 (90 by one wave each, as narrower types were decoded); 512
-// chunks of 32,768 values 164 both ways and 512 of 10,000 two-byte values 78
-// against 74 by one wave each, hence the limit.  With 15 ranges instead of 8:
-// 43 us for one row group, 255 for 512 chunks (waiting waves in the way).
+// The walk is what is left (some 30 us of the kernel's 38 for a row group of
+// 10,000 values).  Measured against the three passes, by calls: one row group
+// 47 to 42 us, 256 of them 77 to 63 (90 by one wave each, as narrower types
+// were decoded); 512 chunks of 32,768 values 164 both ways and 512 of 10,000
+// two-byte values 78 against 74 by one wave each, hence the limit.  With 15
+// ranges instead of 8 the kernel takes 43 us for one row group, 255 for 512
+// chunks (waiting waves in the way).
 constexpr uint32_t kV2BlockRanges = 8, kV2BlockSmall = 1536;
 constexpr uint32_t kV2BlockThreads = kWave * (kV2BlockRanges + 1);
 

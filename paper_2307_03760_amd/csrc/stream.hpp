@@ -185,9 +185,10 @@ using InRing = InRingT<kFetchBytes>;
 // An input ring without a landing buffer or fetch-ahead: each fetch of F
 // bytes (F = 512, or a multiple of 1 KiB) lands straight in the ring half
 // whose bytes are no longer needed, and the wave waits for it.  For decoders
-// that spend tens of microseconds on a kilobyte of input (Deflate, LZ4) the
-// wait costs a few percent, and the LDS it saves (a landing buffer and, at
-// F = 512, half the ring) is what limits how many of their waves a CU holds.
+// that spend tens of microseconds on a kilobyte of input (Deflate's headers and
+// its window-by-window decoder) the wait costs a few percent, and the LDS it
+// saves (a landing buffer and, at F = 512, half the ring) is what limits how
+// many of their waves a CU holds.
 // Same interface and guarantee as InRingT: after ensure(end), bytes
 // [end - F, end) are readable; bytes past the chunk read as zero.
 template <uint32_t F>

@@ -10,12 +10,12 @@
 // a round costs about what a wave's round costs and takes kTeam times the
 // input.
 //
-// Measured against one wave per chunk: 48 chunks of 60 KB 624 to 175 us, 49
-// ORC blocks of 256 KiB 2.58 to 0.63 ms, 256 chunks of 64 KiB 689 to 195 us
+// Measured against one wave per chunk: 48 chunks of 60 KB 624 to 162 us, 49
+// ORC blocks of 256 KiB 2.58 to 0.65 ms, 256 chunks of 64 KiB 689 to 195 us
 // with teams of 16; 512 chunks of 64 KiB 727 to 302 us with teams of 8.  1,024
 // chunks fill the GPU a wave each (780 us against 899 in teams of 8), hence
-// the limits.  Of a 64 KiB text chunk's 400,000 cycles the passes take some
-// 130,000, the copies 70,000, the block header and its tables 55,000.
+// the limits.  Of a 64 KiB text chunk's 372,000 cycles the passes take some
+// 120,000, the copies 70,000, the block header and its tables 40,000.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
