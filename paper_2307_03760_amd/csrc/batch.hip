@@ -25,9 +25,11 @@
 
 namespace codag {
 
-// head[0]: the queue's next position; head[1]: the launch has RLE chunks only.
+// head[0]: the queue's next position, from `dealt` on in decode_batch's launches;
+// head[1]: the launch has RLE chunks only.
 constexpr uint32_t kResetThreads = 1024;
-__global__ void __launch_bounds__(kResetThreads) reset_queue(uint32_t *head, const uint8_t *codecs, uint32_t n) {
+__global__ void __launch_bounds__(kResetThreads) reset_queue(uint32_t *head, const uint8_t *codecs, uint32_t n,
+                                                             uint32_t dealt) {
     __shared__ uint32_t s_lz77;
     const uint32_t t = threadIdx.x;
     if (t == 0) s_lz77 = 0;
@@ -44,7 +46,7 @@ __global__ void __launch_bounds__(kResetThreads) reset_queue(uint32_t *head, con
     if (ballot(lz77) && lane() == 0) s_lz77 = 1;  // the same value from every wave
     __syncthreads();
     if (t == 0) {
-        head[0] = 0;
+        head[0] = s_lz77 ? dealt : 0;
         head[1] = s_lz77 ? 0 : 1;
     }
 }
@@ -53,10 +55,16 @@ __global__ void __launch_bounds__(kResetThreads) reset_queue(uint32_t *head, con
 constexpr uint32_t kBatchRingWords = kRingLdsWords > kRoundInWords ? kRingLdsWords : kRoundInWords;
 
 // Each wave claims `claim` consecutive queue positions at a time (one
-// atomic add for several small chunks) until the queue is empty.  Every
-// store of a per-chunk result is made by all lanes with the same value (a
-// one-lane branch inside this loop would make the compiler treat the loop
-// as divergent).
+// atomic add for several small chunks) until the queue is empty.  The first
+// ones are dealt, a claim to every workgroup's first wave, then one to every
+// second: claimed by whichever wave came first, a longest-first queue's largest
+// chunks lay on a few CUs together, in each other's way, and the slowest of them
+// is the launch.  (2,000 chunks, seven of them the largest: 4,130 to 4,370 us by
+// what else was launched, 3,880 dealt, 4,150 with a workgroup's waves dealt
+// neighbours.  20,000 chunks longest first 11.6 to 11.1 ms, in index order 12.7
+// and 12.8.)  Every store of a per-chunk result is made by all lanes with the
+// same value (a one-lane branch inside this loop would make the compiler treat
+// the loop as divergent).
 template <int TB, uint32_t H, int WPB>
 __global__ void __launch_bounds__(kWave * WPB)
     decode_batch(const uint8_t *codecs, const uint8_t *comp, const uint64_t *coff, uint8_t *out,
@@ -67,16 +75,17 @@ __global__ void __launch_bounds__(kWave * WPB)
     __shared__ __align__(16) WaveScratch<CODAG_DEFLATE, TB, H> s_scratch[WPB];
     const uint32_t wave = uni(threadIdx.x / kWave);
     if (uni(head[1])) return;  // decode_batch_rle has them all
-    uint32_t idx = 0, last = 0;
+    uint32_t idx = (wave * gridDim.x + blockIdx.x) * claim;
+    uint32_t last = idx + claim;
     for (;;) {
         if (idx == last) {
             // Lane 0 adds; the others add zero, so lane 0's old value is the
             // claimed position whatever order the lanes' adds are applied in.
             idx = uni(atomicAdd(head, lane() == 0 ? claim : 0u));
-            if (idx >= n) break;
-            last = min(idx + claim, n);
+            last = idx + claim;
         }
         const uint32_t q = idx++;
+        if (q >= n) break;
         uint32_t c = order ? uni(order[q]) : q;
         if (c >= n) {  // not a permutation: report the queue position
             atomicMin(err, (unsigned long long)error_key(q, CODAG_E_INVALID_ARGUMENT));
@@ -219,11 +228,15 @@ int resolve_opts(const codag_batch_opts *in, codag_batch_opts *o) {
     return CODAG_OK;
 }
 
+// Workgroups of decode_batch.
+uint32_t batch_blocks(const codag_plan *p) {
+    return (uint32_t)std::max<int64_t>(1, ((int64_t)p->num_cus * p->opts.waves_per_cu) / p->opts.waves_per_block);
+}
+
 template <int TB, uint32_t H, int WPB>
 void launch_decode(codag_plan *p, const BatchArgs &a, const uint32_t *order, unsigned long long *err,
                    hipStream_t s) {
-    uint32_t blocks = (uint32_t)std::max<int64_t>(1, ((int64_t)p->num_cus * p->opts.waves_per_cu) / WPB);
-    hipLaunchKernelGGL((decode_batch<TB, H, WPB>), dim3(blocks), dim3(kWave * WPB), 0, s, a.codecs,
+    hipLaunchKernelGGL((decode_batch<TB, H, WPB>), dim3(batch_blocks(p)), dim3(kWave * WPB), 0, s, a.codecs,
                        a.comp, a.coff, a.out, a.ooff, (uint32_t)a.n, order, p->head,
                        (uint32_t)p->opts.chunks_per_claim, a.status, err, a.ticks);
 }
@@ -252,7 +265,8 @@ void launch_decode_tb(codag_plan *p, const BatchArgs &a, const uint32_t *order,
 
 // Enqueue the whole sequence on s.
 int enqueue(codag_plan *p, const BatchArgs &a, unsigned long long *err, hipStream_t s) {
-    hipLaunchKernelGGL(reset_queue, dim3(1), dim3(kResetThreads), 0, s, p->head, a.codecs, (uint32_t)a.n);
+    hipLaunchKernelGGL(reset_queue, dim3(1), dim3(kResetThreads), 0, s, p->head, a.codecs, (uint32_t)a.n,
+                       batch_blocks(p) * (uint32_t)(p->opts.waves_per_block * p->opts.chunks_per_claim));
     const uint32_t *order = nullptr;
     if (p->opts.order == CODAG_ORDER_GIVEN) {
         order = a.order;
